@@ -2094,14 +2094,18 @@ int grid_upload(mcrt_ctx* ctx, const mcrt_grid_desc* d, hipStream_t st, int32_t*
     UP(lon_s, los.data(), los.size(), dp);
     UP(lon_c, loc.data(), loc.size(), dp);
     UP(vol_r, volr.data(), volr.size(), dp);
-    std::vector<double> faces;
-    faces.reserve((size_t)nlay + 1 + 3 * ((size_t)nlat + 1) + 2 * (size_t)nlon);
-    faces.insert(faces.end(), d->r_edges, d->r_edges + nlay + 1);
+    std::vector<double2> faces;
+    faces.reserve((size_t)nlay + nlat + nlon + 1);
+    for (int k = 0; k < nlay; ++k) faces.push_back(make_double2(d->r_edges[k], d->r_edges[k + 1]));
     gd.lat_base = (int)faces.size();
-    for (int e = 0; e <= nlat; ++e) faces.insert(faces.end(), {lat[e], ls2[e], lc2[e]});
+    for (int j = 0; j < nlat; ++j) faces.push_back(make_double2(lsn[j], lsn[j + 1]));
+    gd.eq_edge = 0;
+    for (int e = 1; e < nlat; ++e)
+        if (lsn[e] != 0.0 && std::fabs(lsn[e]) < 1e-8) gd.eq_edge = e;
     gd.lon_base = (int)faces.size();
-    for (int e = 0; e < nlon; ++e) faces.insert(faces.end(), {los[e], loc[e]});
-    UP(faces, faces.data(), faces.size(), dp);
+    for (int e = 0; e <= nlon; ++e) faces.push_back(make_double2(los[e % nlon], loc[e % nlon]));
+    double2* d2;
+    UP(faces, faces.data(), faces.size(), d2);
     if (borrow) {  // read in place; the caller owns them
         gd.T = d->T;
         gd.P = d->P;

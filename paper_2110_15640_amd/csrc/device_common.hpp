@@ -437,13 +437,12 @@ __device__ __forceinline__ double interp_tp(F lnk, const Bracket& bt, const Brac
 }
 
 
-// Arithmetic of a crossing.  The exact form rounds every product and sum on
-// its own and divides correctly rounded, operation for operation as the FP64
-// oracle; the fast form, taken by the FP32-mixed transport, contracts a
-// product and a sum into one multiply-add and divides through the hardware
-// reciprocal (good to about 5e-8 on gfx950) refined by one Newton step and a
-// residual correction: within an ulp of the rounded quotient, and equal to it
-// on every one of 2^20 random operands over 30 decades tried on the device.
+// Arithmetic of a walk.  The exact form rounds every product and sum on its
+// own and divides and takes roots correctly rounded, as the FP64 oracle; the
+// fast form, taken by the FP32-mixed transport, contracts a product and a sum
+// into one multiply-add.  A packet's path amplifies a last-bit difference of
+// a crossing at every interaction in thick, patchy clouds, so each form's
+// operations are part of what it computes and stay as they are.
 template <bool FAST>
 __host__ __device__ __forceinline__ double wk_mad(double a, double b, double c)
 {
@@ -451,461 +450,411 @@ __host__ __device__ __forceinline__ double wk_mad(double a, double b, double c)
     else return a * b + c;
 }
 
+// a / b from the hardware reciprocal (good to about 5e-8 on gfx950): Newton
+// steps and a residual correction.  One step (fast form) is within an ulp of
+// the rounded quotient; two (exact form) are the steps by which the library's
+// division rounds correctly, without its scaling of the ends of the exponent
+// range, which the operands of a walk (lengths of ~1e9 cm, their squares and
+// differences, direction cosines, extinctions) do not reach.  b = 0 gives a
+// NaN, which callers discard.
 template <bool FAST>
 __host__ __device__ __forceinline__ double wk_div(double a, double b)
 {
-    if constexpr (FAST) {
-        double r = __builtin_amdgcn_rcp(b);
-        r = fma(r, fma(-b, r, 1.0), r);
-        const double qt = a * r;
-        return fma(fma(-b, qt, a), r, qt);
-    } else {
-        return a / b;
-    }
+#if defined(__HIP_DEVICE_COMPILE__) || defined(MCRT_EMULATE_RCP)
+    double r = __builtin_amdgcn_rcp(b);
+    r = fma(r, fma(-b, r, 1.0), r);
+    if constexpr (!FAST) r = fma(r, fma(-b, r, 1.0), r);
+    const double qt = a * r;
+    return fma(fma(-b, qt, a), r, qt);
+#else
+    return a / b;
+#endif
 }
 
-// Square root of x >= 0 (finite).  The fast form refines the hardware
-// reciprocal square root y ~ 1/sqrt(x) by Goldschmidt's iteration (g = x y,
-// h = y/2, r = 1/2 - h g, g <- g + g r, h <- h + h r) and one correction
-// g <- g + (x - g^2) h, which bring it within an ulp of the rounded root
-// (equal to it on 2^20 random operands over 30 decades tried on the device;
-// y is good to about 5e-8); without the library's range scaling, which these
-// operands (squared lengths of ~1e9 cm and their differences) never need.
+// Square root of x (0 for x <= 0) from the hardware reciprocal square root
+// y ~ 1/sqrt(x) by Goldschmidt's iteration (g = x y, h = y/2, r = 1/2 - h g,
+// g <- g + g r, h <- h + h r) and corrections g <- g + (x - g^2) h: one within
+// an ulp (fast form), two correctly rounded (exact form; as the library's
+// root, again without its range scaling).
 template <bool FAST>
 __host__ __device__ __forceinline__ double wk_sqrt(double x)
 {
-    if constexpr (FAST) {
-        const double y = __builtin_amdgcn_rsq(x);
-        double g = x * y, h = 0.5 * y;
-        const double r = fma(-h, g, 0.5);
-        g = fma(g, r, g);
-        h = fma(h, r, h);
-        g = fma(fma(-g, g, x), h, g);
-        return x > 0.0 ? g : 0.0;
-    } else {
-        return sqrt(x);
-    }
+#if defined(__HIP_DEVICE_COMPILE__) || defined(MCRT_EMULATE_RCP)
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    if constexpr (!FAST) g = fma(fma(-g, g, x), h, g);
+    return x > 0.0 ? g : 0.0;
+#else
+    return x > 0.0 ? sqrt(x) : 0.0;
+#endif
+}
+
+// min and max of two non-NaN doubles, one instruction (the library's forms
+// first quiet their operands)
+__host__ __device__ __forceinline__ double wk_min(double a, double b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+#else
+    return a < b ? a : b;
+#endif
+}
+__host__ __device__ __forceinline__ double wk_max(double a, double b)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+#else
+    return a > b ? a : b;
+#endif
 }
 
 // ---------------------------------------------------------------- walker
-// Straight-line walk through the cells from an origin p0 along unit d.  Along
-// a straight line every face surface is met at fixed ray parameters t (a
-// shell or a cone at most twice, a longitude plane once), so the walk keeps
-// the parameters of the current cell's faces and, after a crossing, computes
-// only the faces that are new to the cell: one shell, one cone or one plane.
-// Positions are never advanced step by step (p(t) = p0 + t d), so there is no
-// drift; tie order and entry-face rules are those of exit_distance.
+// Straight-line walk through the cells from an origin p0 along unit d.  Every
+// face surface is met at fixed ray parameters t, so positions are never
+// advanced step by step (p(t) = p0 + t d: no drift).  Of each kind of face
+// only the next one along the walk is kept, because a straight line meets
+// them in a known order:
+//   shells     inward while its nearest point to the centre is ahead and the
+//              next inner sphere is met, then outward for good; the sphere
+//              crossed last on the way in is the first one met on the way out
+//              (its far root is kept);
+//   planes     the longitude grows or shrinks all along a line (the sign of
+//              px dy - py dx), so one edge per cell can be met;
+//   cones      sin(lat) = z / r has one extremum along a line and tends to
+//              dz.  With P the line's nearest point to the centre, q2 = |P|^2
+//              and M = Pz^2 + q2 dz^2, the extremum is a maximum for Pz > 0
+//              and its sin^2(lat) is M / q2.  While it is ahead and reaches
+//              the edge in front (M >= s^2 q2, s the edge's sine), or with no
+//              extremum ahead if dz lies beyond s, that edge is next;
+//              otherwise, after the extremum, the edge behind if dz lies
+//              beyond that.
+// So a step is a minimum of three parameters, and a crossing recomputes the
+// one it used: one square root and one division for whatever kinds of face
+// the lanes of a wave cross.  Ties go to the shell, the cone, the plane.  A
+// slab's walk has shells only.
+//
+// What it replaced kept both roots of both cones, both planes and both shells
+// of the cell (nine parameters) and chose among them at every step.
 struct Walker {
-    double px, py, pz;      // origin
-    double dx, dy, dz;      // unit direction
-    double t;               // distance walked from the origin
-    double B0, C0;          // p0 . d, |p0|^2 (spherical) ; unused for the slab
-    double tout, tin;       // outer-face exit / inner-face hit (INFINITY = none)
-    double tin_far;         // far root of the inner sphere when tin is set: the
-                            // outer face's exit once that sphere is crossed
-    double lo1, lo2;        // lower latitude cone roots on its nappe, ascending
-    double hi1, hi2;        // upper latitude cone roots
-    double tlo, thi;        // lower / upper longitude half-plane hits
+    double px, py, pz;  // origin
+    double dx, dy, dz;  // unit direction
+    double t;           // distance walked from the origin
+    double B0, C0;      // p0 . d, |p0|^2 (spherical)
+    double ts, tc, tp;  // next shell, cone and plane (INFINITY = none)
+    double far;         // while inward: the far root of the sphere at ts
     int i, j, k;
-    int c;                  // cell index (k * nlat + j) * nlon + i, kept as the walk moves
-    int ef;                 // face by which the current cell was entered
+    int c;              // cell index (k * nlat + j) * nlon + i, kept as the walk moves
+    int fl;             // WF_ bits
 };
+enum {
+    WF_INWARD = 1,    // ts is the cell's inner shell
+    WF_UP = 2,        // tc is the row's upper cone
+    WF_EAST = 4,      // the longitude grows along the walk
+    WF_EQ = 8,        // the walk just entered a row at GridDev::eq_edge: wk_row_roots sets tc
+    WF_FROM_LO = 16,  // ... through the row's lower edge
+    WF_FROM_HI = 32   // ... through its upper edge
+};
+enum { X_NONE = 0, X_SHELL = 1, X_CONE = 2, X_PLANE = 3 };
 
-// The faces of a walk's first cell (wk_start); FAST: the fast arithmetic of
-// wk_mad, wk_div and wk_sqrt, otherwise every operation rounded on its own.
-template <bool FAST = false>
-__host__ __device__ __forceinline__ void wk_shells(const GridDev& g, Walker& w, bool need_out, bool need_in)
+__host__ __device__ __forceinline__ double2 wk_face(const GridDev& g, int e) { return g.faces[e]; }
+
+// The latitude edge a walk in row j meets next, rising (up) or falling in
+// latitude; sl, su: the sines of the row's edges.  upper: it is edge j + 1,
+// met while the latitude rises (edge j: while it falls); met: there is one.
+struct ConePick {
+    double s;
+    bool met, upper;
+};
+__host__ __device__ __forceinline__ ConePick wk_cone_pick(const GridDev& g, const Walker& w, bool up, double sl, double su)
 {
-    if (g.geom == 1) {
-        if (need_out) w.tout = w.dz > 0.0 ? fmax(wk_div<FAST>(g.r[w.k + 1] - w.pz, w.dz), w.t) : INFINITY;
-        if (need_in) w.tin = w.dz < 0.0 ? fmax(wk_div<FAST>(g.r[w.k] - w.pz, w.dz), w.t) : INFINITY;
-        return;
-    }
-    if (need_out) {
-        double R = g.r[w.k + 1];
-        double C = wk_mad<FAST>(-R, R, w.C0);
-        double D = wk_mad<FAST>(w.B0, w.B0, -C);
-        if (D < 0.0) D = 0.0;
-        double sq = wk_sqrt<FAST>(D);
-        double far = (w.B0 <= 0.0) ? (-w.B0 + sq) : wk_div<FAST>(-C, w.B0 + sq);
-        w.tout = fmax(far, w.t);
-    }
-    if (need_in) {
-        w.tin = INFINITY;
-        if (w.B0 < 0.0) {
-            double R = g.r[w.k];
-            double C = wk_mad<FAST>(-R, R, w.C0);
-            double D = wk_mad<FAST>(w.B0, w.B0, -C);
-            if (D >= 0.0) {
-                const double q = -w.B0 + wk_sqrt<FAST>(D);
-                double nr = wk_div<FAST>(C, q);
-                if (nr >= w.t || C < 0.0) {
-                    w.tin = fmax(nr, w.t);
-                    w.tin_far = q;
-                }
-            }
-        }
-    }
+    ConePick p;
+    const double q2 = fma(-w.B0, w.B0, w.C0), Pz = fma(-w.B0, w.dz, w.pz);
+    const double M = fma(Pz, Pz, (q2 * w.dz) * w.dz);
+    const bool turn = up ? Pz > 0.0 : Pz < 0.0;         // the extremum is ahead
+    const double sf = up ? su : sl, sb = up ? sl : su;  // the edges in front and behind
+    const bool top = w.j + 1 < g.nlat, bottom = w.j > 0;  // a pole is no face
+    const bool past_f = up ? w.dz > sf : w.dz < sf, past_b = up ? w.dz < sb : w.dz > sb;
+    const bool front = (up ? top : bottom) && (turn ? fma(-(sf * sf), q2, M) >= 0.0 : past_f);
+    const bool back = !front && turn && (up ? bottom : top) && past_b;
+    p.s = front ? sf : sb;
+    p.met = front || back;
+    p.upper = up == front;
+    return p;
 }
+
+// Whether row j lies at the edge whose cone cannot be told from the equator.
+__host__ __device__ __forceinline__ bool wk_at_eq(const GridDev& g, int j) { return j == g.eq_edge || j + 1 == g.eq_edge; }
 
 // Coefficients of the latitude cone z^2 cos^2(lat) = (x^2 + y^2) sin^2(lat)
 // along p0 + t d: a t^2 + 2 b t + c = 0.  The exact form evaluates them as
-// written; the fast form (FP32-mixed transport) uses cos^2 + sin^2 = 1 and
-// |d| = 1, i.e. a = dz^2 - sin^2, b = pz dz - (p0.d) sin^2,
-// c = pz^2 - |p0|^2 sin^2 (three multiply-adds instead of fifteen operations).
+// written; the fast form uses cos^2 + sin^2 = 1 and |d| = 1, i.e.
+// a = dz^2 - sin^2, b = pz dz - (p0.d) sin^2, c = pz^2 - |p0|^2 sin^2.
 template <bool FAST>
-__host__ __device__ __forceinline__ void wk_cone_coef(const GridDev& g, const Walker& w, int e, double& a, double& b,
-                                                      double& c)
+__host__ __device__ __forceinline__ void wk_cone_coef(const Walker& w, double s, double c2, double& a, double& b, double& c)
 {
-    const double s2 = g.lat_s2[e];
+    const double s2 = s * s;
     if constexpr (FAST) {
         a = fma(w.dz, w.dz, -s2);
         b = fma(w.pz, w.dz, -(w.B0 * s2));
         c = fma(w.pz, w.pz, -(w.C0 * s2));
     } else {
-        const double c2 = g.lat_c2[e];
         a = w.dz * w.dz * c2 - (w.dx * w.dx + w.dy * w.dy) * s2;
         b = w.pz * w.dz * c2 - (w.px * w.dx + w.py * w.dy) * s2;
         c = w.pz * w.pz * c2 - (w.px * w.px + w.py * w.py) * s2;
     }
 }
 
-// Roots of the latitude cone of edge e on the nappe of its sign (or the
-// equatorial plane), ascending, INFINITY where absent.
-template <bool FAST = false>
-__host__ __device__ __forceinline__ void wk_cone(const GridDev& g, const Walker& w, int e, double& r1, double& r2)
+// Root of a face as a quotient: num * (1 / den) in the fast form, num / den
+// in the exact one.
+template <bool FAST>
+__host__ __device__ __forceinline__ double wk_root(double num, double den)
 {
-    r1 = INFINITY;
-    r2 = INFINITY;
-    double tb = g.lat[e];
-    if (tb == 0.0) {
-        if (w.dz != 0.0) r1 = wk_div<FAST>(-w.pz, w.dz);
-        return;
+    if constexpr (FAST) return num * wk_div<true>(1.0, den);
+    else return wk_div<false>(num, den);
+}
+
+// The root at which the picked edge is met, q/a (first) or c/q of the cone's
+// quadratic with q = -(b + sign(b) sqrt(disc)), as a quotient: of
+// (-b -+ sqrt(disc)) / a the one of + sign(s) is met rising.
+// The equator (s = 0) is the plane z = 0.
+template <bool FAST>
+__host__ __device__ __forceinline__ bool wk_cone_root(const Walker& w, const ConePick& p, double a, double b, double c,
+                                                      double sq, double& num, double& den)
+{
+    if (p.s == 0.0) {
+        num = -w.pz;
+        den = w.dz;
+        return w.dz != 0.0;
     }
-    double a, b, c;
-    wk_cone_coef<FAST>(g, w, e, a, b, c);
-    double x0 = INFINITY, x1 = INFINITY;
+    const bool first = (b >= 0.0) == ((p.s > 0.0) != p.upper);
     if (a == 0.0) {
-        if (b != 0.0) x0 = wk_div<FAST>(-c, 2.0 * b);
-    } else {
-        double disc = wk_mad<FAST>(b, b, -(a * c));
-        if (disc >= 0.0) {
-            double sq = wk_sqrt<FAST>(disc);
-            double q = -(b + (b >= 0.0 ? sq : -sq));
-            if constexpr (FAST) {  // both roots from one reciprocal, as in wk_cross_end
-                if (q != 0.0) {
-                    const double inv = wk_div<true>(1.0, a * q);
-                    x0 = (q * q) * inv;
-                    x1 = (c * a) * inv;
-                } else {
-                    x0 = 0.0;
-                }
-            } else {
-                x0 = wk_div<FAST>(q, a);
-                if (q != 0.0) x1 = wk_div<FAST>(c, q);
-            }
-        }
+        num = -c;
+        den = 2.0 * b;
+        return b != 0.0;
     }
-    const double z0 = wk_mad<FAST>(x0, w.dz, w.pz), z1 = wk_mad<FAST>(x1, w.dz, w.pz);
-    bool ok0 = x0 < INFINITY && (tb > 0.0 ? (z0 > 0.0) : (z0 < 0.0));
-    bool ok1 = x1 < INFINITY && (tb > 0.0 ? (z1 > 0.0) : (z1 < 0.0));
-    if (!ok0) x0 = INFINITY;
-    if (!ok1) x1 = INFINITY;
-    r1 = fmin(x0, x1);
-    r2 = fmax(x0, x1);
-    if (!(r1 < INFINITY)) r2 = INFINITY;
+    const double q = -(b + (b >= 0.0 ? sq : -sq));
+    if constexpr (FAST) {
+        num = first ? q * q : c * a;
+        den = a * q;
+    } else {
+        num = first ? q : c;
+        den = first ? a : q;
+    }
+    return den != 0.0;
 }
 
-// Hit of the longitude half-plane of edge e (upper = the cell's upper face).
-template <bool FAST = false>
-__host__ __device__ __forceinline__ double wk_plane(const GridDev& g, const Walker& w, int e, bool upper)
+// cos^2 of the picked latitude edge (read by the exact form only)
+template <bool FAST>
+__host__ __device__ __forceinline__ double wk_cos2(const GridDev& g, const Walker& w, const ConePick& p)
 {
-    double sb = g.lon_s[e], cb = g.lon_c[e];
-    double nx = -sb, ny = cb;
-    double dn = wk_mad<FAST>(w.dx, nx, w.dy * ny);
-    if (upper ? !(dn > 0.0) : !(dn < 0.0)) return INFINITY;
-    double th = fmax(wk_div<FAST>(-wk_mad<FAST>(w.px, nx, w.py * ny), dn), w.t);
-    double hx = wk_mad<FAST>(th, w.dx, w.px), hy = wk_mad<FAST>(th, w.dy, w.py);
-    return (wk_mad<FAST>(cb, hx, sb * hy) > 0.0) ? th : INFINITY;
+    if constexpr (FAST) return 0.0;
+    else return g.lat_c2[w.j + (p.upper ? 1 : 0)];
 }
 
-template <bool FAST = false>
-__host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, double px, double py, double pz, double dx,
-                                         double dy, double dz, int i, int j, int k, int ef)
+// Start of a walk at (px, py, pz) in cell (i, j, k) along unit d.
+template <bool FAST>
+__host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, double px, double py, double pz,
+                                                  double dx, double dy, double dz, int i, int j, int k)
 {
     w.px = px; w.py = py; w.pz = pz;
     w.dx = dx; w.dy = dy; w.dz = dz;
     w.t = 0.0;
     w.i = i; w.j = j; w.k = k;
     w.c = (k * g.nlat + j) * g.nlon + i;
-    w.ef = ef;
-    w.B0 = px * dx + py * dy + pz * dz;
-    w.C0 = px * px + py * py + pz * pz;
-    wk_shells<FAST>(g, w, true, true);
-    w.lo1 = w.lo2 = w.hi1 = w.hi2 = INFINITY;
-    w.tlo = w.thi = INFINITY;
-    if (g.geom == 1) return;
-    if (j > 0) wk_cone<FAST>(g, w, j, w.lo1, w.lo2);
-    if (j < g.nlat - 1) wk_cone<FAST>(g, w, j + 1, w.hi1, w.hi2);
-    if (g.nlon > 1) {
-        w.tlo = wk_plane<FAST>(g, w, i, false);
-        w.thi = wk_plane<FAST>(g, w, i + 1 == g.nlon ? 0 : i + 1, true);
-    }
-}
-
-// Next cone root at or after t; roots of the cone just crossed must lie more
-// than 1e-9 |p| ahead (the same entry-face tolerance as exit_distance).
-__host__ __device__ __forceinline__ double wk_next_root(double r1, double r2, double t, double lo)
-{
-    if (r1 >= lo) return r1;
-    if (r2 >= lo) return r2;
-    return INFINITY;
-}
-
-// Parameter and face of the next crossing (ties: outer, inner, lat-low,
-// lat-high, lon-low, lon-high).
-template <bool FAST = false>
-__host__ __device__ __forceinline__ int wk_next(const GridDev& g, const Walker& w, double& tf, double r_top = 0.0)
-{
-    double best = w.tout;
-    int face = w.tout < INFINITY ? F_OUT : F_NONE;
-    if (w.tin < best) { best = w.tin; face = F_IN; }
+    w.tc = w.tp = INFINITY;
+    w.far = 0.0;
+    const double2 fr = wk_face(g, k);
     if (g.geom == 1) {
-        tf = best;
-        return face;
+        w.B0 = w.C0 = 0.0;
+        w.fl = dz > 0.0 ? 0 : WF_INWARD;
+        const double x = wk_div<FAST>((dz > 0.0 ? fr.y : fr.x) - pz, dz);
+        w.ts = dz != 0.0 ? wk_max(x, 0.0) : INFINITY;
+        return;
     }
-    // entry-face tolerance 1e-9 |p|, with |p| bounded by the cell's outer
-    // radius (it only separates a re-found root of the cone just crossed,
-    // ~1e-16 |p| away, from genuine ones); the fast form bounds |p| by the
-    // top of the grid, r_top (the caller's, no gather per step)
-    double lo = w.t;
-    if (w.ef == F_LATLO || w.ef == F_LATHI) lo = w.t + 1e-9 * (FAST ? r_top : g.r[w.k + 1]);
-    double a = wk_next_root(w.lo1, w.lo2, w.t, w.ef == F_LATLO ? lo : w.t);
-    if (a < best) { best = a; face = F_LATLO; }
-    double b = wk_next_root(w.hi1, w.hi2, w.t, w.ef == F_LATHI ? lo : w.t);
-    if (b < best) { best = b; face = F_LATHI; }
-    if (w.tlo < best) { best = w.tlo; face = F_LONLO; }
-    if (w.thi < best) { best = w.thi; face = F_LONHI; }
-    tf = best;
-    return face;
+    const bool east = px * dy - py * dx > 0.0;
+    const double2 fc = wk_face(g, g.lat_base + j);
+    const double2 fp = wk_face(g, g.lon_base + i + (east ? 1 : 0));
+    const double B = px * dx + py * dy + pz * dz;
+    const double C0 = px * px + py * py + pz * pz;
+    w.B0 = B;
+    w.C0 = C0;
+    // the inner sphere where the walk goes inward and meets it, else the outer one
+    const double Ci = wk_mad<FAST>(-fr.x, fr.x, C0), Di = wk_mad<FAST>(B, B, -Ci);
+    const double Co = wk_mad<FAST>(-fr.y, fr.y, C0), Do = wk_mad<FAST>(B, B, -Co);
+    bool inward = B < 0.0 && Di >= 0.0;
+    const double sq = wk_sqrt<FAST>(inward ? Di : Do);
+    const double q = B <= 0.0 ? -B + sq : B + sq;
+    const double x = wk_div<FAST>(inward ? Ci : -Co, q);
+    w.ts = wk_max(inward || B > 0.0 ? x : q, 0.0);
+    w.far = q;
+    w.fl = (inward ? WF_INWARD : 0) | (east ? WF_EAST : 0);
+    double num, den;
+    if (g.nlat > 1) {
+        const double q2 = fma(-B, B, C0), Pz = fma(-B, dz, pz);
+        const bool up = fma(dz, q2, -(Pz * B)) > 0.0;  // the sign of d sin(lat) / dt
+        const ConePick p = wk_cone_pick(g, w, up, fc.x, fc.y);
+        w.fl |= p.upper ? WF_UP : 0;
+        if (g.eq_edge > 0 && wk_at_eq(g, j)) w.fl |= WF_EQ;
+        double a, b, c;
+        wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
+        const double sqc = wk_sqrt<FAST>(wk_mad<FAST>(b, b, -(a * c)));
+        const bool ok = wk_cone_root<FAST>(w, p, a, b, c, sqc, num, den);
+        double r;
+        if constexpr (FAST) r = (p.s == 0.0 || a == 0.0) ? wk_div<true>(num, den) : wk_root<true>(num, den);
+        else r = wk_root<false>(num, den);
+        w.tc = p.met && ok ? wk_max(r, 0.0) : INFINITY;
+    }
+    if (g.nlon > 1) {
+        const double nx = -fp.x, ny = fp.y;
+        const double dn = wk_mad<FAST>(dx, nx, dy * ny);
+        const double r = wk_div<FAST>(-wk_mad<FAST>(px, nx, py * ny), dn);
+        w.tp = (east ? dn > 0.0 : dn < 0.0) ? wk_max(r, 0.0) : INFINITY;
+    }
 }
 
-// Move to parameter tf on face f, enter the neighbour cell and compute the
-// faces that are new to it.  Returns false when the walk left the grid
-// (k == nlay: top; k < 0: surface).
-//
-// Every crossing needs exactly one new surface: the next outer sphere
-// (outward), the next inner sphere (inward; the new outer face is the sphere
-// just crossed, whose far root was kept with tin), the next cone, or the next
-// longitude plane.  All of them are met where A t^2 + 2 B t + C = 0 (planes
-// and the equator: the linear B2 t + C = 0), so one branch-free body solves
-// that equation for every lane of a wave, whatever face kind it crosses, and
-// per-kind selects pick the roots.  The arithmetic of each kind is the same,
-// operation for operation, as in wk_shells, wk_cone and wk_plane (in the
-// exact form; FAST: see wk_mad and wk_div).
-// The grid-table values a crossing reads, loaded by wk_cross_begin so that a
-// caller can issue other loads (the extinction gather) before the crossing's
-// arithmetic in wk_cross_end waits for them: v1 = the new sphere's radius,
-// the cone's latitude or the plane's sin(lon); v2 = the cone's sin^2(lat) or
-// the plane's cos(lon); v3 = the cone's cos^2(lat) (exact form only).
+// Parameter and kind of the next crossing.
+__host__ __device__ __forceinline__ int wk_next(const Walker& w, double& tf)
+{
+    tf = wk_min(wk_min(w.ts, w.tc), w.tp);
+    return w.ts <= tf ? (tf < INFINITY ? X_SHELL : X_NONE) : (w.tc <= tf ? X_CONE : X_PLANE);
+}
+
+// The face-table values a crossing reads, loaded by wk_cross_begin so that a
+// caller can issue other loads before the crossing's arithmetic in
+// wk_cross_end waits for them.
 struct CrossIn {
-    double v1, v2, v3;
+    double2 f;
     bool inside;
 };
 
-// Index update and table loads of a crossing, without branches: every lane
-// of a wave runs the same instructions whatever face it crosses (a lane with
-// no face, f < 0, keeps its indices and loads in-range entries it ignores).
-template <bool FAST = false>
-__host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Walker& w, int f, double tf)
+// Index update and table load of a crossing at tf of kind x (a face), without
+// branches.
+__host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Walker& w, int x, double tf)
 {
-    CrossIn x;
+    CrossIn in;
     w.t = tf;
-    const bool valid = f >= 0;
-    const bool shell = valid && f <= F_IN, cone = f == F_LATLO || f == F_LATHI, plane = f == F_LONLO || f == F_LONHI;
-    const bool outward = f == F_OUT, down = f == F_LATLO, west = f == F_LONLO;
-    const int dk = shell ? (outward ? 1 : -1) : 0;
-    const int dj = cone ? (down ? -1 : 1) : 0;
-    const bool wrap = west ? (w.i == 0) : (w.i + 1 == g.nlon);
-    const int ni = west ? (w.i == 0 ? g.nlon - 1 : w.i - 1) : (w.i + 1 == g.nlon ? 0 : w.i + 1);
-    const int di = plane ? (west ? (wrap ? g.nlon - 1 : -1) : (wrap ? 1 - g.nlon : 1)) : 0;
-    w.k += dk;
-    w.j += dj;
-    w.i = plane ? ni : w.i;
-    w.c += dk * (g.nlon * g.nlat) + dj * g.nlon + di;
-    w.ef = shell ? (outward ? F_IN : F_OUT)
-                 : (cone ? (down ? F_LATHI : F_LATLO) : (plane ? (west ? F_LONHI : F_LONLO) : w.ef));
-    x.inside = valid && w.k < g.nlay && w.k >= 0;
-    const int kr = outward ? w.k + 1 : w.k;
-    const int kk = kr < 0 ? 0 : (kr > g.nlay ? g.nlay : kr);
-    const int e = down ? w.j : w.j + 1;
-    const bool has = down ? w.j > 0 : w.j < g.nlat - 1;
-    const int ee = g.lat_base + 3 * ((cone && has) ? e : 0);
-    const int ep = g.lon_base + 2 * (west ? w.i : (w.i + 1 == g.nlon ? 0 : w.i + 1));
-    const int o1 = shell ? kk : (cone ? ee : ep);
-    const int o2 = (cone ? ee : ep) + 1;
-    x.v1 = g.faces[o1];
-    x.v2 = g.faces[o2];
-    x.v3 = FAST ? 0.0 : g.faces[ee + 2];
-    return x;
+    const bool shell = x == X_SHELL, cone = x == X_CONE;
+    const int dk = (w.fl & WF_INWARD) ? -1 : 1, dj = (w.fl & WF_UP) ? 1 : -1, east = (w.fl & WF_EAST) ? 1 : 0;
+    const int ie = w.i + 1 == g.nlon ? 0 : w.i + 1, iw = (w.i == 0 ? g.nlon : w.i) - 1;
+    const int di = (east ? ie : iw) - w.i;
+    w.k += shell ? dk : 0;
+    w.j += cone ? dj : 0;
+    w.i += shell || cone ? 0 : di;
+    w.c += shell ? dk * (g.nlon * g.nlat) : (cone ? dj * g.nlon : di);
+    in.inside = (unsigned)w.k < (unsigned)g.nlay;
+    in.f = wk_face(g, shell ? (in.inside ? w.k : 0) : (cone ? g.lat_base + w.j : g.lon_base + w.i + east));
+    return in;
 }
 
-template <bool FAST = false>
-__host__ __device__ __forceinline__ bool wk_cross_end(const GridDev& g, Walker& w, int f, const CrossIn& x)
+// The face that replaces the one just crossed.
+template <bool FAST>
+__host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& w, int x, const CrossIn& in)
 {
-    if (!x.inside) return false;
-    const bool shell = f <= F_IN, cone = f == F_LATLO || f == F_LATHI;
-    const bool outward = f == F_OUT, down = f == F_LATLO, west = f == F_LONLO;
-    const bool slab = g.geom == 1;
-    // the new surface: coefficients of A t^2 + 2 B t + C (A = 0: B2 t + C)
-    double A = 0.0, B = 0.0, C = 0.0, B2 = 0.0;
-    bool has = true;     // a surface to intersect at all
-    bool equator = false;
-    double tb = 0.0, sb = 0.0, cb = 0.0;
-    if (shell) {
-        const double R = x.v1;
-        has = outward || slab || w.B0 < 0.0;
-        if (slab) {
-            B2 = w.dz;
-            C = w.pz - R;
-        } else {
-            A = 1.0;
-            B = w.B0;
-            C = wk_mad<FAST>(-R, R, w.C0);
-        }
-    } else if (cone) {
-        has = down ? w.j > 0 : w.j < g.nlat - 1;
-        tb = x.v1;
-        equator = tb == 0.0;
-        if (equator) {
-            B2 = w.dz;
-            C = w.pz;
-        } else {
-            const double s2 = x.v2;
-            if constexpr (FAST) {  // as wk_cone_coef's fast form
-                A = fma(w.dz, w.dz, -s2);
-                B = fma(w.pz, w.dz, -(w.B0 * s2));
-                C = fma(w.pz, w.pz, -(w.C0 * s2));
-            } else {
-                const double c2 = x.v3;
-                A = wk_mad<FAST>(w.dz * w.dz, c2, -(wk_mad<FAST>(w.dx, w.dx, w.dy * w.dy) * s2));
-                B = wk_mad<FAST>(w.pz * w.dz, c2, -(wk_mad<FAST>(w.px, w.dx, w.py * w.dy) * s2));
-                C = wk_mad<FAST>(w.pz * w.pz, c2, -(wk_mad<FAST>(w.px, w.px, w.py * w.py) * s2));
-            }
-            B2 = 2.0 * B;
-        }
-    } else {
-        sb = x.v1;
-        cb = x.v2;
-        const double nx = -sb, ny = cb;
-        const double dn = wk_mad<FAST>(w.dx, nx, w.dy * ny);
-        has = west ? dn < 0.0 : dn > 0.0;
-        B2 = dn;
-        C = wk_mad<FAST>(w.px, nx, w.py * ny);
+    const bool shell = x == X_SHELL, cone = x == X_CONE;
+    const bool inward = (w.fl & WF_INWARD) != 0;
+    const double R = inward ? in.f.x : in.f.y;
+    if (g.geom == 1) {
+        w.ts = wk_max(wk_div<FAST>(R - w.pz, w.dz), w.t);
+        return;
     }
-    // one solve for every lane
-    const bool quad = A != 0.0;
-    const double D = wk_mad<FAST>(B, B, -(A * C));
-    const double sq = wk_sqrt<FAST>(fmax(D, 0.0));
-    const bool neg = cone ? B >= 0.0 : B > 0.0;  // the sign rule of each kind at B = 0
-    const double q = neg ? -(B + sq) : (-B + sq);
-    // one division gives the near root q / A of a quadric (a shell has A = 1)
-    // or the root -C / B2 of a linear face, whichever the lane has
-    double rd, x1q;
-    if constexpr (FAST) {
-        // both roots of a quadric from one reciprocal, 1/(A q): q/A = q^2/(A q)
-        // and C/q = C A/(A q); a linear face's root -C/B2 from 1/B2
-        const bool qz = quad && q == 0.0;
-        const double den = quad ? (qz ? A : A * q) : B2;
-        const double inv = wk_div<true>(1.0, den);
-        rd = quad ? (qz ? 0.0 : (q * q) * inv) : -C * inv;
-        x1q = (quad && !qz) ? (C * A) * inv : INFINITY;
-    } else {
-        rd = wk_div<FAST>(quad ? q : -C, quad ? A : B2);
-        x1q = (quad && q != 0.0) ? wk_div<FAST>(C, q) : INFINITY;
-    }
-    const double x0q = rd;
-    const double xl = (!quad && B2 != 0.0) ? rd : INFINITY;
-    if (shell) {
-        if (slab) {
-            const double x = fmax(wk_div<FAST>(-C, B2), w.t);  // (R - pz) / dz
-            if (outward) {
-                w.tout = w.dz > 0.0 ? x : INFINITY;
-                w.tin = INFINITY;
-            } else {
-                w.tout = INFINITY;
-                w.tin = w.dz < 0.0 ? x : INFINITY;
-            }
-            return true;
-        }
-        if (outward) {  // far root of the next outer sphere; the sphere crossed is behind
-            w.tout = fmax(B > 0.0 ? x1q : x0q, w.t);
-            w.tin = INFINITY;
-        } else {        // outer face: the sphere just crossed; inner face: the next sphere, if hit
-            w.tout = fmax(w.tin_far, w.t);
-            w.tin = INFINITY;
-            if (has && D >= 0.0 && (x1q >= w.t || C < 0.0)) {
-                w.tin = fmax(x1q, w.t);
-                w.tin_far = q;
-            }
-        }
-        return true;
-    }
+    // a t^2 + 2 b t + c of the shell or cone
+    double b = w.B0, c = wk_mad<FAST>(-R, R, w.C0), a = 1.0, D;
+    ConePick p{};
     if (cone) {
-        double r1 = INFINITY, r2 = INFINITY;
-        if (has) {
-            if (equator) {
-                r1 = w.dz != 0.0 ? xl : INFINITY;
-            } else {
-                double x0 = INFINITY, x1 = INFINITY;
-                if (!quad) {
-                    x0 = B != 0.0 ? rd : INFINITY;
-                } else if (D >= 0.0) {
-                    x0 = x0q;
-                    x1 = x1q;
-                }
-                const bool ok0 = x0 < INFINITY && (tb > 0.0 ? (wk_mad<FAST>(x0, w.dz, w.pz) > 0.0)
-                                                            : (wk_mad<FAST>(x0, w.dz, w.pz) < 0.0));
-                const bool ok1 = x1 < INFINITY && (tb > 0.0 ? (wk_mad<FAST>(x1, w.dz, w.pz) > 0.0)
-                                                            : (wk_mad<FAST>(x1, w.dz, w.pz) < 0.0));
-                if (!ok0) x0 = INFINITY;
-                if (!ok1) x1 = INFINITY;
-                r1 = fmin(x0, x1);
-                r2 = fmax(x0, x1);
-                if (!(r1 < INFINITY)) r2 = INFINITY;
+        const bool up = (w.fl & WF_UP) != 0;
+        p = wk_cone_pick(g, w, up, in.f.x, in.f.y);
+        w.fl = (w.fl & ~WF_UP) | (p.upper ? WF_UP : 0);
+        if (g.eq_edge > 0 && wk_at_eq(g, w.j)) w.fl |= WF_EQ | (up ? WF_FROM_LO : WF_FROM_HI);
+        wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
+        D = wk_mad<FAST>(b, b, -(a * c));
+    } else {
+        D = wk_mad<FAST>(b, b, -c);
+    }
+    const double sq = wk_sqrt<FAST>(D);
+    const double q = b > 0.0 ? -(b + sq) : -b + sq;  // of the shell
+    double num, den;
+    bool met = true;
+    if (shell) {
+        const bool first = !inward && !(b > 0.0);  // far root of a sphere whose nearest point is still ahead
+        if constexpr (FAST) {
+            num = first ? q * q : c;
+            den = q;
+        } else {
+            num = first ? q : c;
+            den = first ? 1.0 : q;
+        }
+        met = den != 0.0;
+    } else if (cone) {
+        met = wk_cone_root<FAST>(w, p, a, b, c, sq, num, den);
+        met = met && p.met;
+    } else {
+        const double nx = -in.f.x, ny = in.f.y;
+        den = wk_mad<FAST>(w.dx, nx, w.dy * ny);
+        num = -wk_mad<FAST>(w.px, nx, w.py * ny);
+        met = (w.fl & WF_EAST) ? den > 0.0 : den < 0.0;
+    }
+    const double r = wk_root<FAST>(num, den);
+    if (shell) {
+        const bool hit = D >= 0.0 && (r >= w.t || c < 0.0);  // (a sphere met on the way out always is)
+        w.ts = wk_max(!inward || hit ? (met ? r : 0.0) : w.far, w.t);
+        if (inward && !hit) w.fl &= ~WF_INWARD;
+        w.far = q;
+    } else {
+        const double v = met ? wk_max(r, w.t) : INFINITY;
+        if (cone) w.tc = v;
+        else w.tp = v;
+    }
+}
+
+// tc of a walk that has just entered a row at the edge eq_edge.  Where an edge
+// lies within rounding of the equator without being it (sin^2 < 1e-16), its
+// two cone roots are one to rounding and which nappe each lies on is decided
+// by rounding, so that edge may be met once, twice or not at all.  The
+// results of such grids are those of taking, of the roots of both edges that
+// fall on their nappe, the first one ahead (past 1e-9 of the radius for the
+// edge just crossed).
+template <bool FAST>
+__host__ __device__ __forceinline__ void wk_row_roots(const GridDev& g, Walker& w)
+{
+    const double tol = 1e-9 * g.faces[g.nlay - 1].y;
+    const double2 f = wk_face(g, g.lat_base + w.j);
+    double best = INFINITY;
+    bool upper = false;
+    for (int e = 0; e < 2; ++e) {
+        const int je = w.j + e;
+        if (je == 0 || je == g.nlat) continue;
+        const double s = e ? f.y : f.x;
+        double a, b, c;
+        wk_cone_coef<FAST>(w, s, FAST ? 0.0 : g.lat_c2[je], a, b, c);
+        const double disc = wk_mad<FAST>(b, b, -(a * c));
+        if (!(disc >= 0.0) || a == 0.0) continue;
+        const double sq = wk_sqrt<FAST>(disc);
+        const double q = -(b + (b >= 0.0 ? sq : -sq));
+        double x0 = 0.0, x1 = INFINITY;
+        if (q != 0.0) {
+            x0 = FAST ? wk_root<FAST>(q * q, a * q) : wk_root<FAST>(q, a);
+            x1 = FAST ? wk_root<FAST>(c * a, a * q) : wk_root<FAST>(c, q);
+        }
+        const double lo = (w.fl & (e ? WF_FROM_HI : WF_FROM_LO)) ? w.t + tol : w.t;
+        for (int m = 0; m < 2; ++m) {
+            const double x = m ? x1 : x0, z = wk_mad<FAST>(x, w.dz, w.pz);
+            if (x < INFINITY && x >= lo && (s > 0.0 ? z > 0.0 : z < 0.0) && x < best) {
+                best = x;
+                upper = e == 1;
             }
         }
-        // the cone crossed becomes the opposite face of the new cell
-        const double k1 = down ? w.lo1 : w.hi1, k2 = down ? w.lo2 : w.hi2;
-        if (down) {
-            w.hi1 = k1; w.hi2 = k2;
-            w.lo1 = r1; w.lo2 = r2;
-        } else {
-            w.lo1 = k1; w.lo2 = k2;
-            w.hi1 = r1; w.hi2 = r2;
-        }
-        return true;
     }
-    // longitude half-plane (the one crossed is behind the ray: never met again)
-    double th = INFINITY;
-    if (has) {
-        th = fmax(xl, w.t);
-        const double hx = wk_mad<FAST>(th, w.dx, w.px), hy = wk_mad<FAST>(th, w.dy, w.py);
-        if (!(wk_mad<FAST>(cb, hx, sb * hy) > 0.0)) th = INFINITY;
-    }
-    w.tlo = west ? th : INFINITY;
-    w.thi = west ? INFINITY : th;
-    return true;
+    w.tc = best;
+    w.fl = (w.fl & ~(WF_UP | WF_EQ | WF_FROM_LO | WF_FROM_HI)) | (upper ? WF_UP : 0);
 }
-
-template <bool FAST = false>
-__host__ __device__ __forceinline__ bool wk_cross(const GridDev& g, Walker& w, int f, double tf)
-{
-    const CrossIn x = wk_cross_begin<FAST>(g, w, f, tf);
-    return wk_cross_end<FAST>(g, w, f, x);
-}
-
-__host__ __device__ __forceinline__ int wk_cell(const GridDev& /*g*/, const Walker& w) { return w.c; }
 
 }  // namespace dev
 }  // namespace mcrt

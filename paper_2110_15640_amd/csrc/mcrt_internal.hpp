@@ -28,11 +28,13 @@ struct GridDev {
     const double* lon_c;   // cos(lon edge) [nlon]
     const double* vol_r;   // (r_{k+1}^3 - r_k^3)/3 [nlay]
     // the edge values a crossing reads, in one array so that one base and a
-    // per-lane offset reach any of them: r[k] at k; (lat, sin^2, cos^2) of
-    // latitude edge e at lat_base + 3 e; (sin, cos) of longitude edge e at
-    // lon_base + 2 e
-    const double* faces;
+    // per-lane offset reach any of them with one 16-byte load: the layer's
+    // (r[k], r[k + 1]) at k; (sin lat[j], sin lat[j + 1]) of row j at
+    // lat_base + j; (sin, cos) of longitude edge e (edge nlon = edge 0) at
+    // lon_base + e
+    const double2* faces;
     int lat_base, lon_base;
+    int eq_edge;  // latitude edge within rounding of the equator but not on it (0 = none)
     const float* T;
     const float* P;
     const double* rho;

@@ -27,6 +27,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "mcrt_internal.hpp"
 
@@ -44,8 +46,7 @@ constexpr int kProbeDone = 15, kTauSet = 14;
 enum { E_INTERACT = 0, E_ESCAPE = 1, E_SURFACE = 2, E_LOST = 3, E_PEEL_DONE = 4 };
 // Birth record of a packet, kept in the counter columns of its row until the
 // packet dies: position, direction, weight, packed cell (i | j << 11 | k << 21)
-// * 8 + (entry face + 1) (-1: nothing emits), then the index of the solve
-// whose optics it uses;
+// (-1: nothing emits), then the index of the solve whose optics it uses;
 // with a Lambert floor, the weight the floor has absorbed so far; with
 // forced interactions, the unscattered fractions booked so far to the floor
 // (B_SURF) and to escape (B_FESC).
@@ -67,7 +68,7 @@ struct ColdLDS {
     double W0[kTPB], w_rr[kTPB];
     unsigned long long gid[kTPB];
     uint32_t ijk[kTPB];   // event cell: i | j << 11 | k << 21
-    uint32_t st[kTPB];    // observer:4 | birth:1 | smode:1 | entry face + 1:3 | capped:1 | lost:1 | surface:1 | solve:20
+    uint32_t st[kTPB];    // observer:4 | birth:1 | smode:1 | 3 unused | capped:1 | lost:1 | surface:1 | solve:20
     uint32_t e[kTPB];
     int nint[kTPB];
 };
@@ -112,8 +113,6 @@ struct Lane {
     __device__ Bits o() { return Bits{&C->st[t], 0, 0xFu}; }
     __device__ Bits birth() { return Bits{&C->st[t], 4, 0x1u}; }
     __device__ Bits smode() { return Bits{&C->st[t], 5, 0x1u}; }
-    __device__ int sef() { return (int)((C->st[t] >> 6) & 0x7u) - 1; }
-    __device__ void set_sef(int ef) { Bits{&C->st[t], 6, 0x7u} = ef + 1; }
     __device__ Bits ncapped() { return Bits{&C->st[t], 9, 0x1u}; }
     __device__ Bits nlost() { return Bits{&C->st[t], 10, 0x1u}; }
     __device__ Bits surf() { return Bits{&C->st[t], 11, 0x1u}; }  // the event is a reflection by the floor
@@ -143,12 +142,9 @@ __device__ __forceinline__ double ld(const void* p, int c)
     return ((gdouble*)p)[c];
 }
 
-// Address of cell c's value in a per-cell array of the precision's type.
+// The stored type of the optical properties.
 template <bool MIXED>
-__device__ __forceinline__ const void* cell_addr(const void* p, int c)
-{
-    return MIXED ? (const void*)((const float*)p + c) : (const void*)((const double*)p + c);
-}
+using Prop = typename std::conditional<MIXED, float, double>::type;
 
 // Write the packet's row: its peel-off sums, then the counters; `kind` says
 // where its remaining weight went.  EXT (here and below): the kernel form
@@ -210,7 +206,6 @@ __device__ __forceinline__ void start_walk(Lane& L, const GridDev& g, const Batc
                                            bool flight)
 {
     double dx, dy, dz;
-    int ef;
     if constexpr (!EXT) {
         if (flight) {
             const SolveDev& S = A.solves[L.solve()];
@@ -219,13 +214,11 @@ __device__ __forceinline__ void start_walk(Lane& L, const GridDev& g, const Batc
             dx = L.sdx();
             dy = L.sdy();
             dz = L.sdz();
-            ef = L.sef();
         } else {
             observer(L, A, sobs, dx, dy, dz);
             L.tau = 0.0;
-            ef = F_NONE;
         }
-        wk_start<MIXED>(g, L.w, L.sx(), L.sy(), L.sz(), dx, dy, dz, L.si(), L.sj(), L.sk(), ef);
+        wk_start<MIXED>(g, L.w, L.sx(), L.sy(), L.sz(), dx, dy, dz, L.si(), L.sj(), L.sk());
         L.ncw = 0;
         L.mode = flight ? M_FLIGHT : M_PEEL;
         if (!flight && g.geom == 1 && !(dz > 0.0)) {  // a slab peel-off ray that never reaches the top
@@ -244,10 +237,8 @@ __device__ __forceinline__ void start_walk(Lane& L, const GridDev& g, const Batc
                 U2 u = draw(A.seed, S.tag, L.gid() - S.pbase, L.e(), 0);
                 L.tau = -log(u.a);
             }
-            ef = L.sef();
         } else {
             L.tau = 0.0;
-            ef = F_NONE;
         }
         if (kind == M_PEEL) {
             observer(L, A, sobs, dx, dy, dz);
@@ -257,7 +248,7 @@ __device__ __forceinline__ void start_walk(Lane& L, const GridDev& g, const Batc
             dz = L.sdz();
         }
         if (kind == M_PROBE) L.o() = kProbeDone;
-        wk_start<MIXED>(g, L.w, L.sx(), L.sy(), L.sz(), dx, dy, dz, L.si(), L.sj(), L.sk(), ef);
+        wk_start<MIXED>(g, L.w, L.sx(), L.sy(), L.sz(), dx, dy, dz, L.si(), L.sj(), L.sk());
         L.ncw = 0;
         L.mode = kind;
         // a slab peel-off ray that never reaches the top, or a floor peel-off
@@ -275,82 +266,60 @@ __device__ __forceinline__ void start_walk(Lane& L, const GridDev& g, const Batc
 // One cell of a walk.  Flights and peel-off rays share the exit search, the
 // extinction gather and the crossing (a single inlined copy of each, so that
 // a wave holding both kinds executes them once); they differ only in how the
-// optical depth is used and in when the walk stops.  Every walking lane runs
-// the crossing: a lane whose walk ends in this cell (interaction, surface
-// hit, end of a peel-off) discards its walker afterwards, so the walker is
-// never kept in two versions.
+// optical depth is used and in when the walk stops.  ae: the extinction of
+// the walk's cell, gathered when the cell was entered (wk_start's first cell:
+// by the caller), so that a step's end and the next one's start cover the
+// gather's latency.
 template <bool MIXED, bool EXT>
 __device__ __forceinline__ void walk_step(Lane& L, const GridDev& g, const void* aext, const void* aabs,
-                                          const BatchArgs& A, double r_top)
+                                          Prop<MIXED>& ae, const BatchArgs& A)
 {
     double tf;
-    const int f = wk_next<MIXED>(g, L.w, tf, r_top);
+    const int x = wk_next(L.w, tf);
     const double s = tf - L.w.t;
-    const int c = wk_cell(g, L.w);
     const bool flight = L.mode == M_FLIGHT;
     const bool cont = flight && A.absorption == 1;
-    // the walk's parameter and cell before the crossing (the walker keeps its
-    // origin and direction, so the interaction point follows from them)
-    const double t0 = L.w.t;
-    const int ei = L.w.i, ej = L.w.j, ek = L.w.k;
-    // the grid-table loads of the crossing, then the extinction gather (its
-    // address formed first); the crossing's arithmetic waits only for the
-    // former, so the gather's latency overlaps it
-    const void* pe = cell_addr<MIXED>(aext, c);
-    const CrossIn xin = wk_cross_begin<MIXED>(g, L.w, f, tf);
-    const double ae = ld<MIXED>(pe, 0);
-    const double aa = cont ? ld<MIXED>(aabs, c) : 0.0;
-    const bool inside = wk_cross_end<MIXED>(g, L.w, f, xin);
-    const double a = cont ? (ae - aa) : ae;
-    const bool lost = flight && f == F_NONE && !(a > 0.0);
-    const bool hit = flight && !lost && a > 0.0 && L.tau < a * s;
-    const bool pend = !flight && f == F_NONE;
-    if (flight) {
-        if (!lost && !hit) L.tau = wk_mad<MIXED>(-a, s, L.tau);
-        if (cont && !lost) {
-            const double ds = hit ? wk_div<MIXED>(L.tau, a) : s;
-            double wn = L.W * exp(-aa * ds);
-            L.w_abs = L.w_abs + (L.W - wn);
-            L.W = wn;
-        }
-    } else if (!pend) {
-        L.tau = wk_mad<MIXED>(ae, s, L.tau);
+    const double aa = cont ? ld<MIXED>(aabs, L.w.c) : 0.0;
+    const double a = cont ? (double)ae - aa : (double)ae;
+    const bool hit = flight && a > 0.0 && L.tau < a * s;
+    if (cont && (hit || x != X_NONE)) {
+        const double ds = hit ? wk_div<MIXED>(L.tau, a) : s;
+        const double wn = L.W * exp(-aa * ds);
+        L.w_abs = L.w_abs + (L.W - wn);
+        L.W = wn;
     }
-    if (lost || hit || pend) {
+    if (hit || x == X_NONE) {
         L.ncross += L.ncw;
         L.mode = M_EVENT;
-        if (hit) {  // at t0 + tau / a (tau is still the depth left on entering the cell)
-            const double ti = t0 + wk_div<MIXED>(L.tau, a);
+        if (hit) {  // at t + tau / a (tau is the depth left on entering the cell)
+            const double ti = L.w.t + wk_div<MIXED>(L.tau, a);
             L.sx() = wk_mad<MIXED>(ti, L.w.dx, L.w.px);
             L.sy() = wk_mad<MIXED>(ti, L.w.dy, L.w.py);
             L.sz() = wk_mad<MIXED>(ti, L.w.dz, L.w.pz);
-            L.set_cell(ei, ej, ek);
-            L.set_sef(F_NONE);
+            L.set_cell(L.w.i, L.w.j, L.w.k);
         }
-        if (pend) L.tau = INFINITY;
-        L.ev = lost ? E_LOST : (hit ? E_INTERACT : E_PEEL_DONE);
+        if (!flight) L.tau = INFINITY;
+        L.ev = hit ? E_INTERACT : (flight ? E_LOST : E_PEEL_DONE);
         return;
     }
+    const CrossIn in = wk_cross_begin(g, L.w, x, tf);
+    ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? L.w.c : 0);
+    L.tau = wk_mad<MIXED>(flight ? -a : a, s, L.tau);
     L.ncw++;
-    bool done;
-    if (flight) {
-        done = !inside || L.ncw >= g.max_cross;
-        if (done) L.ev = !inside ? (L.w.k >= g.nlay ? E_ESCAPE : E_SURFACE) : E_LOST;
-    } else {
-        // a probe runs to the edge of the grid, the floor included; a
-        // peel-off ray stops beyond tau_peel_max or on the planet
-        const bool probe = EXT && L.mode == M_PROBE;
-        done = true;
-        if (L.tau > (probe ? INFINITY : A.tau_peel_max)) L.tau = INFINITY;
-        else if (!inside) { if (L.w.k < 0 && !probe) L.tau = INFINITY; }
-        else if (L.ncw >= g.max_cross) L.tau = INFINITY;
-        else done = false;
-        if (done) L.ev = E_PEEL_DONE;
-    }
-    if (done) {
+    const bool capped = L.ncw >= g.max_cross;
+    // a probe runs to the edge of the grid, the floor included; a peel-off
+    // ray stops beyond tau_peel_max or on the planet
+    const bool probe = EXT && L.mode == M_PROBE;
+    const bool dark = !flight && !probe && L.tau > A.tau_peel_max;
+    if (!in.inside || capped || dark) {
+        if (flight) L.ev = !in.inside ? (L.w.k >= g.nlay ? E_ESCAPE : E_SURFACE) : E_LOST;
+        else L.ev = E_PEEL_DONE;
+        if (!flight && (in.inside || (L.w.k < 0 && !probe) || dark)) L.tau = INFINITY;
         L.ncross += L.ncw;
         L.mode = M_EVENT;
+        return;
     }
+    wk_cross_end<MIXED>(g, L.w, x, in);
 }
 
 // Pending actions of a lane after an event; each is executed at exactly one
@@ -628,7 +597,6 @@ __device__ __forceinline__ int handle_event(Lane& L, const GridDev& g, const Bat
             L.sdz() = z / rr;
         }
         L.set_cell(L.w.i, L.w.j, 0);
-        L.set_sef(F_IN);
         L.o() = 0;
         L.birth() = 0;
         L.surf() = 1;
@@ -720,7 +688,7 @@ __device__ __forceinline__ void birth_record(const GridDev& g1, const BatchArgs&
             double mu0 = A.mu0 > 0.0 ? A.mu0 : sqrt(1.0 - u.a);
             b[B_X] = 0.0; b[B_Y] = 0.0; b[B_Z] = g.r[g.nlay];
             b[B_DX] = sqrt(fmax(1.0 - mu0 * mu0, 0.0)); b[B_DY] = 0.0; b[B_DZ] = -mu0;
-            b[B_CELL] = (double)(((unsigned long long)(g.nlay - 1) << 21) * 8 + (F_OUT + 1));
+            b[B_CELL] = (double)pack_ijk(0, 0, g.nlay - 1);
         } else {
             double rho = r_toa * sqrt(u.a);
             double a = 2.0 * kPi * u.b;
@@ -731,7 +699,7 @@ __device__ __forceinline__ void birth_record(const GridDev& g1, const BatchArgs&
             locate_column(g, rs);
             b[B_X] = x; b[B_Y] = y; b[B_Z] = z;
             b[B_DX] = -1.0; b[B_DY] = 0.0; b[B_DZ] = 0.0;
-            b[B_CELL] = (double)(pack_ijk(rs.i, rs.j, g.nlay - 1) * 8 + (F_OUT + 1));
+            b[B_CELL] = (double)pack_ijk(rs.i, rs.j, g.nlay - 1);
         }
         b[B_W] = wmul;
         return;
@@ -750,7 +718,7 @@ __device__ __forceinline__ void birth_record(const GridDev& g1, const BatchArgs&
         locate_column(g, rs);
         b[B_X] = rs.x; b[B_Y] = rs.y; b[B_Z] = rs.z;
         b[B_DX] = -1.0; b[B_DY] = 0.0; b[B_DZ] = 0.0;
-        b[B_CELL] = (double)(pack_ijk(rs.i, rs.j, g.nlay - 1) * 8 + (F_OUT + 1));
+        b[B_CELL] = (double)pack_ijk(rs.i, rs.j, g.nlay - 1);
         b[B_W] = bi * limb_weight(A.ld, rs.y, rs.z) * wmul;
         return;
     }
@@ -804,7 +772,7 @@ __device__ __forceinline__ void birth_record(const GridDev& g1, const BatchArgs&
     b[B_DY] = sp * sin(psi);
     b[B_DZ] = mu;
     b[B_W] = S.wbirth[c] * wmul;
-    b[B_CELL] = (double)(pack_ijk(i, j, k) * 8 + (F_NONE + 1));
+    b[B_CELL] = (double)pack_ijk(i, j, k);
 }
 
 // The records of a block's packets are built in LDS and its rows written
@@ -879,9 +847,7 @@ __device__ __forceinline__ int birth(Lane& L, const GridDev& g, const BatchArgs&
         L.ev = -1;
         return A_FINISH;
     }
-    const unsigned long long cc = (unsigned long long)cw;
-    L.C->ijk[L.t] = (uint32_t)(cc >> 3);
-    L.set_sef((int)(cc & 7) - 1);
+    L.C->ijk[L.t] = (uint32_t)cw;
     L.sx() = b[B_X]; L.sy() = b[B_Y]; L.sz() = b[B_Z];
     L.sdx() = b[B_DX]; L.sdy() = b[B_DY]; L.sdz() = b[B_DZ];
     if (S.mode == 0) return A_FLIGHT;
@@ -914,10 +880,11 @@ __global__ void __launch_bounds__(kTPB, MINB) k_transport_persistent(GridDev g1,
     cold.st[threadIdx.x] = 0u;
     const void* aext = nullptr;
     const void* aabs = nullptr;
-    const double r_top1 = MULTI ? 0.0 : g1.r[g1.nlay];  // top of the grid (the fast walk's tolerance scale)
+    Prop<MIXED> ae = 0;  // the extinction of the walk's cell
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
-        if (L.mode <= M_PROBE) walk_step<MIXED, EXT>(L, g, aext, aabs, A, MULTI ? g.r[g.nlay] : r_top1);
+        if (L.mode <= M_PROBE && g.eq_edge > 0 && (L.w.fl & WF_EQ)) wk_row_roots<MIXED>(g, L.w);
+        if (L.mode <= M_PROBE) walk_step<MIXED, EXT>(L, g, aext, aabs, ae, A);
         unsigned long long evm = __ballot(L.mode == M_EVENT);
         unsigned long long walking = __ballot(L.mode <= M_PROBE);
         if (__popcll(evm) < A.ev_threshold && walking != 0) continue;
@@ -983,7 +950,10 @@ __global__ void __launch_bounds__(kTPB, MINB) k_transport_persistent(GridDev g1,
             }
         }
         const GridDev& ga = MULTI ? A.grids[lgrid] : g1;
-        if (act == A_FLIGHT || act == A_PEEL) start_walk<MIXED, EXT>(L, ga, A, sobs, act == A_FLIGHT);
+        if (act == A_FLIGHT || act == A_PEEL) {
+            ae = (Prop<MIXED>)ld<MIXED>(aext, L.cell(ga));
+            start_walk<MIXED, EXT>(L, ga, A, sobs, act == A_FLIGHT);
+        }
         if (__ballot(L.mode != M_IDLE) == 0) break;
     }
 }
