@@ -231,9 +231,7 @@ int mcrt_opacity_free(mcrt_ctx* ctx, int32_t opac_id);
  *   solve runs).
  * tune_ev_threshold, tune_blocks_per_cu, tune_wave_batch: launch shape of the
  *   persistent transport (lanes waiting before events are handled, 256-lane
- *   blocks per compute unit -- 1 to 3 select the spill-free register form, 4
- *   or more the 128-register form --, packets a wave takes at once);
- *   0 = default.
+ *   blocks per compute unit, packets a wave takes at once); 0 = default.
  * graph: albedo and emission blocking solves: non-zero records the solve's
  *   device work (preparation, transport and reduction launches and their
  *   host-to-device parameter copies) as a hipGraph on the first call and

@@ -1102,7 +1102,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
             launch_births(g->dev, A, false, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt], st));
             launch_transport_persistent(g->dev, A, mixed, false, sl.stream_ordered ? serving_blocks(ctx, bpc) : pblocks,
-                                        bpc, st);
+                                        st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt + 1], st));
             double* dump = p->packet_dump ? p->packet_dump + (size_t)(gs ? s0 / ng : s0) * N * no : nullptr;
             launch_reduce_rows(A, nullptr, nb, (double*)v_part, chunks, sums + (size_t)s0 * row_w, row_w, dump, st);
@@ -1659,7 +1659,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
             launch_init_dispensers(A.counter, A.total, st);
             launch_births(hgrids[0], A, true, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li], st));
-            launch_transport_persistent(hgrids[0], A, mixed, true, pblocks, bpc, st);
+            launch_transport_persistent(hgrids[0], A, mixed, true, pblocks, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li + 1], st));
             int chunks_l = 1;
             for (int sg = s0; sg < s1; ++sg)
@@ -2098,7 +2098,8 @@ int grid_upload(mcrt_ctx* ctx, const mcrt_grid_desc* d, hipStream_t st, int32_t*
     faces.reserve((size_t)nlay + nlat + nlon + 1);
     for (int k = 0; k < nlay; ++k) faces.push_back(make_double2(d->r_edges[k], d->r_edges[k + 1]));
     gd.lat_base = (int)faces.size();
-    for (int j = 0; j < nlat; ++j) faces.push_back(make_double2(lsn[j], lsn[j + 1]));
+    for (int j = 0; j < nlat; ++j)  // a pole is no face: out of any sine's reach
+        faces.push_back(make_double2(j == 0 ? -2.0 : lsn[j], j == nlat - 1 ? 2.0 : lsn[j + 1]));
     gd.eq_edge = 0;
     for (int e = 1; e < nlat; ++e)
         if (lsn[e] != 0.0 && std::fabs(lsn[e]) < 1e-8) gd.eq_edge = e;

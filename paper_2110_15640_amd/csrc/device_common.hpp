@@ -551,41 +551,44 @@ struct Walker {
     double ts, tc, tp;  // next shell, cone and plane (INFINITY = none)
     double far;         // while inward: the far root of the sphere at ts
     int i, j, k;
-    int c;              // cell index (k * nlat + j) * nlon + i, kept as the walk moves
-    int fl;             // WF_ bits
+    int dk, dj, di;     // +-1: ts is the outer or inner shell, tc the upper or lower cone, longitude grows or shrinks
+    int eq;             // WE_ bits
 };
 enum {
-    WF_INWARD = 1,    // ts is the cell's inner shell
-    WF_UP = 2,        // tc is the row's upper cone
-    WF_EAST = 4,      // the longitude grows along the walk
-    WF_EQ = 8,        // the walk just entered a row at GridDev::eq_edge: wk_row_roots sets tc
-    WF_FROM_LO = 16,  // ... through the row's lower edge
-    WF_FROM_HI = 32   // ... through its upper edge
+    WE_ROW = 1,      // the walk just entered a row at GridDev::eq_edge: wk_row_roots sets tc
+    WE_FROM_LO = 2,  // ... through the row's lower edge
+    WE_FROM_HI = 4   // ... through its upper edge
 };
-enum { X_NONE = 0, X_SHELL = 1, X_CONE = 2, X_PLANE = 3 };
 
-__host__ __device__ __forceinline__ double2 wk_face(const GridDev& g, int e) { return g.faces[e]; }
+// The face table's entry e (a 32-bit offset from one uniform base).
+__host__ __device__ __forceinline__ double2 wk_face(const GridDev& g, int e)
+{
+    return *(const double2*)((const char*)g.faces + (uint32_t)e * (uint32_t)sizeof(double2));
+}
 
-// The latitude edge a walk in row j meets next, rising (up) or falling in
-// latitude; sl, su: the sines of the row's edges.  upper: it is edge j + 1,
-// met while the latitude rises (edge j: while it falls); met: there is one.
+__host__ __device__ __forceinline__ int wk_cell(const GridDev& g, const Walker& w) { return (w.k * g.nlat + w.j) * g.nlon + w.i; }
+
+// The latitude edge a walk in row j meets next, rising (dj = 1) or falling
+// (-1) in latitude; sl, su: the sines of the row's edges (a pole, which is no
+// face, counts as +-2: beyond reach).  A falling walk is taken mirrored at the
+// equator, so both are one rising case.  upper: it is edge j + 1, met while
+// the latitude rises (edge j: while it falls); met: there is one.
 struct ConePick {
     double s;
     bool met, upper;
 };
-__host__ __device__ __forceinline__ ConePick wk_cone_pick(const GridDev& g, const Walker& w, bool up, double sl, double su)
+__host__ __device__ __forceinline__ ConePick wk_cone_pick(const Walker& w, double q2, double Pz, bool up, double sl, double su)
 {
     ConePick p;
-    const double q2 = fma(-w.B0, w.B0, w.C0), Pz = fma(-w.B0, w.dz, w.pz);
     const double M = fma(Pz, Pz, (q2 * w.dz) * w.dz);
-    const bool turn = up ? Pz > 0.0 : Pz < 0.0;         // the extremum is ahead
     const double sf = up ? su : sl, sb = up ? sl : su;  // the edges in front and behind
-    const bool top = w.j + 1 < g.nlat, bottom = w.j > 0;  // a pole is no face
-    const bool past_f = up ? w.dz > sf : w.dz < sf, past_b = up ? w.dz < sb : w.dz > sb;
-    const bool front = (up ? top : bottom) && (turn ? fma(-(sf * sf), q2, M) >= 0.0 : past_f);
-    const bool back = !front && turn && (up ? bottom : top) && past_b;
+    const double mf = up ? sf : -sf, mb = up ? sb : -sb, mz = up ? w.dz : -w.dz, mP = up ? Pz : -Pz;
+    const bool turn = mP > 0.0;  // the extremum is ahead
+    const bool reach = fma(-(sf * sf), q2, M) >= 0.0, past_f = mz > mf, past_b = mz < mb;
+    const bool front = (turn & reach) | (!turn & past_f);
+    const bool back = !front & turn & past_b;
     p.s = front ? sf : sb;
-    p.met = front || back;
+    p.met = front | back;
     p.upper = up == front;
     return p;
 }
@@ -623,24 +626,15 @@ __host__ __device__ __forceinline__ double wk_root(double num, double den)
 
 // The root at which the picked edge is met, q/a (first) or c/q of the cone's
 // quadratic with q = -(b + sign(b) sqrt(disc)), as a quotient: of
-// (-b -+ sqrt(disc)) / a the one of + sign(s) is met rising.
-// The equator (s = 0) is the plane z = 0.
+// (-b -+ sqrt(disc)) / a the one of + sign(s) is met rising.  A parabolic cone
+// (a = 0) has one root and the equator (s = 0) is the plane z = 0.
 template <bool FAST>
-__host__ __device__ __forceinline__ bool wk_cone_root(const Walker& w, const ConePick& p, double a, double b, double c,
+__host__ __device__ __forceinline__ void wk_cone_root(const Walker& w, const ConePick& p, double a, double b, double c,
                                                       double sq, double& num, double& den)
 {
-    if (p.s == 0.0) {
-        num = -w.pz;
-        den = w.dz;
-        return w.dz != 0.0;
-    }
-    const bool first = (b >= 0.0) == ((p.s > 0.0) != p.upper);
-    if (a == 0.0) {
-        num = -c;
-        den = 2.0 * b;
-        return b != 0.0;
-    }
-    const double q = -(b + (b >= 0.0 ? sq : -sq));
+    const bool bp = b >= 0.0;
+    const bool first = (bp != (p.s > 0.0)) == p.upper;
+    const double q = -(b + (bp ? sq : -sq));
     if constexpr (FAST) {
         num = first ? q * q : c * a;
         den = a * q;
@@ -648,7 +642,10 @@ __host__ __device__ __forceinline__ bool wk_cone_root(const Walker& w, const Con
         num = first ? q : c;
         den = first ? a : q;
     }
-    return den != 0.0;
+    if ((p.s == 0.0) | (a == 0.0)) {
+        num = p.s == 0.0 ? -w.pz : -c;
+        den = p.s == 0.0 ? w.dz : 2.0 * b;
+    }
 }
 
 // cos^2 of the picked latitude edge (read by the exact form only)
@@ -668,13 +665,14 @@ __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, d
     w.dx = dx; w.dy = dy; w.dz = dz;
     w.t = 0.0;
     w.i = i; w.j = j; w.k = k;
-    w.c = (k * g.nlat + j) * g.nlon + i;
     w.tc = w.tp = INFINITY;
     w.far = 0.0;
+    w.eq = 0;
     const double2 fr = wk_face(g, k);
     if (g.geom == 1) {
         w.B0 = w.C0 = 0.0;
-        w.fl = dz > 0.0 ? 0 : WF_INWARD;
+        w.dk = dz > 0.0 ? 1 : -1;
+        w.dj = w.di = 1;
         const double x = wk_div<FAST>((dz > 0.0 ? fr.y : fr.x) - pz, dz);
         w.ts = dz != 0.0 ? wk_max(x, 0.0) : INFINITY;
         return;
@@ -689,42 +687,47 @@ __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, d
     // the inner sphere where the walk goes inward and meets it, else the outer one
     const double Ci = wk_mad<FAST>(-fr.x, fr.x, C0), Di = wk_mad<FAST>(B, B, -Ci);
     const double Co = wk_mad<FAST>(-fr.y, fr.y, C0), Do = wk_mad<FAST>(B, B, -Co);
-    bool inward = B < 0.0 && Di >= 0.0;
+    const bool inward = (B < 0.0) & (Di >= 0.0);
     const double sq = wk_sqrt<FAST>(inward ? Di : Do);
     const double q = B <= 0.0 ? -B + sq : B + sq;
     const double x = wk_div<FAST>(inward ? Ci : -Co, q);
-    w.ts = wk_max(inward || B > 0.0 ? x : q, 0.0);
+    w.ts = wk_max((inward | (B > 0.0)) ? x : q, 0.0);
     w.far = q;
-    w.fl = (inward ? WF_INWARD : 0) | (east ? WF_EAST : 0);
-    double num, den;
-    if (g.nlat > 1) {
-        const double q2 = fma(-B, B, C0), Pz = fma(-B, dz, pz);
-        const bool up = fma(dz, q2, -(Pz * B)) > 0.0;  // the sign of d sin(lat) / dt
-        const ConePick p = wk_cone_pick(g, w, up, fc.x, fc.y);
-        w.fl |= p.upper ? WF_UP : 0;
-        if (g.eq_edge > 0 && wk_at_eq(g, j)) w.fl |= WF_EQ;
-        double a, b, c;
-        wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
-        const double sqc = wk_sqrt<FAST>(wk_mad<FAST>(b, b, -(a * c)));
-        const bool ok = wk_cone_root<FAST>(w, p, a, b, c, sqc, num, den);
-        double r;
-        if constexpr (FAST) r = (p.s == 0.0 || a == 0.0) ? wk_div<true>(num, den) : wk_root<true>(num, den);
-        else r = wk_root<false>(num, den);
-        w.tc = p.met && ok ? wk_max(r, 0.0) : INFINITY;
-    }
+    w.dk = inward ? -1 : 1;
+    w.di = east ? 1 : -1;
+    const double q2 = fma(-B, B, C0), Pz = fma(-B, dz, pz);
+    const ConePick p = wk_cone_pick(w, q2, Pz, fma(dz, q2, -(Pz * B)) > 0.0, fc.x, fc.y);  // the sign of d sin(lat) / dt
+    w.dj = p.upper ? 1 : -1;
+    double num, den, a, b, c;
+    wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
+    wk_cone_root<FAST>(w, p, a, b, c, wk_sqrt<FAST>(wk_mad<FAST>(b, b, -(a * c))), num, den);
+    double r;
+    if constexpr (FAST) r = ((p.s == 0.0) | (a == 0.0)) ? wk_div<true>(num, den) : wk_root<true>(num, den);
+    else r = wk_root<false>(num, den);
+    w.tc = (p.met & (den != 0.0)) ? wk_max(r, 0.0) : INFINITY;
+    if (g.eq_edge > 0 && wk_at_eq(g, j)) w.eq = WE_ROW;
     if (g.nlon > 1) {
         const double nx = -fp.x, ny = fp.y;
         const double dn = wk_mad<FAST>(dx, nx, dy * ny);
-        const double r = wk_div<FAST>(-wk_mad<FAST>(px, nx, py * ny), dn);
-        w.tp = (east ? dn > 0.0 : dn < 0.0) ? wk_max(r, 0.0) : INFINITY;
+        const double v = wk_div<FAST>(-wk_mad<FAST>(px, nx, py * ny), dn);
+        w.tp = (east ? dn > 0.0 : dn < 0.0) ? wk_max(v, 0.0) : INFINITY;
     }
 }
 
-// Parameter and kind of the next crossing.
-__host__ __device__ __forceinline__ int wk_next(const Walker& w, double& tf)
+// Parameter of the next crossing and the kind of its face: a shell, else a
+// cone, else a plane (none: no face ahead, only in a slab).
+struct CrossKind {
+    double t;
+    bool shell, cone, none;
+};
+__host__ __device__ __forceinline__ CrossKind wk_next(const Walker& w)
 {
-    tf = wk_min(wk_min(w.ts, w.tc), w.tp);
-    return w.ts <= tf ? (tf < INFINITY ? X_SHELL : X_NONE) : (w.tc <= tf ? X_CONE : X_PLANE);
+    CrossKind x;
+    x.t = wk_min(wk_min(w.ts, w.tc), w.tp);
+    x.shell = w.ts <= x.t;
+    x.cone = !x.shell & (w.tc <= x.t);
+    x.none = !(x.t < INFINITY);
+    return x;
 }
 
 // The face-table values a crossing reads, loaded by wk_cross_begin so that a
@@ -735,82 +738,78 @@ struct CrossIn {
     bool inside;
 };
 
-// Index update and table load of a crossing at tf of kind x (a face), without
-// branches.
-__host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Walker& w, int x, double tf)
+// Index update and table load of a crossing (of a face), without branches.
+__host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Walker& w, const CrossKind& x)
 {
     CrossIn in;
-    w.t = tf;
-    const bool shell = x == X_SHELL, cone = x == X_CONE;
-    const int dk = (w.fl & WF_INWARD) ? -1 : 1, dj = (w.fl & WF_UP) ? 1 : -1, east = (w.fl & WF_EAST) ? 1 : 0;
-    const int ie = w.i + 1 == g.nlon ? 0 : w.i + 1, iw = (w.i == 0 ? g.nlon : w.i) - 1;
-    const int di = (east ? ie : iw) - w.i;
-    w.k += shell ? dk : 0;
-    w.j += cone ? dj : 0;
-    w.i += shell || cone ? 0 : di;
-    w.c += shell ? dk * (g.nlon * g.nlat) : (cone ? dj * g.nlon : di);
+    w.t = x.t;
+    int ni = w.i + w.di;
+    ni = ni == g.nlon ? 0 : (ni < 0 ? g.nlon - 1 : ni);
+    w.k += x.shell ? w.dk : 0;
+    w.j += x.cone ? w.dj : 0;
+    w.i = (x.shell | x.cone) ? w.i : ni;
     in.inside = (unsigned)w.k < (unsigned)g.nlay;
-    in.f = wk_face(g, shell ? (in.inside ? w.k : 0) : (cone ? g.lat_base + w.j : g.lon_base + w.i + east));
+    const int er = in.inside ? w.k : 0, ec = g.lat_base + w.j, ep = g.lon_base + w.i + (w.di > 0 ? 1 : 0);
+    in.f = wk_face(g, x.shell ? er : (x.cone ? ec : ep));
     return in;
 }
 
 // The face that replaces the one just crossed.
 template <bool FAST>
-__host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& w, int x, const CrossIn& in)
+__host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& w, const CrossKind& x, const CrossIn& in)
 {
-    const bool shell = x == X_SHELL, cone = x == X_CONE;
-    const bool inward = (w.fl & WF_INWARD) != 0;
-    const double R = inward ? in.f.x : in.f.y;
+    const bool outward = w.dk > 0;
+    const double R = outward ? in.f.y : in.f.x;
     if (g.geom == 1) {
         w.ts = wk_max(wk_div<FAST>(R - w.pz, w.dz), w.t);
         return;
     }
     // a t^2 + 2 b t + c of the shell or cone
-    double b = w.B0, c = wk_mad<FAST>(-R, R, w.C0), a = 1.0, D;
+    double b = w.B0, c = wk_mad<FAST>(-R, R, w.C0), a = 1.0;
+    double D = wk_mad<FAST>(b, b, -c);
     ConePick p{};
-    if (cone) {
-        const bool up = (w.fl & WF_UP) != 0;
-        p = wk_cone_pick(g, w, up, in.f.x, in.f.y);
-        w.fl = (w.fl & ~WF_UP) | (p.upper ? WF_UP : 0);
-        if (g.eq_edge > 0 && wk_at_eq(g, w.j)) w.fl |= WF_EQ | (up ? WF_FROM_LO : WF_FROM_HI);
+    if (x.cone) {
+        const bool up = w.dj > 0;
+        p = wk_cone_pick(w, fma(-w.B0, w.B0, w.C0), fma(-w.B0, w.dz, w.pz), up, in.f.x, in.f.y);
+        w.dj = p.upper ? 1 : -1;
+        if (g.eq_edge > 0 && wk_at_eq(g, w.j)) w.eq = WE_ROW | (up ? WE_FROM_LO : WE_FROM_HI);
         wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
         D = wk_mad<FAST>(b, b, -(a * c));
-    } else {
-        D = wk_mad<FAST>(b, b, -c);
     }
     const double sq = wk_sqrt<FAST>(D);
-    const double q = b > 0.0 ? -(b + sq) : -b + sq;  // of the shell
+    // the shell's root: the far one of a sphere whose nearest point is still
+    // ahead as q, else as c / q
+    const double q = b > 0.0 ? -(b + sq) : -b + sq;
+    const bool qfar = outward & !(b > 0.0);
     double num, den;
-    bool met = true;
-    if (shell) {
-        const bool first = !inward && !(b > 0.0);  // far root of a sphere whose nearest point is still ahead
-        if constexpr (FAST) {
-            num = first ? q * q : c;
-            den = q;
-        } else {
-            num = first ? q : c;
-            den = first ? 1.0 : q;
-        }
-        met = den != 0.0;
-    } else if (cone) {
-        met = wk_cone_root<FAST>(w, p, a, b, c, sq, num, den);
-        met = met && p.met;
+    if constexpr (FAST) {
+        num = qfar ? q * q : c;
+        den = q;
     } else {
+        num = qfar ? q : c;
+        den = qfar ? 1.0 : q;
+    }
+    bool met = true;
+    if (x.cone) {
+        wk_cone_root<FAST>(w, p, a, b, c, sq, num, den);
+        met = p.met;
+    } else if (!x.shell) {
         const double nx = -in.f.x, ny = in.f.y;
         den = wk_mad<FAST>(w.dx, nx, w.dy * ny);
         num = -wk_mad<FAST>(w.px, nx, w.py * ny);
-        met = (w.fl & WF_EAST) ? den > 0.0 : den < 0.0;
+        met = (w.di > 0 ? den : -den) > 0.0;
     }
+    const bool finite = den != 0.0;
     const double r = wk_root<FAST>(num, den);
-    if (shell) {
-        const bool hit = D >= 0.0 && (r >= w.t || c < 0.0);  // (a sphere met on the way out always is)
-        w.ts = wk_max(!inward || hit ? (met ? r : 0.0) : w.far, w.t);
-        if (inward && !hit) w.fl &= ~WF_INWARD;
+    if (x.shell) {
+        const bool hit = outward | ((D >= 0.0) & ((r >= w.t) | (c < 0.0)));
+        w.ts = wk_max(hit ? (finite ? r : 0.0) : w.far, w.t);
+        w.dk = hit ? w.dk : 1;
         w.far = q;
     } else {
-        const double v = met ? wk_max(r, w.t) : INFINITY;
-        if (cone) w.tc = v;
-        else w.tp = v;
+        const double v = (met & finite) ? wk_max(r, w.t) : INFINITY;
+        w.tc = x.cone ? v : w.tc;
+        w.tp = x.cone ? w.tp : v;
     }
 }
 
@@ -831,7 +830,7 @@ __host__ __device__ __forceinline__ void wk_row_roots(const GridDev& g, Walker& 
     for (int e = 0; e < 2; ++e) {
         const int je = w.j + e;
         if (je == 0 || je == g.nlat) continue;
-        const double s = e ? f.y : f.x;
+        const double s = e ? f.y : f.x;  // (not a pole here)
         double a, b, c;
         wk_cone_coef<FAST>(w, s, FAST ? 0.0 : g.lat_c2[je], a, b, c);
         const double disc = wk_mad<FAST>(b, b, -(a * c));
@@ -843,7 +842,7 @@ __host__ __device__ __forceinline__ void wk_row_roots(const GridDev& g, Walker& 
             x0 = FAST ? wk_root<FAST>(q * q, a * q) : wk_root<FAST>(q, a);
             x1 = FAST ? wk_root<FAST>(c * a, a * q) : wk_root<FAST>(c, q);
         }
-        const double lo = (w.fl & (e ? WF_FROM_HI : WF_FROM_LO)) ? w.t + tol : w.t;
+        const double lo = (w.eq & (e ? WE_FROM_HI : WE_FROM_LO)) ? w.t + tol : w.t;
         for (int m = 0; m < 2; ++m) {
             const double x = m ? x1 : x0, z = wk_mad<FAST>(x, w.dz, w.pz);
             if (x < INFINITY && x >= lo && (s > 0.0 ? z > 0.0 : z < 0.0) && x < best) {
@@ -853,7 +852,8 @@ __host__ __device__ __forceinline__ void wk_row_roots(const GridDev& g, Walker& 
         }
     }
     w.tc = best;
-    w.fl = (w.fl & ~(WF_UP | WF_EQ | WF_FROM_LO | WF_FROM_HI)) | (upper ? WF_UP : 0);
+    w.dj = upper ? 1 : -1;
+    w.eq = 0;
 }
 
 }  // namespace dev

@@ -30,7 +30,7 @@ struct GridDev {
     // the edge values a crossing reads, in one array so that one base and a
     // per-lane offset reach any of them with one 16-byte load: the layer's
     // (r[k], r[k + 1]) at k; (sin lat[j], sin lat[j + 1]) of row j at
-    // lat_base + j; (sin, cos) of longitude edge e (edge nlon = edge 0) at
+    // lat_base + j (-2 and 2 at the poles); (sin, cos) of longitude edge e (edge nlon = edge 0) at
     // lon_base + e
     const double2* faces;
     int lat_base, lon_base;
@@ -162,7 +162,7 @@ void launch_prep_sources(const GridDev& g, int ncell, const PrepSlot* slots, int
 size_t prep_scratch_doubles(int ncell, int nslots);
 
 void launch_transport_persistent(const GridDev& g, const BatchArgs& a, bool mixed, bool multi, int blocks,
-                                 int blocks_per_cu, hipStream_t stream);
+                                 hipStream_t stream);
 void launch_reduce_rows(const BatchArgs& a, const SolveDev* solves_host, int n_solves,
                         double* partials, int chunks, double* sums, int sums_w, double* dump,
                         hipStream_t stream);

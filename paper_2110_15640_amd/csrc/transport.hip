@@ -148,8 +148,9 @@ using Prop = typename std::conditional<MIXED, float, double>::type;
 
 // Write the packet's row: its peel-off sums, then the counters; `kind` says
 // where its remaining weight went.  EXT (here and below): the kernel form
-// with the Lambert floor, Draine clouds, forced interactions and
-// multiple-scattering transmission; without it that code is compiled out.
+// with the Lambert floor, Draine clouds, forced interactions, continuous
+// absorption and multiple-scattering transmission; without it that code is
+// compiled out.
 template <bool EXT>
 __device__ __forceinline__ void finish_packet(Lane& L, const BatchArgs& A, int kind)
 {
@@ -274,21 +275,25 @@ template <bool MIXED, bool EXT>
 __device__ __forceinline__ void walk_step(Lane& L, const GridDev& g, const void* aext, const void* aabs,
                                           Prop<MIXED>& ae, const BatchArgs& A)
 {
-    double tf;
-    const int x = wk_next(L.w, tf);
-    const double s = tf - L.w.t;
+    const CrossKind x = wk_next(L.w);
+    const double s = x.t - L.w.t;
     const bool flight = L.mode == M_FLIGHT;
-    const bool cont = flight && A.absorption == 1;
-    const double aa = cont ? ld<MIXED>(aabs, L.w.c) : 0.0;
-    const double a = cont ? (double)ae - aa : (double)ae;
-    const bool hit = flight && a > 0.0 && L.tau < a * s;
-    if (cont && (hit || x != X_NONE)) {
-        const double ds = hit ? wk_div<MIXED>(L.tau, a) : s;
-        const double wn = L.W * exp(-aa * ds);
-        L.w_abs = L.w_abs + (L.W - wn);
-        L.W = wn;
+    double a = (double)ae;
+    if constexpr (EXT) {
+        if (A.absorption == 1 && flight) {  // continuous absorption: tau counts scattering only
+            const double aa = ld<MIXED>(aabs, wk_cell(g, L.w));
+            a = a - aa;
+            const bool ends = (a > 0.0) & (L.tau < a * s);
+            if (ends | !x.none) {
+                const double ds = ends ? wk_div<MIXED>(L.tau, a) : s;
+                const double wn = L.W * exp(-aa * ds);
+                L.w_abs = L.w_abs + (L.W - wn);
+                L.W = wn;
+            }
+        }
     }
-    if (hit || x == X_NONE) {
+    const bool hit = flight & (a > 0.0) & (L.tau < a * s);
+    if (hit | x.none) {
         L.ncross += L.ncw;
         L.mode = M_EVENT;
         if (hit) {  // at t + tau / a (tau is the depth left on entering the cell)
@@ -302,16 +307,16 @@ __device__ __forceinline__ void walk_step(Lane& L, const GridDev& g, const void*
         L.ev = hit ? E_INTERACT : (flight ? E_LOST : E_PEEL_DONE);
         return;
     }
-    const CrossIn in = wk_cross_begin(g, L.w, x, tf);
-    ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? L.w.c : 0);
+    const CrossIn in = wk_cross_begin(g, L.w, x);
+    ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? wk_cell(g, L.w) : 0);
     L.tau = wk_mad<MIXED>(flight ? -a : a, s, L.tau);
     L.ncw++;
     const bool capped = L.ncw >= g.max_cross;
     // a probe runs to the edge of the grid, the floor included; a peel-off
     // ray stops beyond tau_peel_max or on the planet
     const bool probe = EXT && L.mode == M_PROBE;
-    const bool dark = !flight && !probe && L.tau > A.tau_peel_max;
-    if (!in.inside || capped || dark) {
+    const bool dark = !flight & !probe & (L.tau > A.tau_peel_max);
+    if (!in.inside | capped | dark) {
         if (flight) L.ev = !in.inside ? (L.w.k >= g.nlay ? E_ESCAPE : E_SURFACE) : E_LOST;
         else L.ev = E_PEEL_DONE;
         if (!flight && (in.inside || (L.w.k < 0 && !probe) || dark)) L.tau = INFINITY;
@@ -855,16 +860,15 @@ __device__ __forceinline__ int birth(Lane& L, const GridDev& g, const BatchArgs&
     return A_PEEL;
 }
 
-// MINB: blocks per CU the register allocation is sized for (4: at most 128
-// VGPRs per lane, 16 waves per CU, with some spills; 2: no spills, ~170 VGPRs,
-// so up to 3 waves per SIMD = 3 blocks per CU), chosen at launch from the
-// requested blocks per CU.
-template <bool MIXED, bool MULTI, int MINB, bool EXT>
-__global__ void __launch_bounds__(kTPB, MINB) k_transport_persistent(GridDev g1, BatchArgs A)
+// Registers: 91 VGPRs (mixed) or 111 (FP64), the extended forms up to 116, so
+// four blocks of four waves are resident per CU, five in the mixed form when
+// the peel-off sums (dynamic LDS, n_out * 256 doubles) leave room.
+template <bool MIXED, bool MULTI, bool EXT>
+__global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, BatchArgs A)
 {
     __shared__ double sobs[2 * 3 * kMaxObs];
     __shared__ ColdLDS cold;
-    __shared__ double Fsh[kMaxObs * kTPB];
+    extern __shared__ double Fsh[];  // [n_out][kTPB]
     if (threadIdx.x < 2 * 3 * kMaxObs) sobs[threadIdx.x] = A.obs[threadIdx.x / (3 * kMaxObs)][threadIdx.x % (3 * kMaxObs)];
     __syncthreads();
     int lgrid = 0;  // grid of the lane's packet (multi-grid launches)
@@ -883,7 +887,7 @@ __global__ void __launch_bounds__(kTPB, MINB) k_transport_persistent(GridDev g1,
     Prop<MIXED> ae = 0;  // the extinction of the walk's cell
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
-        if (L.mode <= M_PROBE && g.eq_edge > 0 && (L.w.fl & WF_EQ)) wk_row_roots<MIXED>(g, L.w);
+        if (L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
         if (L.mode <= M_PROBE) walk_step<MIXED, EXT>(L, g, aext, aabs, ae, A);
         unsigned long long evm = __ballot(L.mode == M_EVENT);
         unsigned long long walking = __ballot(L.mode <= M_PROBE);
@@ -1071,24 +1075,19 @@ void launch_births(const GridDev& g, const BatchArgs& a, bool multi, hipStream_t
 }
 
 void launch_transport_persistent(const GridDev& g, const BatchArgs& a, bool mixed, bool multi, int blocks,
-                                 int blocks_per_cu, hipStream_t stream)
+                                 hipStream_t stream)
 {
-    const bool wide = blocks_per_cu <= 3;  // up to 256 VGPRs: at most 3 waves per SIMD
     // the extended form only when a launch uses one of its features
-    const bool ext = a.surface_albedo > 0.0 || a.cloud_phase == 2 || a.forced != 0 || a.trans_ms != 0;
-#define MCRT_K4(MX, MU, EX)                                                                                      \
-    if (wide)                                                                                                    \
-        hipLaunchKernelGGL((k_transport_persistent<MX, MU, 2, EX>), dim3(blocks), dim3(kTPB), 0, stream, g, a); \
-    else                                                                                                         \
-        hipLaunchKernelGGL((k_transport_persistent<MX, MU, 4, EX>), dim3(blocks), dim3(kTPB), 0, stream, g, a);
-#define MCRT_K4X(MX, MU)              \
-    if (ext) { MCRT_K4(MX, MU, true) } \
-    else { MCRT_K4(MX, MU, false) }
-    if (mixed && multi) { MCRT_K4X(true, true) }
-    else if (mixed) { MCRT_K4X(true, false) }
-    else if (multi) { MCRT_K4X(false, true) }
-    else { MCRT_K4X(false, false) }
-#undef MCRT_K4X
+    const bool ext = a.surface_albedo > 0.0 || a.cloud_phase == 2 || a.forced != 0 || a.trans_ms != 0 ||
+                     a.absorption == 1;
+    const size_t lds = (size_t)a.n_out * kTPB * sizeof(double);
+#define MCRT_K4(MX, MU)                                                                                              \
+    if (ext) hipLaunchKernelGGL((k_transport_persistent<MX, MU, true>), dim3(blocks), dim3(kTPB), lds, stream, g, a); \
+    else hipLaunchKernelGGL((k_transport_persistent<MX, MU, false>), dim3(blocks), dim3(kTPB), lds, stream, g, a);
+    if (mixed && multi) { MCRT_K4(true, true) }
+    else if (mixed) { MCRT_K4(true, false) }
+    else if (multi) { MCRT_K4(false, true) }
+    else { MCRT_K4(false, false) }
 #undef MCRT_K4
 }
 
