@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmcrt.so")
-SOURCES = ["kernels.hip", "prep.hip", "transport.hip", "api.cpp"]
+SOURCES = ["kernels.hip", "prep.hip", "transport.hip", "flight.hip", "api.cpp"]
 
 # -ffp-contract=off keeps every FP64 expression in the order it is written
 # (no fused multiply-add), so the FP64 path agrees with an independent FP64
@@ -20,11 +20,11 @@ HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contrac
             "-Wall", "-Wno-unused-function", "-I" + os.path.join(ROOT, "include")]
 
 
-# The transport kernel's loop holds rare code (sampling, births, phase
+# The transport kernels' loops hold rare code (sampling, births, phase
 # functions) whose many FP64 constants the machine-level loop-invariant motion
 # would keep in registers throughout: 117 instead of 91 VGPRs in the mixed
 # form, 128 with 26 spilled instead of 111 in the FP64 form.
-SOURCE_FLAGS = {"transport.hip": ["-mllvm", "-disable-machine-licm"]}
+SOURCE_FLAGS = {s: ["-mllvm", "-disable-machine-licm"] for s in ("transport.hip", "flight.hip")}
 
 
 def hipcc() -> str:

@@ -88,6 +88,7 @@ struct Slot {
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;  // ordering between the two streams
     std::vector<hipEvent_t> prof_ev;  // pairs around timed launches
+    uint32_t* flag = nullptr;         // pinned word (parked lanes of a split launch)
     std::map<std::string, DevBuf> scratch;  // grow-only, by role
     bool stream_ordered = false;  // serving slots allocate with hipMallocAsync
     // Fixed arena (the allocation-free solve): scratch is carved from it in
@@ -318,6 +319,8 @@ void slot_destroy(mcrt_ctx* ctx, Slot& sl)
     if (sl.stream) (void)hipStreamSynchronize(sl.stream);
     for (auto e : sl.prof_ev) (void)hipEventDestroy(e);
     sl.prof_ev.clear();
+    if (sl.flag) (void)hipHostFree(sl.flag);
+    sl.flag = nullptr;
     if (sl.ev0) (void)hipEventDestroy(sl.ev0);
     if (sl.ev1) (void)hipEventDestroy(sl.ev1);
     if (sl.fork) (void)hipEventDestroy(sl.fork);
@@ -757,6 +760,76 @@ int serving_blocks(mcrt_ctx* ctx, int bpc)
     return std::max(ctx->n_cu, ctx->n_cu * bpc / k);
 }
 
+// Scratch of the split form of the transport (flight.hip) for launches of up
+// to T packets: records for eight events per packet, 2^19
+// to 2^24 of them in all (a launch whose events need more repeats its kernels:
+// at 2^24 a round is tens of milliseconds of the whole device, so the
+// 50 us it costs do not show, and the records stay near 2 GB).  q.rec stays
+// null where the one-kernel form is taken: recorded solves (a graph cannot
+// repeat rounds), served requests and the fixed-scratch solve (both planned
+// without this scratch), and budgets it does not fit in.
+int split_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, bool use_graph, uint64_t T, int n_out, bool mixed, int blocks,
+                  PeelArgs& q)
+{
+    q = PeelArgs{};
+    if (use_graph || sl.arena || sl.stream_ordered || T >= kNoRecord) return MCRT_OK;
+    uint64_t recs = std::min<uint64_t>(std::max<uint64_t>(8 * T, 1ull << 19), 1ull << 24);
+    const size_t lanes = (size_t)blocks * 256;
+    // a wave's chunk: an eighth of its share, so that few slots stay empty
+    const uint64_t chunk = std::min<uint64_t>(std::max<uint64_t>(recs * 64 / (lanes * 8), 16), 256);
+    recs = (recs + kXcds * chunk - 1) / (kXcds * chunk) * (kXcds * chunk);
+    const struct {
+        const char* name;
+        size_t bytes;
+    } want[9] = {{"peel_rec", peel_record_bytes(mixed) * recs},
+                 {"peel_next", sizeof(uint32_t) * recs},
+                 {"peel_f", sizeof(double) * n_out * recs},
+                 {"peel_head", sizeof(uint32_t) * T},
+                 {"peel_ctl", sizeof(uint32_t) * kPeelCtl},
+                 {"peel_cross", sizeof(uint32_t) * T},
+                 {"peel_nx", sizeof(uint32_t) * n_out * recs},
+                 {"peel_park_d", sizeof(double) * kParkD * lanes},
+                 {"peel_park_u", sizeof(uint32_t) * kParkU * lanes}};
+    uint64_t more = 0;
+    for (const auto& w : want) {
+        const size_t have = sl.scratch[w.name].bytes;
+        if (w.bytes > have) more += w.bytes - have;
+    }
+    {
+        std::lock_guard<std::mutex> mk(ctx->mem_mu);
+        if (held_locked(ctx) + more > ctx->budget) return MCRT_OK;
+    }
+    void* p[9];
+    for (int i = 0; i < 9; ++i)
+        if (int rc = slot_scratch(ctx, sl, st, want[i].name, want[i].bytes, &p[i]))
+            return rc == MCRT_EBUDGET || rc == MCRT_ENOMEM ? MCRT_OK : rc;
+    if (!sl.flag) HIPTRY(hipHostMalloc((void**)&sl.flag, sizeof(uint32_t)));
+    q.next = (uint32_t*)p[1];
+    q.f = (double*)p[2];
+    q.head = (uint32_t*)p[3];
+    q.ctl = (uint32_t*)p[4];
+    q.peel_cross = (uint32_t*)p[5];
+    q.nx = (uint32_t*)p[6];
+    q.park_d = (double*)p[7];
+    q.park_u = (uint32_t*)p[8];
+    q.cap = (uint32_t)(recs / kXcds);
+    q.chunk = (uint32_t)chunk;
+    q.n_lanes = (int)lanes;
+    q.rec = p[0];
+    return MCRT_OK;
+}
+
+// One round of a split launch, and the copy of its number of parked lanes.
+int split_round(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const GridDev& g, const BatchArgs& A, const PeelArgs& q, bool mixed,
+                bool multi, int blocks)
+{
+    launch_flight(g, A, q, mixed, multi, blocks, st);
+    launch_peel(g, A, q, mixed, multi, ctx->n_cu * 5, st);
+    launch_peel_sum(A, q, st);
+    HIPTRY(hipMemcpyAsync(sl.flag, q.ctl + 2 * kXcds * kCtlStride, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    return MCRT_OK;
+}
+
 // Sky-plane axes of observer o for images: vertical e_v = z projected on the
 // plane normal to o (x when o is along z), horizontal e_h = e_v x o.
 void sky_axes(const double* o, double* out)
@@ -948,6 +1021,14 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     }
     const int bpc = p->tune_blocks_per_cu > 0 ? p->tune_blocks_per_cu : 4;
     const int pblocks = ctx->n_cu * bpc;
+    const uint64_t t_max = (uint64_t)(gs ? batch / ng : batch) * N;  // packets of a launch
+    PeelArgs Q;
+    if ((rc = split_scratch(ctx, sl, st, p->graph != 0, t_max, no, mixed, pblocks, Q))) return rc;
+    const bool split = Q.rec != nullptr;
+    A.head = Q.head;
+    A.peel_cross = Q.peel_cross;
+    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
+    if (split && A.lanes < 64) A.batch = A.lanes;
     if (npix) {
         A.npix = npix;
         A.img_half = g->r_toa;
@@ -1010,6 +1091,28 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     PrepSlot* pin_slots = ge ? (PrepSlot*)(pin_solves + (size_t)nbatches * batch) : nullptr;
     std::vector<std::vector<SolveDev>> host_solves(use_graph ? 0 : nbatches);
     std::vector<std::vector<PrepSlot>> host_slots(use_graph ? 0 : nbatches);
+
+    // The reduction of batch bt's rows (nb solves).
+    auto reduce = [&](int bt, int nb) {
+        const int s0 = bt * batch;
+        double* dump = p->packet_dump ? p->packet_dump + (size_t)(gs ? s0 / ng : s0) * N * no : nullptr;
+        launch_reduce_rows(A, nb, (double*)v_part, chunks, sums + (size_t)s0 * row_w, row_w, dump, st);
+    };
+    // Waits for batch bt; further rounds of a split launch whose records ran
+    // out, then the reduction again.
+    auto complete = [&](int bt, int nb) -> int {
+        HIPTRY(hipStreamSynchronize(st));
+        if (!split || *sl.flag == 0) return MCRT_OK;
+        Q.resume = 1;
+        while (*sl.flag != 0) {
+            launch_peel_reset(Q, st);
+            if (int r2 = split_round(ctx, sl, st, g->dev, A, Q, mixed, false, pblocks)) return r2;
+            HIPTRY(hipStreamSynchronize(st));
+        }
+        if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt + 1], st));
+        reduce(bt, nb);
+        return MCRT_OK;
+    };
 
     // The device chain: tally clear, Doppler shifts, then per batch the solve
     // tables, preparation, births, transport and reduction.
@@ -1101,14 +1204,21 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
             launch_init_dispensers(A.counter, A.total, st);
             launch_births(g->dev, A, false, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt], st));
-            launch_transport_persistent(g->dev, A, mixed, false, sl.stream_ordered ? serving_blocks(ctx, bpc) : pblocks,
-                                        st);
+            if (split) {
+                Q.resume = 0;
+                launch_peel_reset(Q, st);
+                if (int r2 = split_round(ctx, sl, st, g->dev, A, Q, mixed, false, pblocks)) return r2;
+            } else {
+                launch_transport_persistent(g->dev, A, mixed, false,
+                                            sl.stream_ordered ? serving_blocks(ctx, bpc) : pblocks, st);
+            }
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt + 1], st));
-            double* dump = p->packet_dump ? p->packet_dump + (size_t)(gs ? s0 / ng : s0) * N * no : nullptr;
-            launch_reduce_rows(A, nullptr, nb, (double*)v_part, chunks, sums + (size_t)s0 * row_w, row_w, dump, st);
+            reduce(bt, nb);
             // the next batch reuses the slots: in eager form its pageable host tables are
             // copied only after this batch ran
-            if (!use_graph && bt + 1 < nbatches) HIPTRY(hipStreamSynchronize(st));
+            if (!use_graph && bt + 1 < nbatches) {
+                if (int r2 = complete(bt, nb)) return r2;
+            }
         }
         return MCRT_OK;
     };
@@ -1138,6 +1248,11 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     std::vector<double> hs((size_t)nsolve * row_w);
     HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
     if ((rc = finish_timing(ctx, sl, st, res))) return rc;
+    if (split && *sl.flag != 0) {
+        if ((rc = complete(nbatches - 1, nsolve - (nbatches - 1) * batch))) return rc;
+        HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
+        if ((rc = finish_timing(ctx, sl, st, res))) return rc;
+    }
     if (prof && (rc = prof_collect(ctx, sl, (size_t)nbatches, res))) return rc;
     if (use_graph) res->kernel_ms = res->elapsed_ms;  // the whole replay
 
@@ -1500,6 +1615,19 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
     A.peel_w = 1.0;
     const int bpc = common->tune_blocks_per_cu > 0 ? common->tune_blocks_per_cu : 4;
     const int pblocks = ctx->n_cu * bpc;
+    uint64_t t_max = 1;  // packets of a launch
+    for (auto& L : launches) {
+        uint64_t t = 0;
+        for (int s = L.first; s < L.second; ++s) t += it[fl[s].item]->p.n_packets;
+        t_max = std::max(t_max, t);
+    }
+    PeelArgs Q;
+    if ((rc = split_scratch(ctx, sl, st, common->graph != 0, t_max, no, mixed, pblocks, Q))) return rc;
+    const bool split = Q.rec != nullptr;
+    A.head = Q.head;
+    A.peel_cross = Q.peel_cross;
+    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
+    if (split && A.lanes < 64) A.batch = A.lanes;
     // Replayable form (params.graph): the chain below is recorded once per set
     // of arguments (items, parameters, launch partition, stream and scratch
     // addresses) with its host tables in pinned memory, and replayed after.
@@ -1576,6 +1704,29 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
         t_slots = e_slots.data();
     }
     for (size_t q = 0; q < grids.size(); ++q) t_grids[q] = hgrids[q];
+
+    // The reduction of launch li's rows.
+    auto reduce = [&](size_t li) {
+        const int s0 = launches[li].first, s1 = launches[li].second;
+        int chunks_l = 1;
+        for (int sg = s0; sg < s1; ++sg)
+            chunks_l = std::max(chunks_l, reduce_rows_chunks(it[fl[sg].item]->p.n_packets));
+        launch_reduce_rows(A, s1 - s0, (double*)v_part, chunks_l, sums + (size_t)s0 * row_w, row_w, nullptr, st);
+    };
+    // Waits for launch li; further rounds of a split launch, as in solve_packets.
+    auto complete = [&](size_t li) -> int {
+        HIPTRY(hipStreamSynchronize(st));
+        if (!split || *sl.flag == 0) return MCRT_OK;
+        Q.resume = 1;
+        while (*sl.flag != 0) {
+            launch_peel_reset(Q, st);
+            if (int r2 = split_round(ctx, sl, st, hgrids[0], A, Q, mixed, true, pblocks)) return r2;
+            HIPTRY(hipStreamSynchronize(st));
+        }
+        if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li + 1], st));
+        reduce(li);
+        return MCRT_OK;
+    };
 
     auto enqueue = [&]() -> int {
         HIPTRY(hipMemcpyAsync(v_grids, t_grids, sizeof(GridDev) * grids.size(), hipMemcpyHostToDevice, st));
@@ -1659,16 +1810,20 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
             launch_init_dispensers(A.counter, A.total, st);
             launch_births(hgrids[0], A, true, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li], st));
-            launch_transport_persistent(hgrids[0], A, mixed, true, pblocks, st);
+            if (split) {
+                Q.resume = 0;
+                launch_peel_reset(Q, st);
+                if (int r2 = split_round(ctx, sl, st, hgrids[0], A, Q, mixed, true, pblocks)) return r2;
+            } else {
+                launch_transport_persistent(hgrids[0], A, mixed, true, pblocks, st);
+            }
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li + 1], st));
-            int chunks_l = 1;
-            for (int sg = s0; sg < s1; ++sg)
-                chunks_l = std::max(chunks_l, reduce_rows_chunks(it[fl[sg].item]->p.n_packets));
-            launch_reduce_rows(A, nullptr, nb, (double*)v_part, chunks_l, sums + (size_t)s0 * row_w, row_w, nullptr,
-                               st);
+            reduce(li);
             // in eager form the next launch's pageable tables are copied only after
             // this launch ran; stream order alone protects the reused device buffers
-            if (!use_graph && li + 1 < launches.size()) HIPTRY(hipStreamSynchronize(st));
+            if (!use_graph && li + 1 < launches.size()) {
+                if (int r2 = complete(li)) return r2;
+            }
         }
         return MCRT_OK;
     };
@@ -1698,6 +1853,11 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
     HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
     mcrt_result tr{};
     if ((rc = finish_timing(ctx, sl, st, &tr))) return rc;
+    if (split && *sl.flag != 0) {
+        if ((rc = complete(launches.size() - 1))) return rc;
+        HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
+        if ((rc = finish_timing(ctx, sl, st, &tr))) return rc;
+    }
     if (prof && (rc = prof_collect(ctx, sl, launches.size(), &tr))) return rc;
     if (use_graph) tr.kernel_ms = tr.elapsed_ms;  // the whole replay
     // per item post-processing, as for the single-request solves

@@ -121,6 +121,7 @@ struct BatchArgs {
     double r_toa;
     double obs[2][3 * kMaxObs];  // observer directions for albedo [0] and emission [1] solves
     int batch;         // packets a wave takes from the dispenser at once
+    int lanes;         // lanes of a wave that carry packets (split launches)
     int ev_threshold;  // waiting lanes that trigger event handling
     int cloud_phase;   // 0 Henyey-Greenstein, 1 two-term Henyey-Greenstein, 2 Draine (g_cld holds G)
     double draine_alpha;
@@ -139,7 +140,40 @@ struct BatchArgs {
     int npix;
     double img_half;
     double img_axes[6 * kMaxObs];
+    // split launches: each packet's first peel-off record (null: peel-offs run inside the transport)
+    uint32_t* head;
+    uint32_t* peel_cross;  // and the crossings of its peel-off rays so far
 };
+
+// Scratch of a split launch (flight.hip): flights append a record per event
+// that peels off, a second kernel walks the peel-off rays of all records, a
+// third adds their contributions to the packets' rows in the order of events.
+constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
+struct PeelArgs {
+    void* rec;        // records, one region per XCD
+    uint32_t* head;   // BatchArgs.head and peel_cross
+    uint32_t* peel_cross;
+    uint32_t* next;   // the packet's next record
+    double* f;        // [record][n_out]: the rays' contributions and crossings
+    uint32_t* nx;
+    uint32_t cap;     // records per region (a multiple of chunk)
+    uint32_t chunk;   // records a wave takes at once
+    uint32_t* ctl;    // counters a cache line apart: records and dispensed rays per region, parked lanes
+    double* park_d;   // lanes that found the regions full: their packets (resumed by the next round)
+    uint32_t* park_u;
+    int n_lanes;      // lanes of the flight kernel (the same in every round of a launch)
+    int resume;       // not the first round
+};
+constexpr int kCtlStride = 32;  // words
+constexpr int kPeelCtl = (2 * kXcds + 1) * kCtlStride;
+constexpr int kParkD = 10, kParkU = 9;
+size_t peel_record_bytes(bool mixed);
+void launch_peel_reset(const PeelArgs& q, hipStream_t stream);
+void launch_flight(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool mixed, bool multi, int blocks,
+                   hipStream_t stream);
+void launch_peel(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool mixed, bool multi, int blocks,
+                 hipStream_t stream);
+void launch_peel_sum(const BatchArgs& a, const PeelArgs& q, hipStream_t stream);
 
 // One solve slot of a batched preparation.
 struct PrepSlot {
@@ -163,9 +197,8 @@ size_t prep_scratch_doubles(int ncell, int nslots);
 
 void launch_transport_persistent(const GridDev& g, const BatchArgs& a, bool mixed, bool multi, int blocks,
                                  hipStream_t stream);
-void launch_reduce_rows(const BatchArgs& a, const SolveDev* solves_host, int n_solves,
-                        double* partials, int chunks, double* sums, int sums_w, double* dump,
-                        hipStream_t stream);
+void launch_reduce_rows(const BatchArgs& a, int n_solves, double* partials, int chunks, double* sums, int sums_w,
+                        double* dump, hipStream_t stream);
 int reduce_rows_chunks(unsigned long long max_n);
 void launch_fill_u64(unsigned long long* p, unsigned long long v, hipStream_t stream);
 void launch_init_dispensers(unsigned long long* counters, unsigned long long total, hipStream_t stream);

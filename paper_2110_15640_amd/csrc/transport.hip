@@ -27,41 +27,16 @@
 #include <math.h>
 #include <stdint.h>
 
-#include <type_traits>
-
-#include "device_common.hpp"
-#include "mcrt_internal.hpp"
+#include "transport_common.hpp"
 
 namespace mcrt {
 namespace {
 using namespace dev;
 
-// Lane modes; the walking ones come first: a flight, a peel-off ray, or the
-// probe of a forced interaction (the optical depth to the grid's edge along
-// the packet direction).
-enum { M_FLIGHT = 0, M_PEEL = 1, M_PROBE = 2, M_EVENT = 3, M_DEAD = 4, M_BIRTH = 5, M_IDLE = 6 };
-// Observer-field values outside the observer range: the walk that ended was a
-// probe, or the next flight's optical depth is already chosen.
-constexpr int kProbeDone = 15, kTauSet = 14;
-enum { E_INTERACT = 0, E_ESCAPE = 1, E_SURFACE = 2, E_LOST = 3, E_PEEL_DONE = 4 };
-// Birth record of a packet, kept in the counter columns of its row until the
-// packet dies: position, direction, weight, packed cell (i | j << 11 | k << 21)
-// (-1: nothing emits), then the index of the solve whose optics it uses;
-// with a Lambert floor, the weight the floor has absorbed so far; with
-// forced interactions, the unscattered fractions booked so far to the floor
-// (B_SURF) and to escape (B_FESC).
-enum { B_X = 0, B_Y, B_Z, B_DX, B_DY, B_DZ, B_W, B_CELL, B_SOLVE, B_SURF, B_FESC };
-
-__host__ __device__ __forceinline__ unsigned long long pack_ijk(int i, int j, int k)
-{
-    return (unsigned long long)i | ((unsigned long long)j << 11) | ((unsigned long long)k << 21);
-}
-
 // Per-lane state that the cell walk does not touch lives in LDS (one slot
 // per lane, structure of arrays) so the registers hold only the walking ray;
 // small fields are packed into 32-bit words.  The packet's peel-off sums
 // accumulate in LDS too and reach memory once, with its whole row.
-constexpr int kTPB = 256;
 struct ColdLDS {
     double sx[kTPB], sy[kTPB], sz[kTPB];      // event point
     double sdx[kTPB], sdy[kTPB], sdz[kTPB];   // packet direction
@@ -71,20 +46,6 @@ struct ColdLDS {
     uint32_t st[kTPB];    // observer:4 | birth:1 | smode:1 | 3 unused | capped:1 | lost:1 | surface:1 | solve:20
     uint32_t e[kTPB];
     int nint[kTPB];
-};
-
-// A bit field [sh, sh + w) of a packed LDS word, used like an int.
-struct Bits {
-    uint32_t* p;
-    int sh;
-    uint32_t m;
-    __device__ operator int() const { return (int)((*p >> sh) & m); }
-    __device__ Bits& operator=(int v)
-    {
-        *p = (*p & ~(m << sh)) | (((uint32_t)v & m) << sh);
-        return *this;
-    }
-    __device__ Bits& operator+=(int v) { return *this = (int)*this + v; }
 };
 
 struct Lane {
@@ -125,59 +86,13 @@ struct Lane {
     __device__ int cell(const GridDev& g) { return (sk() * g.nlat + sj()) * g.nlon + si(); }
 };
 
-// floor(total * x / kXcds) without overflow.
-__device__ __forceinline__ unsigned long long chunk_edge(unsigned long long total, int x)
-{
-    return (total / kXcds) * (unsigned long long)x + (total % kXcds) * (unsigned long long)x / kXcds;
-}
-
-template <bool MIXED>
-__device__ __forceinline__ double ld(const void* p, int c)
-{
-    // per-cell optical properties live in global memory: load through the
-    // global address space (a global, not a flat, load)
-    typedef const __attribute__((address_space(1))) float gfloat;
-    typedef const __attribute__((address_space(1))) double gdouble;
-    if (MIXED) return (double)((gfloat*)p)[c];
-    return ((gdouble*)p)[c];
-}
-
-// The stored type of the optical properties.
-template <bool MIXED>
-using Prop = typename std::conditional<MIXED, float, double>::type;
-
-// Write the packet's row: its peel-off sums, then the counters; `kind` says
-// where its remaining weight went.  EXT (here and below): the kernel form
-// with the Lambert floor, Draine clouds, forced interactions, continuous
-// absorption and multiple-scattering transmission; without it that code is
-// compiled out.
+// Write the packet's row: its peel-off sums, then the counters.
 template <bool EXT>
 __device__ __forceinline__ void finish_packet(Lane& L, const BatchArgs& A, int kind)
 {
     double* row = A.rows + L.gid() * (unsigned long long)A.row_w;
     for (int o = 0; o < A.n_out; ++o) row[o] = (EXT && A.trans_ms) ? L.W0() - L.Fo(o) : L.Fo(o);
-    row += A.n_out;
-    if (EXT) {
-        // weight booked before the end: absorbed by a Lambert floor (which
-        // never ends a packet) or the unscattered fractions of forced flights
-        const double wsurf = (A.surface_albedo > 0.0 || A.forced) ? row[B_SURF] : 0.0;
-        const double wesc = A.forced ? row[B_FESC] : 0.0;
-        row[K_ESC] = kind == K_ESC ? wesc + L.W : wesc;
-        row[K_SURF] = kind == K_SURF ? wsurf + L.W : wsurf;
-    } else {
-        row[K_ESC] = kind == K_ESC ? L.W : 0.0;
-        row[K_SURF] = kind == K_SURF ? L.W : 0.0;
-    }
-    row[K_ABS] = L.w_abs;
-    row[K_RR] = L.w_rr();
-    row[K_CAP] = kind == K_CAP ? L.W : 0.0;
-    row[K_LOST] = kind == K_LOST ? L.W : 0.0;
-    row[K_NINT] = (double)L.nint();
-    row[K_NCROSS] = (double)L.ncross;
-    row[K_NCAPPED] = (double)L.ncapped();
-    row[K_NLOST] = (double)L.nlost();
-    row[K_W0] = L.W0();
-    L.mode = M_DEAD;
+    finish_counters<EXT>(L, A, kind);
 }
 
 __device__ __forceinline__ void observer(Lane& L, const BatchArgs& A, const double* sobs, double& ox, double& oy,
@@ -262,203 +177,6 @@ __device__ __forceinline__ void start_walk(Lane& L, const GridDev& g, const Batc
             L.ev = E_PEEL_DONE;
         }
     }
-}
-
-// One cell of a walk.  Flights and peel-off rays share the exit search, the
-// extinction gather and the crossing (a single inlined copy of each, so that
-// a wave holding both kinds executes them once); they differ only in how the
-// optical depth is used and in when the walk stops.  ae: the extinction of
-// the walk's cell, gathered when the cell was entered (wk_start's first cell:
-// by the caller), so that a step's end and the next one's start cover the
-// gather's latency.
-template <bool MIXED, bool EXT>
-__device__ __forceinline__ void walk_step(Lane& L, const GridDev& g, const void* aext, const void* aabs,
-                                          Prop<MIXED>& ae, const BatchArgs& A)
-{
-    const CrossKind x = wk_next(L.w);
-    const double s = x.t - L.w.t;
-    const bool flight = L.mode == M_FLIGHT;
-    double a = (double)ae;
-    if constexpr (EXT) {
-        if (A.absorption == 1 && flight) {  // continuous absorption: tau counts scattering only
-            const double aa = ld<MIXED>(aabs, wk_cell(g, L.w));
-            a = a - aa;
-            const bool ends = (a > 0.0) & (L.tau < a * s);
-            if (ends | !x.none) {
-                const double ds = ends ? wk_div<MIXED>(L.tau, a) : s;
-                const double wn = L.W * exp(-aa * ds);
-                L.w_abs = L.w_abs + (L.W - wn);
-                L.W = wn;
-            }
-        }
-    }
-    const bool hit = flight & (a > 0.0) & (L.tau < a * s);
-    if (hit | x.none) {
-        L.ncross += L.ncw;
-        L.mode = M_EVENT;
-        if (hit) {  // at t + tau / a (tau is the depth left on entering the cell)
-            const double ti = L.w.t + wk_div<MIXED>(L.tau, a);
-            L.sx() = wk_mad<MIXED>(ti, L.w.dx, L.w.px);
-            L.sy() = wk_mad<MIXED>(ti, L.w.dy, L.w.py);
-            L.sz() = wk_mad<MIXED>(ti, L.w.dz, L.w.pz);
-            L.set_cell(L.w.i, L.w.j, L.w.k);
-        }
-        if (!flight) L.tau = INFINITY;
-        L.ev = hit ? E_INTERACT : (flight ? E_LOST : E_PEEL_DONE);
-        return;
-    }
-    const CrossIn in = wk_cross_begin(g, L.w, x);
-    ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? wk_cell(g, L.w) : 0);
-    L.tau = wk_mad<MIXED>(flight ? -a : a, s, L.tau);
-    L.ncw++;
-    const bool capped = L.ncw >= g.max_cross;
-    // a probe runs to the edge of the grid, the floor included; a peel-off
-    // ray stops beyond tau_peel_max or on the planet
-    const bool probe = EXT && L.mode == M_PROBE;
-    const bool dark = !flight & !probe & (L.tau > A.tau_peel_max);
-    if (!in.inside | capped | dark) {
-        if (flight) L.ev = !in.inside ? (L.w.k >= g.nlay ? E_ESCAPE : E_SURFACE) : E_LOST;
-        else L.ev = E_PEEL_DONE;
-        if (!flight && (in.inside || (L.w.k < 0 && !probe) || dark)) L.tau = INFINITY;
-        L.ncross += L.ncw;
-        L.mode = M_EVENT;
-        return;
-    }
-    wk_cross_end<MIXED>(g, L.w, x, in);
-}
-
-// Pending actions of a lane after an event; each is executed at exactly one
-// place in the kernel loop so its code (and register demand) appears once.
-enum { A_NONE = 0, A_PEEL = 1, A_FLIGHT = 2, A_SCATTER = 3, A_FINISH = 4 };
-
-// Survival weight update, scattering angle, rotation, roulette, event cap.
-// A reflection by the Lambert floor takes the same steps: its albedo is A_s,
-// its absorbed share goes to the floor, and its polar cosine about the
-// normal (held as the packet direction) is sqrt(zeta), block 1, slot a.
-template <bool MIXED, bool EXT>
-__device__ __forceinline__ int scatter(Lane& L, const GridDev& g, const BatchArgs& A, const SolveDev& S)
-{
-    const unsigned long long q = L.gid() - S.pbase;
-    const bool sf = EXT && L.surf();
-    const int c = L.cell(g);
-    const double om = sf ? A.surface_albedo : ld<MIXED>(S.omega, c);
-    const double pg = sf ? 0.0 : ld<MIXED>(S.p_gas, c), gc = sf ? 0.0 : ld<MIXED>(S.g_cld, c);
-    if (sf) {
-        double* b = A.rows + L.gid() * (unsigned long long)A.row_w + A.n_out;
-        b[B_SURF] = b[B_SURF] + L.W * (1.0 - om);
-        L.W = L.W * om;
-    } else if (A.absorption != 1) {
-        L.w_abs += L.W * (1.0 - om);
-        L.W = L.W * om;
-    }
-    const double usel = draw(A.seed, S.tag, q, L.e(), 0).b;  // scatterer choice of this event
-    U2 u1 = draw(A.seed, S.tag, q, L.e(), 1);
-    // two-term HG clouds: the forward lobe g with weight 1 - (g/2)^2 or the
-    // backward lobe -g/2, chosen by block 2, slot b of the event
-    double globe = gc;
-    if (A.cloud_phase == 1 && !sf && !(usel < pg)) {
-        const double g2 = -0.5 * gc, a = 1.0 - g2 * g2;
-        globe = draw(A.seed, S.tag, q, L.e(), 2).b < a ? gc : g2;
-    }
-    // Draine clouds (g_cld holds G): rejection from HG(G), candidate 0 from
-    // block 1, slot a with acceptance block 2, slot b; candidate k >= 1 from
-    // block 2 + k; at most 32 candidates
-    const bool draine = EXT && A.cloud_phase == 2 && !sf && !(usel < pg);
-    if (MIXED) {
-        float z = fminf((float)u1.a, 0.99999994f);
-        float mu;
-        float g32 = (float)globe;
-        auto hgs = [g32](float zz) {
-            if (fabsf(g32) < 1e-6f) return 2.0f * zz - 1.0f;
-            const float t = (1.0f - g32 * g32) / (1.0f - g32 + 2.0f * g32 * zz);
-            return (1.0f + g32 * g32 - t * t) / (2.0f * g32);
-        };
-        if (sf) {
-            mu = sqrtf(z);
-        } else if ((float)usel < (float)pg) {
-            float qq = 4.0f * z - 2.0f;
-            float u = cbrtf(qq + sqrtf(qq * qq + 1.0f));
-            mu = u - 1.0f / u;
-        } else {
-            mu = hgs(z);
-        }
-        if (draine) {
-            const float al = (float)A.draine_alpha;
-            float zc = (float)draw(A.seed, S.tag, q, L.e(), 2).b;
-            for (int k = 1; k < 32 && !(zc * (1.0f + al) < 1.0f + al * mu * mu); ++k) {
-                const U2 cd = draw(A.seed, S.tag, q, L.e(), 2 + k);
-                mu = hgs(fminf((float)cd.a, 0.99999994f));
-                zc = (float)cd.b;
-            }
-        }
-        mu = fminf(fmaxf(mu, -1.0f), 1.0f);
-        float st = sqrtf(fmaxf(1.0f - mu * mu, 0.0f));
-        float sp, cp;
-        __sincosf((float)(2.0 * kPi) * (float)u1.b, &sp, &cp);
-        float dx = (float)L.sdx(), dy = (float)L.sdy(), dz = (float)L.sdz();
-        float nx, ny, nz;
-        if (fabsf(dz) < 0.99999f) {
-            float t = sqrtf(1.0f - dz * dz);
-            float it = 1.0f / t;
-            nx = st * (dx * dz * cp - dy * sp) * it + dx * mu;
-            ny = st * (dy * dz * cp + dx * sp) * it + dy * mu;
-            nz = -st * cp * t + dz * mu;
-        } else {
-            float sgn = dz >= 0.0f ? 1.0f : -1.0f;
-            nx = st * cp;
-            ny = st * sp;
-            nz = sgn * mu;
-        }
-        // renormalised in FP64 (the traversal takes |d| = 1): one refined
-        // reciprocal square root and three products
-        double ddx = nx, ddy = ny, ddz = nz;
-        const double nn = fma(ddx, ddx, fma(ddy, ddy, ddz * ddz));
-        double y = __builtin_amdgcn_rsq(nn);
-        y = y * fma(-0.5 * nn, y * y, 1.5);
-        y = y * fma(-0.5 * nn, y * y, 1.5);
-        L.sdx() = ddx * y;
-        L.sdy() = ddy * y;
-        L.sdz() = ddz * y;
-    } else {
-        double mu = sf ? sqrt(u1.a) : ((usel < pg) ? sample_rayleigh(u1.a) : sample_hg(u1.a, globe));
-        if (draine) {
-            const double al = A.draine_alpha;
-            double zc = draw(A.seed, S.tag, q, L.e(), 2).b;
-            for (int k = 1; k < 32 && !(zc * (1.0 + al) < 1.0 + al * mu * mu); ++k) {
-                const U2 cd = draw(A.seed, S.tag, q, L.e(), 2 + k);
-                mu = sample_hg(cd.a, globe);
-                zc = cd.b;
-            }
-        }
-        rotate_dir(L.sdx(), L.sdy(), L.sdz(), mu, 2.0 * kPi * u1.b);
-    }
-    if (L.W < A.rr_threshold * L.W0()) {
-        U2 u2 = draw(A.seed, S.tag, q, L.e(), 2);
-        if (u2.a < A.rr_survive) {
-            double wn = L.W / A.rr_survive;
-            L.w_rr() -= (wn - L.W);
-            L.W = wn;
-        } else {
-            L.w_rr() += L.W;
-            L.W = 0.0;
-            L.ev = -1;
-            return A_FINISH;
-        }
-    }
-    if ((long long)L.e() >= A.max_events) {
-        L.ncapped() += 1;
-        L.ev = K_CAP;
-        return A_FINISH;
-    }
-    L.e() += 1;
-    return A_FLIGHT;
-}
-
-// Pixel of a sky-plane coordinate x on npix pixels over [-half, half].
-__device__ __forceinline__ int pixel_of(double x, double half, int npix)
-{
-    const int q = (int)floor((x + half) / (2.0 * half) * (double)npix);
-    return q < 0 ? 0 : (q >= npix ? npix - 1 : q);
 }
 
 // Bookkeeping of one event; returns the action that follows.  L.ev carries
@@ -611,19 +329,6 @@ __device__ __forceinline__ int handle_event(Lane& L, const GridDev& g, const Bat
     L.ev = L.ev == E_ESCAPE ? K_ESC : (L.ev == E_SURFACE ? K_SURF : K_LOST);
     return A_FINISH;
 }
-
-// Index of the solve that owns global packet gid (last solve with begin <= gid).
-__device__ __forceinline__ int solve_of(const BatchArgs& A, unsigned long long gid)
-{
-    int lo = 0, hi = A.n_solves - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (A.solves[mid].begin <= gid) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 
 // K4a: births of every packet of a batch (albedo: uniform on the top disk or
 // the slab's incidence; emission: cell from the biased CDF, uniform position in
@@ -821,12 +526,16 @@ __global__ void __launch_bounds__(256) k_births(GridDev g1, BatchArgs A)
     const int n = (int)(left < 256 ? left : 256) * w;
     double* dst = A.rows + r0 * (unsigned long long)w;
     for (int x = threadIdx.x; x < n; x += 256) dst[x] = sh[x];
+    if (A.head && gid < A.total) {
+        A.head[gid] = kNoRecord;
+        A.peel_cross[gid] = 0u;
+    }
 }
 
 // New packet L.gid: load its birth record and return the first action (a
 // flight for albedo, the emission-point peel-off, or finish if none emits).
 template <bool EXT>
-__device__ __forceinline__ int birth(Lane& L, const GridDev& g, const BatchArgs& A)
+__device__ __forceinline__ int birth(Lane& L, const BatchArgs& A)
 {
     const double* b = A.rows + L.gid() * (unsigned long long)A.row_w + A.n_out;
     if (EXT) {
@@ -894,7 +603,11 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
         if (__popcll(evm) < A.ev_threshold && walking != 0) continue;
         int act = A_NONE;
         if (L.mode == M_EVENT) act = handle_event<MIXED, EXT>(L, g, A);
-        if (act == A_SCATTER) act = scatter<MIXED, EXT>(L, g, A, A.solves[L.solve()]);
+        if (act == A_SCATTER) {
+            const SolveDev& S = A.solves[L.solve()];
+            const int c = L.cell(g);
+            act = scatter<MIXED, EXT>(L, A, S, ld<MIXED>(S.omega, c), ld<MIXED>(S.p_gas, c), ld<MIXED>(S.g_cld, c));
+        }
         for (int pass = 0; pass < 2; ++pass) {
             if (act == A_FINISH) {
                 finish_packet<EXT>(L, A, L.ev);
@@ -905,32 +618,10 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
             unsigned long long dead = __ballot(L.mode == M_DEAD);
             while (dead != 0) {
                 if (res_next >= res_end) {
-                    if (exhausted) break;
-                    // the packet range is split into one contiguous chunk per XCD (blocks are
-                    // dealt to the XCDs round-robin), so each XCD's L2 holds the optics of
-                    // its own solves; a wave whose chunk is drained helps the next ones
-                    unsigned long long base = 0, end = 0;
-                    if (lane == 0) {
-                        const int x0 = (int)(blockIdx.x % kXcds);
-                        for (int q = 0; q < kXcds; ++q) {
-                            const int x = (x0 + q) % kXcds;
-                            const unsigned long long lim = chunk_edge(A.total, x + 1);
-                            const unsigned long long b = atomicAdd(A.counter + x, (unsigned long long)A.batch);
-                            if (b < lim) {
-                                base = b;
-                                end = b + (unsigned long long)A.batch < lim ? b + A.batch : lim;
-                                break;
-                            }
-                        }
-                    }
-                    base = __shfl(base, 0);
-                    end = __shfl(end, 0);
-                    if (end == 0) {
+                    if (exhausted || !refill(A, lane, res_next, res_end)) {
                         exhausted = true;
                         break;
                     }
-                    res_next = base;
-                    res_end = end;
                 }
                 unsigned long long avail = res_end - res_next;
                 int cnt = __popcll(dead);
@@ -946,8 +637,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
             if (L.mode == M_DEAD && exhausted) L.mode = M_IDLE;
             if (L.mode == M_BIRTH) {
                 if (MULTI) lgrid = A.solves[solve_of(A, L.gid())].grid;
-                const GridDev& gb = MULTI ? A.grids[lgrid] : g1;
-                act = birth<EXT>(L, gb, A);
+                act = birth<EXT>(L, A);
                 const SolveDev& S = A.solves[L.solve()];  // the solve the birth record chose
                 aext = S.a_ext;
                 aabs = S.a_abs;
@@ -991,7 +681,11 @@ __global__ void __launch_bounds__(kRT) k_rows_partial(BatchArgs A, double* __res
     if (r0 < R) {
 #pragma unroll 4
         for (unsigned long long q = q0 + r0; q < qe; q += R) {
-            const double v = rows[q * (unsigned long long)w];
+            double v = rows[q * (unsigned long long)w];
+            // the rows of a split launch hold F itself also for transmission,
+            // and the crossings of the flights only
+            if (A.head && c == A.n_out + K_NCROSS) v += (double)A.peel_cross[S.begin + q];
+            if (A.head && A.trans_ms && c < A.n_out) v = rows[q * (unsigned long long)w + A.n_out + K_W0 - c] - v;
             acc = acc + v;
             acc2 = acc2 + v * v;
             if (dump && c < A.n_out) dump[(S.begin + q) * (unsigned long long)A.n_out + c] = v;
@@ -1093,8 +787,8 @@ void launch_transport_persistent(const GridDev& g, const BatchArgs& a, bool mixe
 
 int reduce_rows_chunks(unsigned long long max_n) { return (int)((max_n + kChunk - 1) / kChunk); }
 
-void launch_reduce_rows(const BatchArgs& a, const SolveDev* /*solves_host*/, int n_solves, double* partials,
-                        int chunks, double* sums, int sums_w, double* dump, hipStream_t stream)
+void launch_reduce_rows(const BatchArgs& a, int n_solves, double* partials, int chunks, double* sums, int sums_w,
+                        double* dump, hipStream_t stream)
 {
     const int pw = 2 * a.n_out + kNCounters;
     hipLaunchKernelGGL(k_rows_partial, dim3(chunks, n_solves), dim3(kRT), 0, stream, a, partials, chunks, dump);
