@@ -826,7 +826,7 @@ int split_round(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const GridDev& g, const
     launch_flight(g, A, q, mixed, multi, blocks, st);
     launch_peel(g, A, q, mixed, multi, ctx->n_cu * 5, st);
     launch_peel_sum(A, q, st);
-    HIPTRY(hipMemcpyAsync(sl.flag, q.ctl + 2 * kXcds * kCtlStride, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPTRY(hipMemcpyAsync(sl.flag, q.ctl + 2 * kXcds * kCtrStride, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     return MCRT_OK;
 }
 
@@ -964,6 +964,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     }
     batch = std::min(batch, kMaxSolvesPerLaunch);
     if (gs) batch = std::max(ng, batch / ng * ng);  // whole bands per launch
+    const int ctr_stride = sl.arena ? 1 : kCtrStride;
     void *v_opt, *v_optf = nullptr, *v_src = nullptr, *v_rows, *v_sums, *v_part, *v_ps = nullptr,
                  *v_shift = nullptr, *v_solves, *v_slots, *v_ctr;
     if ((rc = slot_scratch(ctx, sl, st, "optics", sizeof(double) * 5 * (size_t)ncell * batch, &v_opt))) return rc;
@@ -974,7 +975,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     if ((rc = slot_scratch(ctx, sl, st, "row_part", sizeof(double) * (size_t)batch * chunks * pw, &v_part))) return rc;
     if ((rc = slot_scratch(ctx, sl, st, "solves", sizeof(SolveDev) * (size_t)batch, &v_solves))) return rc;
     if ((rc = slot_scratch(ctx, sl, st, "prep_slots", sizeof(PrepSlot) * (size_t)batch, &v_slots))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "dispenser", sizeof(unsigned long long) * kXcds, &v_ctr))) return rc;
+    if ((rc = slot_scratch(ctx, sl, st, "dispenser", sizeof(unsigned long long) * kXcds * ctr_stride, &v_ctr))) return rc;
     if (mode == MCRT_MODE_EMISSION) {
         if ((rc = slot_scratch(ctx, sl, st, "sources", src_b * batch, &v_src))) return rc;
         if ((rc = slot_scratch(ctx, sl, st, "prep_scratch", sizeof(double) * prep_scratch_doubles(ncell, batch), &v_ps)))
@@ -990,6 +991,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
 
     BatchArgs A{};
     A.counter = (unsigned long long*)v_ctr;
+    A.ctr_stride = ctr_stride;
     A.rows = (double*)v_rows;
     A.row_w = prow;
     A.seed = p->seed;
@@ -1023,12 +1025,15 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     const int pblocks = ctx->n_cu * bpc;
     const uint64_t t_max = (uint64_t)(gs ? batch / ng : batch) * N;  // packets of a launch
     PeelArgs Q;
-    if ((rc = split_scratch(ctx, sl, st, p->graph != 0, t_max, no, mixed, pblocks, Q))) return rc;
+    // a split launch of few packets spreads them over all waves
+    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
+    const int fblocks = (int)std::min<uint64_t>(pblocks, (t_max + 4 * A.lanes - 1) / (4 * A.lanes));
+    if ((rc = split_scratch(ctx, sl, st, p->graph != 0, t_max, no, mixed, fblocks, Q))) return rc;
     const bool split = Q.rec != nullptr;
     A.head = Q.head;
     A.peel_cross = Q.peel_cross;
-    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
     if (split && A.lanes < 64) A.batch = A.lanes;
+    if (split && p->tune_ev_threshold <= 0) A.ev_threshold = 32;  // (flights only: 3 % faster than 16 at full launches)
     if (npix) {
         A.npix = npix;
         A.img_half = g->r_toa;
@@ -1106,7 +1111,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
         Q.resume = 1;
         while (*sl.flag != 0) {
             launch_peel_reset(Q, st);
-            if (int r2 = split_round(ctx, sl, st, g->dev, A, Q, mixed, false, pblocks)) return r2;
+            if (int r2 = split_round(ctx, sl, st, g->dev, A, Q, mixed, false, fblocks)) return r2;
             HIPTRY(hipStreamSynchronize(st));
         }
         if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt + 1], st));
@@ -1201,13 +1206,13 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
             A.solves = (const SolveDev*)v_solves;
             A.n_solves = nb;
             A.total = (unsigned long long)(gs ? nb / ng : nb) * N;
-            launch_init_dispensers(A.counter, A.total, st);
+            launch_init_dispensers(A.counter, A.ctr_stride, A.total, st);
             launch_births(g->dev, A, false, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt], st));
             if (split) {
                 Q.resume = 0;
                 launch_peel_reset(Q, st);
-                if (int r2 = split_round(ctx, sl, st, g->dev, A, Q, mixed, false, pblocks)) return r2;
+                if (int r2 = split_round(ctx, sl, st, g->dev, A, Q, mixed, false, fblocks)) return r2;
             } else {
                 launch_transport_persistent(g->dev, A, mixed, false,
                                             sl.stream_ordered ? serving_blocks(ctx, bpc) : pblocks, st);
@@ -1579,7 +1584,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
     if ((rc = slot_scratch(ctx, sl, st, "row_part", sizeof(double) * max_slots * chunks * pw, &v_part))) return rc;
     if ((rc = slot_scratch(ctx, sl, st, "solves", sizeof(SolveDev) * max_slots, &v_solves))) return rc;
     if ((rc = slot_scratch(ctx, sl, st, "prep_slots", sizeof(PrepSlot) * max_slots, &v_slots))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "dispenser", sizeof(unsigned long long) * kXcds, &v_ctr))) return rc;
+    if ((rc = slot_scratch(ctx, sl, st, "dispenser", sizeof(unsigned long long) * kXcds * kCtrStride, &v_ctr))) return rc;
     if ((rc = slot_scratch(ctx, sl, st, "grid_table", sizeof(GridDev) * grids.size(), &v_grids))) return rc;
     if ((rc = slot_scratch(ctx, sl, st, "prep_scratch", sizeof(double) * max_prep, &v_ps))) return rc;
     double* sums = (double*)v_sums;
@@ -1588,6 +1593,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
 
     BatchArgs A{};
     A.counter = (unsigned long long*)v_ctr;
+    A.ctr_stride = kCtrStride;
     A.row_w = prow;
     A.grids = (const GridDev*)v_grids;
     A.seed = common->seed;
@@ -1622,12 +1628,15 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
         t_max = std::max(t_max, t);
     }
     PeelArgs Q;
-    if ((rc = split_scratch(ctx, sl, st, common->graph != 0, t_max, no, mixed, pblocks, Q))) return rc;
+    // a split launch of few packets spreads them over all waves
+    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
+    const int fblocks = (int)std::min<uint64_t>(pblocks, (t_max + 4 * A.lanes - 1) / (4 * A.lanes));
+    if ((rc = split_scratch(ctx, sl, st, common->graph != 0, t_max, no, mixed, fblocks, Q))) return rc;
     const bool split = Q.rec != nullptr;
     A.head = Q.head;
     A.peel_cross = Q.peel_cross;
-    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
     if (split && A.lanes < 64) A.batch = A.lanes;
+    if (split && common->tune_ev_threshold <= 0) A.ev_threshold = 32;
     // Replayable form (params.graph): the chain below is recorded once per set
     // of arguments (items, parameters, launch partition, stream and scratch
     // addresses) with its host tables in pinned memory, and replayed after.
@@ -1720,7 +1729,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
         Q.resume = 1;
         while (*sl.flag != 0) {
             launch_peel_reset(Q, st);
-            if (int r2 = split_round(ctx, sl, st, hgrids[0], A, Q, mixed, true, pblocks)) return r2;
+            if (int r2 = split_round(ctx, sl, st, hgrids[0], A, Q, mixed, true, fblocks)) return r2;
             HIPTRY(hipStreamSynchronize(st));
         }
         if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li + 1], st));
@@ -1807,13 +1816,13 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
             A.solves = (const SolveDev*)v_solves;
             A.n_solves = nb;
             A.total = begin;
-            launch_init_dispensers(A.counter, A.total, st);
+            launch_init_dispensers(A.counter, A.ctr_stride, A.total, st);
             launch_births(hgrids[0], A, true, st);
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li], st));
             if (split) {
                 Q.resume = 0;
                 launch_peel_reset(Q, st);
-                if (int r2 = split_round(ctx, sl, st, hgrids[0], A, Q, mixed, true, pblocks)) return r2;
+                if (int r2 = split_round(ctx, sl, st, hgrids[0], A, Q, mixed, true, fblocks)) return r2;
             } else {
                 launch_transport_persistent(hgrids[0], A, mixed, true, pblocks, st);
             }
@@ -1956,7 +1965,7 @@ uint64_t estimate_bytes(mcrt_ctx* ctx, const Request& r, GridRes* g, OpacRes* op
     if (r.p.g_sampling) batch = std::max<uint64_t>(r.ng, batch / r.ng * r.ng);  // whole bands, as the solve rounds
     const uint64_t chunks = (uint64_t)reduce_rows_chunks(N);
     uint64_t b = opt_b * batch + row_b * batch + nsolve * row_w * 8 + batch * chunks * pw * 8 +
-                 batch * (sizeof(SolveDev) + sizeof(PrepSlot)) + 64;
+                 batch * (sizeof(SolveDev) + sizeof(PrepSlot)) + 8 * kXcds * kCtrStride;
     if (r.mode == MCRT_MODE_EMISSION) b += src_b * batch + prep_scratch_doubles((int)ncell, (int)batch) * 8;
     if (op->kind == MCRT_OPAC_HIRES) b += ncell * 8;
     return b + (1ULL << 20);

@@ -13,8 +13,9 @@
 //
 // The records live in a fixed number of slots, one region per XCD, which waves
 // take in chunks: counters that every wave of the device adds to are worth few
-// additions (one per 16 records and per 64 rays, in one cache line, made the
-// 25 x 8 x 1e5 emission solve 0.39 s instead of TIME_SPLIT).  A lane
+// additions (one per
+// event pass and per 64 rays, in one cache line, made the 25 x 8 x 1e5 emission
+// solve 0.39 s instead of 0.046).  A lane
 // that finds them full parks its packet; the host then repeats the three
 // kernels until no lane is parked.  A packet's contributions are added in the
 // order of its events whatever the rounds, so results do not depend on them,
@@ -219,9 +220,9 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     unsigned long long res_next = 0, res_end = 0;
-    bool exhausted = false;
+    bool exhausted = false, own = true;
     uint32_t rec_next = 0, rec_end = 0;  // the wave's chunk of records
-    bool full = false;                   // no region has a chunk left
+    bool full = false, rec_own = true;   // no region has a chunk left; its own has
     FLane L;
     L.C = &cold;
     L.t = threadIdx.x;
@@ -258,9 +259,8 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
         if (L.mode <= M_PROBE) walk_step<MIXED, EXT>(L, g, aext, aabs, ae, A);
         const unsigned long long walking = __ballot(L.mode <= M_PROBE);
         const unsigned long long waits = __ballot(L.mode == M_EVENT || (L.mode == M_DEAD && !exhausted));
-        // (at a launch's end a quarter of the lanes left wait for each other at most)
-        const int enough = exhausted ? (__popcll(waits | walking) + 3) / 4 : A.ev_threshold;
-        if (__popcll(waits) < enough && walking != 0) continue;
+        // ev_threshold of 64 lanes, in proportion where fewer carry packets
+        if (64 * __popcll(waits) < A.ev_threshold * __popcll(waits | walking) && walking != 0) continue;
         int act = A_NONE;
         if (L.mode == M_EVENT) act = flight_event<EXT>(L, g, A);
         if (act == A_FINISH) {
@@ -271,7 +271,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
         unsigned long long dead = __ballot(L.mode == M_DEAD);
         while (dead != 0) {
             if (res_next >= res_end) {
-                if (exhausted || !refill(A, lane, res_next, res_end)) {
+                if (exhausted || !refill(A, lane, own, res_next, res_end)) {
                     exhausted = true;
                     break;
                 }
@@ -303,15 +303,9 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
             uint32_t r = kNoRecord;
             for (uint32_t given = 0; given < n;) {
                 if (rec_next == rec_end) {
-                    uint32_t base = kNoRecord;
-                    if (lane == 0 && !full) {
-                        for (int q = 0; q < kXcds && base == kNoRecord; ++q) {
-                            const int x = (int)((blockIdx.x + q) % kXcds);
-                            const uint32_t at = atomicAdd(Q.ctl + x * kCtlStride, Q.chunk);
-                            if (at < Q.cap) base = (uint32_t)x * Q.cap + at;
-                        }
-                    }
-                    base = __shfl(base, 0);
+                    uint32_t base = kNoRecord, at;
+                    const int x = full ? -1 : take_share(Q.ctl, kCtrStride, Q.cap, Q.chunk, lane, rec_own, at);
+                    if (x >= 0) base = (uint32_t)x * Q.cap + at;
                     if (base == kNoRecord) {
                         full = true;
                         break;
@@ -394,7 +388,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
         u[5 * n] = (uint32_t)L.nint(); u[6 * n] = (uint32_t)L.ncross;
     }
     const unsigned long long left = __ballot(parked);
-    if (lane == 0 && left != 0) atomicAdd(Q.ctl + 2 * kXcds * kCtlStride, (uint32_t)__popcll(left));
+    if (lane == 0 && left != 0) atomicAdd(Q.ctl + 2 * kXcds * kCtrStride, (uint32_t)__popcll(left));
 }
 
 // The phase-function weight of a ray at cosine mu of its record, times 1/(4 pi).
@@ -441,7 +435,9 @@ __device__ __forceinline__ double peel_weight(const BatchArgs& A, double w, doub
 // One peel-off ray per lane: ray q of region x is observer q % n_out of its
 // record q / n_out, taken by waves of the region's XCD first (whose L2 holds the optics the region's flights used).
 enum { P_IDLE = 0, P_WALK = 1, P_DONE = 2 };
-constexpr int kPeelThreshold = 16;  // lanes without a ray that trigger the handing out of new ones
+// Lanes without a ray that trigger the handing out of new ones: a start costs
+// about two steps.  8: 50.5 ms, 16: 46.1, 24: 45.9, 32: 47.3 (25 x 8 x 1e5 emission packets, mixed)
+constexpr int kPeelThreshold = 24;
 
 template <bool MIXED, bool MULTI>
 __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
@@ -460,7 +456,16 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     Prop<MIXED> ae = 0;
     const void* aext = nullptr;
     uint32_t res_next = 0, res_end = 0, region = 0;  // the wave's rays
-    int turn = 0;                                    // regions tried so far
+    bool more = true;                                // a region may have rays left
+    uint32_t rays = 0;                               // lane x: those of region x
+    if (lane < kXcds) {
+        const uint32_t n = Q.ctl[lane * kCtrStride];
+        rays = (n < Q.cap ? n : Q.cap) * n_out;
+    }
+    bool own = true;
+    // an eighth of a wave's part of its XCD's rays at once
+    uint32_t share = __shfl(rays, (int)(blockIdx.x % kXcds)) / (gridDim.x / kXcds * (kTPB / 64) * 8u + 1u) & ~63u;
+    if (share < 64u) share = 64u;
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
         if (state == P_WALK) {
@@ -487,8 +492,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
             }
         }
         const unsigned long long walking = __ballot(state == P_WALK);
-        const bool more = turn < kXcds || res_next < res_end;
-        if (walking != 0 && (!more || 64 - __popcll(walking) < kPeelThreshold)) continue;
+        if (walking != 0 && ((!more && res_next >= res_end) || 64 - __popcll(walking) < kPeelThreshold)) continue;
         if (state == P_DONE) {
             state = P_IDLE;
             double f;
@@ -528,29 +532,16 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
         unsigned long long idle = __ballot(state == P_IDLE);
         while (idle != 0) {
             if (res_next >= res_end) {
-                while (turn < kXcds) {
-                    region = (uint32_t)((blockIdx.x + turn) % kXcds);
-                    uint32_t b0 = 0, e0 = 0;
-                    if (lane == 0) {
-                        const uint32_t n = Q.ctl[region * kCtlStride];
-                        const uint32_t rays = (n < Q.cap ? n : Q.cap) * n_out;
-                        // an eighth of an XCD's wave's share at once
-                        const uint32_t share = rays / (gridDim.x / kXcds * (kTPB / 64) * 8u + 1u) & ~63u;
-                        const uint32_t b = atomicAdd(Q.ctl + (kXcds + region) * kCtlStride, share < 64u ? 64u : share);
-                        if (b < rays) {
-                            b0 = b;
-                            e0 = b + (share < 64u ? 64u : share) < rays ? b + (share < 64u ? 64u : share) : rays;
-                        }
-                    }
-                    res_next = __shfl(b0, 0);
-                    res_end = __shfl(e0, 0);
-                    if (res_end != 0) break;
-                    ++turn;
-                }
-                if (turn >= kXcds) {
-                    res_next = res_end = 0;
+                uint32_t at = 0;
+                const int x = more ? take_share(Q.ctl + kXcds * kCtrStride, kCtrStride, rays, share, lane, own, at) : -1;
+                if (x < 0) {
+                    more = false;
                     break;
                 }
+                region = (uint32_t)x;
+                const uint32_t lim = __shfl(rays, x);
+                res_next = at;
+                res_end = at + share < lim ? at + share : lim;
             }
             const uint32_t avail = res_end - res_next;
             const uint32_t cnt = (uint32_t)__popcll(idle);
@@ -605,7 +596,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
                 }
             }
         }
-        if (__ballot(state != P_IDLE) == 0 && turn >= kXcds && res_next >= res_end) break;
+        if (__ballot(state != P_IDLE) == 0 && !more && res_next >= res_end) break;
     }
 }
 
@@ -641,7 +632,7 @@ __global__ void __launch_bounds__(256) k_peel_sum(BatchArgs A, PeelArgs Q)
 
 __global__ void k_peel_reset(PeelArgs Q)
 {
-    if (threadIdx.x <= 2 * kXcds) Q.ctl[threadIdx.x * kCtlStride] = 0u;
+    if (threadIdx.x <= 2 * kXcds) Q.ctl[threadIdx.x * kCtrStride] = 0u;
 }
 
 }  // namespace

@@ -9,6 +9,7 @@ namespace mcrt {
 constexpr int kMaxObs = 8;
 constexpr int kMaxSolvesPerLaunch = 1 << 20;  // solve index field of the transport's packed lane state
 constexpr int kXcds = 8;                      // packet dispensers per launch, one per XCD
+constexpr int kCtrStride = 32;                // words between counters that all waves share (cache lines of their own)
 constexpr int kNCounters = 11;
 enum Counter { K_ESC = 0, K_SURF, K_ABS, K_RR, K_CAP, K_LOST, K_NINT, K_NCROSS, K_NCAPPED, K_NLOST, K_W0 };
 
@@ -106,6 +107,7 @@ struct BatchArgs {
     const GridDev* grids;  // per-solve grids of a multi-grid launch (else unused)
     unsigned long long total;     // packets over all solves
     unsigned long long* counter;  // kXcds packet dispensers (one chunk of the packets each)
+    int ctr_stride;               // elements between them (cache lines of their own where scratch allows)
     double* rows;                 // [total][row_w]: F per observer, then counters
     int row_w;
     uint64_t seed;
@@ -164,8 +166,7 @@ struct PeelArgs {
     int n_lanes;      // lanes of the flight kernel (the same in every round of a launch)
     int resume;       // not the first round
 };
-constexpr int kCtlStride = 32;  // words
-constexpr int kPeelCtl = (2 * kXcds + 1) * kCtlStride;
+constexpr int kPeelCtl = (2 * kXcds + 1) * kCtrStride;
 constexpr int kParkD = 10, kParkU = 9;
 size_t peel_record_bytes(bool mixed);
 void launch_peel_reset(const PeelArgs& q, hipStream_t stream);
@@ -201,7 +202,7 @@ void launch_reduce_rows(const BatchArgs& a, int n_solves, double* partials, int 
                         double* dump, hipStream_t stream);
 int reduce_rows_chunks(unsigned long long max_n);
 void launch_fill_u64(unsigned long long* p, unsigned long long v, hipStream_t stream);
-void launch_init_dispensers(unsigned long long* counters, unsigned long long total, hipStream_t stream);
+void launch_init_dispensers(unsigned long long* counters, int stride, unsigned long long total, hipStream_t stream);
 void launch_fill_f64(double* p, size_t n, double v, hipStream_t stream);
 void launch_births(const GridDev& g, const BatchArgs& a, bool multi, hipStream_t stream);
 

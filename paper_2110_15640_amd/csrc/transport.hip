@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     unsigned long long res_next = 0, res_end = 0;
-    bool exhausted = false;
+    bool exhausted = false, own = true;
     Lane L;
     L.C = &cold;
     L.F = Fsh;
@@ -618,7 +618,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
             unsigned long long dead = __ballot(L.mode == M_DEAD);
             while (dead != 0) {
                 if (res_next >= res_end) {
-                    if (exhausted || !refill(A, lane, res_next, res_end)) {
+                    if (exhausted || !refill(A, lane, own, res_next, res_end)) {
                         exhausted = true;
                         break;
                     }
@@ -747,9 +747,9 @@ __global__ void k_fill_u64(unsigned long long* p, unsigned long long v)
 
 // Packet dispensers of a launch: counter x starts at the first packet of
 // chunk x = [edge(x), edge(x + 1)), edge(x) = floor(total * x / kXcds).
-__global__ void k_init_dispensers(unsigned long long* c, unsigned long long total)
+__global__ void k_init_dispensers(unsigned long long* c, int stride, unsigned long long total)
 {
-    if (blockIdx.x == 0 && threadIdx.x < kXcds) c[threadIdx.x] = chunk_edge(total, (int)threadIdx.x);
+    if (blockIdx.x == 0 && threadIdx.x < kXcds) c[threadIdx.x * stride] = chunk_edge(total, (int)threadIdx.x);
 }
 
 // Fill n doubles (a kernel, so that recorded graphs hold no memset nodes).
@@ -800,9 +800,9 @@ void launch_fill_u64(unsigned long long* p, unsigned long long v, hipStream_t st
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, stream, p, v);
 }
 
-void launch_init_dispensers(unsigned long long* counters, unsigned long long total, hipStream_t stream)
+void launch_init_dispensers(unsigned long long* counters, int stride, unsigned long long total, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_init_dispensers, dim3(1), dim3(64), 0, stream, counters, total);
+    hipLaunchKernelGGL(k_init_dispensers, dim3(1), dim3(64), 0, stream, counters, stride, total);
 }
 
 void launch_fill_f64(double* p, size_t n, double v, hipStream_t stream)
