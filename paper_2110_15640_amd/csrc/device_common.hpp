@@ -560,6 +560,21 @@ enum {
     WE_FROM_HI = 4   // ... through its upper edge
 };
 
+// The geometry a walk is compiled for: spherical, slab, or the grid's own.
+enum { GEO_SPHERE = 0, GEO_SLAB = 1, GEO_ANY = 2 };
+template <int GEO>
+__host__ __device__ __forceinline__ bool wk_slab(const GridDev& g)
+{
+    if constexpr (GEO == GEO_ANY) return g.geom == 1;
+    else return GEO == GEO_SLAB;
+}
+
+// v, negated where the top bit of m is set (m = -1 or 1: a sign).
+__host__ __device__ __forceinline__ double wk_flip(double v, int m)
+{
+    return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ ((uint64_t)((uint32_t)m & 0x80000000u) << 32));
+}
+
 // The face table's entry e (a 32-bit offset from one uniform base).
 __host__ __device__ __forceinline__ double2 wk_face(const GridDev& g, int e)
 {
@@ -577,16 +592,17 @@ struct ConePick {
     double s;
     bool met, upper;
 };
-__host__ __device__ __forceinline__ ConePick wk_cone_pick(const Walker& w, double q2, double Pz, bool up, double sl, double su)
+__host__ __device__ __forceinline__ ConePick wk_cone_pick(const Walker& w, double q2, double Pz, int dj, double sl, double su)
 {
     ConePick p;
+    const bool up = dj > 0;
     const double M = fma(Pz, Pz, (q2 * w.dz) * w.dz);
     const double sf = up ? su : sl, sb = up ? sl : su;  // the edges in front and behind
-    const double mf = up ? sf : -sf, mb = up ? sb : -sb, mz = up ? w.dz : -w.dz, mP = up ? Pz : -Pz;
-    const bool turn = mP > 0.0;  // the extremum is ahead
-    const bool reach = fma(-(sf * sf), q2, M) >= 0.0, past_f = mz > mf, past_b = mz < mb;
-    const bool front = (turn & reach) | (!turn & past_f);
-    const bool back = !front & turn & past_b;
+    const double mz = wk_flip(w.dz, dj);
+    const bool turn = wk_flip(Pz, dj) > 0.0;  // the extremum is ahead
+    const double reach = turn ? fma(-(sf * sf), q2, M) : mz - wk_flip(sf, dj);
+    const bool front = reach > 0.0;
+    const bool back = !front & turn & (mz < wk_flip(sb, dj));
     p.s = front ? sf : sb;
     p.met = front | back;
     p.upper = up == front;
@@ -657,7 +673,7 @@ __host__ __device__ __forceinline__ double wk_cos2(const GridDev& g, const Walke
 }
 
 // Start of a walk at (px, py, pz) in cell (i, j, k) along unit d.
-template <bool FAST>
+template <bool FAST, int GEO = GEO_ANY>
 __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, double px, double py, double pz,
                                                   double dx, double dy, double dz, int i, int j, int k)
 {
@@ -669,7 +685,7 @@ __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, d
     w.far = 0.0;
     w.eq = 0;
     const double2 fr = wk_face(g, k);
-    if (g.geom == 1) {
+    if (wk_slab<GEO>(g)) {
         w.B0 = w.C0 = 0.0;
         w.dk = dz > 0.0 ? 1 : -1;
         w.dj = w.di = 1;
@@ -696,7 +712,8 @@ __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, d
     w.dk = inward ? -1 : 1;
     w.di = east ? 1 : -1;
     const double q2 = fma(-B, B, C0), Pz = fma(-B, dz, pz);
-    const ConePick p = wk_cone_pick(w, q2, Pz, fma(dz, q2, -(Pz * B)) > 0.0, fc.x, fc.y);  // the sign of d sin(lat) / dt
+    // (rising or falling: the sign of d sin(lat) / dt)
+    const ConePick p = wk_cone_pick(w, q2, Pz, fma(dz, q2, -(Pz * B)) > 0.0 ? 1 : -1, fc.x, fc.y);
     w.dj = p.upper ? 1 : -1;
     double num, den, a, b, c;
     wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
@@ -720,13 +737,20 @@ struct CrossKind {
     double t;
     bool shell, cone, none;
 };
+template <int GEO = GEO_ANY>
 __host__ __device__ __forceinline__ CrossKind wk_next(const Walker& w)
 {
     CrossKind x;
-    x.t = wk_min(wk_min(w.ts, w.tc), w.tp);
-    x.shell = w.ts <= x.t;
-    x.cone = !x.shell & (w.tc <= x.t);
-    x.none = !(x.t < INFINITY);
+    if constexpr (GEO == GEO_SLAB) {
+        x.t = w.ts;
+        x.shell = true;
+        x.cone = false;
+    } else {
+        x.t = wk_min(wk_min(w.ts, w.tc), w.tp);
+        x.shell = w.ts <= x.t;
+        x.cone = !x.shell & (w.tc <= x.t);
+    }
+    x.none = GEO != GEO_SPHERE && !(x.t < INFINITY);
     return x;
 }
 
@@ -739,10 +763,17 @@ struct CrossIn {
 };
 
 // Index update and table load of a crossing (of a face), without branches.
+template <int GEO = GEO_ANY>
 __host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Walker& w, const CrossKind& x)
 {
     CrossIn in;
     w.t = x.t;
+    if constexpr (GEO == GEO_SLAB) {
+        w.k += w.dk;
+        in.inside = (unsigned)w.k < (unsigned)g.nlay;
+        in.f = wk_face(g, in.inside ? w.k : 0);
+        return in;
+    }
     int ni = w.i + w.di;
     ni = ni == g.nlon ? 0 : (ni < 0 ? g.nlon - 1 : ni);
     w.k += x.shell ? w.dk : 0;
@@ -755,57 +786,53 @@ __host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Wal
 }
 
 // The face that replaces the one just crossed.
-template <bool FAST>
+template <bool FAST, int GEO = GEO_ANY>
 __host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& w, const CrossKind& x, const CrossIn& in)
 {
     const bool outward = w.dk > 0;
     const double R = outward ? in.f.y : in.f.x;
-    if (g.geom == 1) {
+    if (wk_slab<GEO>(g)) {
         w.ts = wk_max(wk_div<FAST>(R - w.pz, w.dz), w.t);
         return;
     }
-    // a t^2 + 2 b t + c of the shell or cone
-    double b = w.B0, c = wk_mad<FAST>(-R, R, w.C0), a = 1.0;
-    double D = wk_mad<FAST>(b, b, -c);
-    ConePick p{};
+    // shell: t^2 + 2 B0 t + c; cone: ca t^2 + 2 cb t + cc
+    const double c = wk_mad<FAST>(-R, R, w.C0);
+    double D = wk_mad<FAST>(w.B0, w.B0, -c);
+    double ca, cb, cc;
+    ConePick p;
     if (x.cone) {
-        const bool up = w.dj > 0;
-        p = wk_cone_pick(w, fma(-w.B0, w.B0, w.C0), fma(-w.B0, w.dz, w.pz), up, in.f.x, in.f.y);
+        const int dj = w.dj;
+        p = wk_cone_pick(w, fma(-w.B0, w.B0, w.C0), fma(-w.B0, w.dz, w.pz), dj, in.f.x, in.f.y);
         w.dj = p.upper ? 1 : -1;
-        if (g.eq_edge > 0 && wk_at_eq(g, w.j)) w.eq = WE_ROW | (up ? WE_FROM_LO : WE_FROM_HI);
-        wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), a, b, c);
-        D = wk_mad<FAST>(b, b, -(a * c));
+        if (g.eq_edge > 0 && wk_at_eq(g, w.j)) w.eq = WE_ROW | (dj > 0 ? WE_FROM_LO : WE_FROM_HI);
+        wk_cone_coef<FAST>(w, p.s, wk_cos2<FAST>(g, w, p), ca, cb, cc);
+        D = wk_mad<FAST>(cb, cb, -(ca * cc));
     }
     const double sq = wk_sqrt<FAST>(D);
-    // the shell's root: the far one of a sphere whose nearest point is still
-    // ahead as q, else as c / q
-    const double q = b > 0.0 ? -(b + sq) : -b + sq;
-    const bool qfar = outward & !(b > 0.0);
-    double num, den;
-    if constexpr (FAST) {
-        num = qfar ? q * q : c;
-        den = q;
-    } else {
-        num = qfar ? q : c;
-        den = qfar ? 1.0 : q;
-    }
+    // the shell's root: with m = |B0| + sqrt(D), the far one of a sphere whose
+    // nearest point is still ahead is m, any other next one c / m up to sign
+    const double m = fabs(w.B0) + sq;
+    const bool past = w.B0 > 0.0, mfar = outward & !past;
+    double num = past ? -c : c, den = m;
+    if constexpr (FAST) num = mfar ? m * m : num;
     bool met = true;
     if (x.cone) {
-        wk_cone_root<FAST>(w, p, a, b, c, sq, num, den);
+        wk_cone_root<FAST>(w, p, ca, cb, cc, sq, num, den);
         met = p.met;
     } else if (!x.shell) {
         const double nx = -in.f.x, ny = in.f.y;
         den = wk_mad<FAST>(w.dx, nx, w.dy * ny);
         num = -wk_mad<FAST>(w.px, nx, w.py * ny);
-        met = (w.di > 0 ? den : -den) > 0.0;
+        met = wk_flip(den, w.di) > 0.0;
     }
     const bool finite = den != 0.0;
-    const double r = wk_root<FAST>(num, den);
+    double r = wk_root<FAST>(num, den);
     if (x.shell) {
+        if constexpr (!FAST) r = mfar ? m : r;
         const bool hit = outward | ((D >= 0.0) & ((r >= w.t) | (c < 0.0)));
         w.ts = wk_max(hit ? (finite ? r : 0.0) : w.far, w.t);
         w.dk = hit ? w.dk : 1;
-        w.far = q;
+        w.far = m;
     } else {
         const double v = (met & finite) ? wk_max(r, w.t) : INFINITY;
         w.tc = x.cone ? v : w.tc;

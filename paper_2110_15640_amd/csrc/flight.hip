@@ -191,7 +191,7 @@ __device__ __forceinline__ int flight_event(FLane& L, const GridDev& g, const Ba
 
 // The packet's next flight (its optical depth from the event's block 0, slot
 // a, unless a forced interaction chose it) or the probe before a forced one.
-template <bool MIXED, bool EXT>
+template <bool MIXED, bool EXT, int GEO>
 __device__ __forceinline__ void start_flight(FLane& L, const GridDev& g, const BatchArgs& A)
 {
     int kind = M_FLIGHT;
@@ -207,12 +207,12 @@ __device__ __forceinline__ void start_flight(FLane& L, const GridDev& g, const B
         const SolveDev& S = A.solves[L.solve()];
         L.tau = -log(draw(A.seed, S.tag, L.gid() - S.pbase, L.e(), 0).a);
     }
-    wk_start<MIXED>(g, L.w, L.w.px, L.w.py, L.w.pz, L.w.dx, L.w.dy, L.w.dz, L.si(), L.sj(), L.sk());
+    wk_start<MIXED, GEO>(g, L.w, L.w.px, L.w.py, L.w.pz, L.w.dx, L.w.dy, L.w.dz, L.si(), L.sj(), L.sk());
     L.ncw = 0;
     L.mode = kind;
 }
 
-template <bool MIXED, bool MULTI, bool EXT>
+template <bool MIXED, bool MULTI, bool EXT, int GEO>
 __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, PeelArgs Q)
 {
     __shared__ FlightLDS cold;
@@ -255,8 +255,8 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
     }
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
-        if (L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
-        if (L.mode <= M_PROBE) walk_step<MIXED, EXT>(L, g, aext, aabs, ae, A);
+        if (GEO != GEO_SLAB && L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
+        if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO>(L, g, aext, aabs, ae, A);
         const unsigned long long walking = __ballot(L.mode <= M_PROBE);
         const unsigned long long waits = __ballot(L.mode == M_EVENT || (L.mode == M_DEAD && !exhausted));
         // ev_threshold of 64 lanes, in proportion where fewer carry packets
@@ -368,7 +368,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
         if (act == A_FINISH) finish_counters<EXT>(L, A, L.ev);
         if (act == A_FLIGHT) {
             ae = (Prop<MIXED>)ld<MIXED>(aext, L.cell(ga));
-            start_flight<MIXED, EXT>(L, ga, A);
+            start_flight<MIXED, EXT, GEO>(L, ga, A);
         }
         if (__ballot(L.mode != M_IDLE && L.mode != M_PARKED) == 0) break;
     }
@@ -439,7 +439,7 @@ enum { P_IDLE = 0, P_WALK = 1, P_DONE = 2 };
 // about two steps.  8: 50.5 ms, 16: 46.1, 24: 45.9, 32: 47.3 (25 x 8 x 1e5 emission packets, mixed)
 constexpr int kPeelThreshold = 24;
 
-template <bool MIXED, bool MULTI>
+template <bool MIXED, bool MULTI, int GEO>
 __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
 {
     __shared__ double sobs[2 * 3 * kMaxObs];
@@ -469,26 +469,22 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
         if (state == P_WALK) {
-            if (g.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(g, w);
-            const CrossKind x = wk_next(w);
-            if (x.none) {
-                tau = INFINITY;
+            if (GEO != GEO_SLAB && g.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(g, w);
+            // (a slab ray that meets no face was dark from the start)
+            const CrossKind x = wk_next<GEO>(w);
+            const double s = x.t - w.t, a = (double)ae;
+            const CrossIn in = wk_cross_begin<GEO>(g, w, x);
+            ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? wk_cell(g, w) : 0);
+            tau = wk_mad<MIXED>(a, s, tau);
+            ncw++;
+            // the ray ends at the top; beyond tau_peel_max, on the planet or
+            // after too many cells nothing of it arrives
+            const bool dark = tau > A.tau_peel_max;
+            if (!in.inside | dark | (ncw >= g.max_cross)) {
+                if (dark | in.inside | (w.k < 0)) tau = INFINITY;
                 state = P_DONE;
             } else {
-                const double s = x.t - w.t, a = (double)ae;
-                const CrossIn in = wk_cross_begin(g, w, x);
-                ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? wk_cell(g, w) : 0);
-                tau = wk_mad<MIXED>(a, s, tau);
-                ncw++;
-                // the ray ends at the top; beyond tau_peel_max, on the planet
-                // or after too many cells nothing of it arrives
-                const bool dark = tau > A.tau_peel_max;
-                if (!in.inside | dark | (ncw >= g.max_cross)) {
-                    if (dark | in.inside | (w.k < 0)) tau = INFINITY;
-                    state = P_DONE;
-                } else {
-                    wk_cross_end<MIXED>(g, w, x, in);
-                }
+                wk_cross_end<MIXED, GEO>(g, w, x, in);
             }
         }
         const unsigned long long walking = __ballot(state == P_WALK);
@@ -581,7 +577,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
                 }
                 const double mu = v.nx * dx + v.ny * dy + v.nz * dz;
                 // a slab ray that never reaches the top, a floor ray below the horizon
-                const bool dark = (gs.geom == 1 && !(dz > 0.0)) || (kind == R_FLOOR && !(mu > 0.0));
+                const bool dark = (GEO == GEO_SLAB && !(dz > 0.0)) || (kind == R_FLOOR && !(mu > 0.0));
                 if (kind == R_BIRTH) wt = v.w;
                 else if (kind == R_FLOOR) wt = mu > 0.0 ? v.w * (mu / kPi) : 0.0;
                 else wt = peel_weight<MIXED>(A, v.w, mu, (double)v.pg, (double)v.gc);
@@ -589,7 +585,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
                 ncw = 0;
                 const int i = (int)(v.ijk & 0x7FFu), j = (int)((v.ijk >> 11) & 0x3FFu), k = (int)(v.ijk >> 21);
                 ae = (Prop<MIXED>)ld<MIXED>(aext, (k * gs.nlat + j) * gs.nlon + i);
-                wk_start<MIXED>(gs, w, px, py, v.z, dx, dy, dz, i, j, k);
+                wk_start<MIXED, GEO>(gs, w, px, py, v.z, dx, dy, dz, i, j, k);
                 if (dark) {
                     tau = INFINITY;
                     state = P_DONE;
@@ -649,23 +645,44 @@ void launch_flight(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool
 {
     const bool ext = a.surface_albedo > 0.0 || a.cloud_phase == 2 || a.forced != 0 || a.trans_ms != 0 ||
                      a.absorption == 1;
-#define MCRT_K4(MX, MU)                                                                                   \
-    if (ext) hipLaunchKernelGGL((k_flight<MX, MU, true>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q); \
-    else hipLaunchKernelGGL((k_flight<MX, MU, false>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q);
-    if (mixed && multi) { MCRT_K4(true, true) }
-    else if (mixed) { MCRT_K4(true, false) }
-    else if (multi) { MCRT_K4(false, true) }
-    else { MCRT_K4(false, false) }
-#undef MCRT_K4
+    // (slabs come without a grid table)
+    const int geo = multi ? GEO_SPHERE : g.geom;
+#define MCRT_K(MX, MU, EX, GE) hipLaunchKernelGGL((k_flight<MX, MU, EX, GE>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q)
+#define MCRT_KX(MX, MU, GE)                \
+    do {                                   \
+        if (ext) MCRT_K(MX, MU, true, GE); \
+        else MCRT_K(MX, MU, false, GE);    \
+    } while (0)
+    if (geo == GEO_SLAB) {
+        if (mixed) MCRT_KX(true, false, GEO_SLAB);
+        else MCRT_KX(false, false, GEO_SLAB);
+    } else if (multi) {
+        if (mixed) MCRT_KX(true, true, GEO_SPHERE);
+        else MCRT_KX(false, true, GEO_SPHERE);
+    } else {
+        if (mixed) MCRT_KX(true, false, GEO_SPHERE);
+        else MCRT_KX(false, false, GEO_SPHERE);
+    }
+#undef MCRT_KX
+#undef MCRT_K
 }
 
 void launch_peel(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool mixed, bool multi, int blocks,
                  hipStream_t stream)
 {
-    if (mixed && multi) hipLaunchKernelGGL((k_peel<true, true>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q);
-    else if (mixed) hipLaunchKernelGGL((k_peel<true, false>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q);
-    else if (multi) hipLaunchKernelGGL((k_peel<false, true>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q);
-    else hipLaunchKernelGGL((k_peel<false, false>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q);
+    const int geo = multi ? GEO_SPHERE : g.geom;
+#define MCRT_K(MX, MU, GE) hipLaunchKernelGGL((k_peel<MX, MU, GE>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q)
+    if (geo == GEO_SLAB) {
+        if (mixed) MCRT_K(true, false, GEO_SLAB);
+        else MCRT_K(false, false, GEO_SLAB);
+    } else if (multi) {
+        if (mixed) MCRT_K(true, true, GEO_SPHERE);
+        else MCRT_K(false, true, GEO_SPHERE);
+    } else {
+        if (mixed) MCRT_K(true, false, GEO_SPHERE);
+        else MCRT_K(false, false, GEO_SPHERE);
+    }
+#undef MCRT_K
 }
 
 void launch_peel_sum(const BatchArgs& a, const PeelArgs& q, hipStream_t stream)

@@ -80,11 +80,11 @@ using Prop = typename std::conditional<MIXED, float, double>::type;
 // the walk's cell, gathered when the cell was entered (wk_start's first cell:
 // by the caller), so that a step's end and the next one's start cover the
 // gather's latency.
-template <bool MIXED, bool EXT, class LaneT>
+template <bool MIXED, bool EXT, int GEO, class LaneT>
 __device__ __forceinline__ void walk_step(LaneT& L, const GridDev& g, const void* aext, const void* aabs,
                                           Prop<MIXED>& ae, const BatchArgs& A)
 {
-    const CrossKind x = wk_next(L.w);
+    const CrossKind x = wk_next<GEO>(L.w);
     const double s = x.t - L.w.t;
     const bool flight = L.mode == M_FLIGHT;
     double a = (double)ae;
@@ -116,7 +116,7 @@ __device__ __forceinline__ void walk_step(LaneT& L, const GridDev& g, const void
         L.ev = hit ? E_INTERACT : (flight ? E_LOST : E_PEEL_DONE);
         return;
     }
-    const CrossIn in = wk_cross_begin(g, L.w, x);
+    const CrossIn in = wk_cross_begin<GEO>(g, L.w, x);
     ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? wk_cell(g, L.w) : 0);
     L.tau = wk_mad<MIXED>(flight ? -a : a, s, L.tau);
     L.ncw++;
@@ -133,7 +133,7 @@ __device__ __forceinline__ void walk_step(LaneT& L, const GridDev& g, const void
         L.mode = M_EVENT;
         return;
     }
-    wk_cross_end<MIXED>(g, L.w, x, in);
+    wk_cross_end<MIXED, GEO>(g, L.w, x, in);
 }
 
 // Pending actions of a lane after an event; each is executed at exactly one
