@@ -90,6 +90,10 @@ struct Slot {
     std::vector<hipEvent_t> prof_ev;  // pairs around timed launches
     uint32_t* flag = nullptr;         // pinned word (parked lanes of a split launch)
     std::map<std::string, DevBuf> scratch;  // grow-only, by role
+    // scratch of forms that a solve takes only where it fits: given back when
+    // another allocation of the slot does not (never while the solve uses it)
+    std::map<std::string, DevBuf> spare;
+    bool spare_busy = false;
     bool stream_ordered = false;  // serving slots allocate with hipMallocAsync
     // Fixed arena (the allocation-free solve): scratch is carved from it in
     // order, from offset 0 at every call, instead of allocated.
@@ -246,7 +250,13 @@ void dev_free(mcrt_ctx* ctx, DevBuf& b, hipStream_t ordered = nullptr)
 }
 
 // Scratch buffer of at least `bytes` under `name` in slot `sl` (grow-only).
-int slot_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const char* name, size_t bytes, void** out)
+void release_spare(mcrt_ctx* ctx, Slot& sl)
+{
+    for (auto& kv : sl.spare) dev_free(ctx, kv.second, sl.stream_ordered ? sl.stream : nullptr);
+    sl.spare.clear();
+}
+
+int slot_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const char* name, size_t bytes, void** out, bool spare = false)
 {
     if (sl.arena) {
         const size_t at = (sl.arena_off + 255) & ~(size_t)255;
@@ -257,7 +267,7 @@ int slot_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const char* name, size
         sl.arena_off = at + bytes;
         return MCRT_OK;
     }
-    DevBuf& b = sl.scratch[name];
+    DevBuf& b = (spare ? sl.spare : sl.scratch)[name];
     if (b.bytes < bytes) {
         if (b.p) {
             if (!sl.stream_ordered) {  // the old buffer may still be read by queued work
@@ -267,9 +277,61 @@ int slot_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const char* name, size
             dev_free(ctx, b, sl.stream_ordered ? st : nullptr);
         }
         int rc = dev_alloc(ctx, bytes, b, sl.stream_ordered ? st : nullptr);
+        if ((rc == MCRT_EBUDGET || rc == MCRT_ENOMEM) && !spare && !sl.spare_busy && !sl.spare.empty()) {
+            if (!sl.stream_ordered) HIPTRY(hipStreamSynchronize(sl.stream));
+            release_spare(ctx, sl);
+            rc = dev_alloc(ctx, bytes, b, sl.stream_ordered ? st : nullptr);
+        }
         if (rc) return rc;
     }
     *out = b.p;
+    return MCRT_OK;
+}
+
+// What the budget leaves a blocking slot.  Its own scratch is regrown in place
+// (each buffer freed before its larger successor is allocated), so it counts as
+// room: repeated calls then plan the same launches as the first.
+uint64_t slot_room(mcrt_ctx* ctx, const Slot& sl)
+{
+    uint64_t own = 0;
+    for (const auto& kv : sl.scratch) own += kv.second.bytes;
+    for (const auto& kv : sl.spare) own += kv.second.bytes;
+    std::lock_guard<std::mutex> mk(ctx->mem_mu);
+    const uint64_t held = held_locked(ctx);
+    return ctx->budget - std::min(ctx->budget, held - std::min(held, own));
+}
+
+// Scratch of an optional form, all or nothing: whether it is there.
+struct Want {
+    const char* name;
+    size_t bytes;
+};
+int spare_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const Want* want, int n, void** p, bool& there)
+{
+    there = false;
+    uint64_t more = 0, all = 0, spare = 0;
+    for (int i = 0; i < n; ++i) {
+        const size_t have = sl.spare[want[i].name].bytes;
+        if (want[i].bytes > have) more += want[i].bytes - have;
+        all += want[i].bytes;
+    }
+    for (const auto& kv : sl.spare) spare += kv.second.bytes;
+    bool fits, fits_alone;  // beside the spare scratch that is held; in its place
+    {
+        std::lock_guard<std::mutex> mk(ctx->mem_mu);
+        const uint64_t held = held_locked(ctx);
+        fits = held + more <= ctx->budget;
+        fits_alone = held - spare + all <= ctx->budget;
+    }
+    if (!fits) {
+        if (sl.spare_busy || !fits_alone) return MCRT_OK;
+        HIPTRY(hipStreamSynchronize(sl.stream));
+        release_spare(ctx, sl);
+    }
+    for (int i = 0; i < n; ++i)
+        if (int rc = slot_scratch(ctx, sl, st, want[i].name, want[i].bytes, &p[i], true))
+            return rc == MCRT_EBUDGET || rc == MCRT_ENOMEM ? MCRT_OK : rc;
+    there = true;
     return MCRT_OK;
 }
 
@@ -277,6 +339,7 @@ void release_scratch(mcrt_ctx* ctx, Slot& sl)
 {
     for (auto& kv : sl.scratch) dev_free(ctx, kv.second, sl.stream_ordered ? sl.stream : nullptr);
     sl.scratch.clear();
+    release_spare(ctx, sl);
 }
 
 // A stream on a hardware queue of its own: made with a CU mask that covers
@@ -710,7 +773,7 @@ void drop_graphs(mcrt_ctx* ctx, int32_t gid, int32_t oid)
 bool reclaim_main(mcrt_ctx* ctx)
 {
     std::unique_lock<std::mutex> lk(ctx->main_mu, std::try_to_lock);
-    if (!lk.owns_lock() || ctx->main.scratch.empty()) return false;
+    if (!lk.owns_lock() || (ctx->main.scratch.empty() && ctx->main.spare.empty())) return false;
     (void)hipSetDevice(ctx->device);
     (void)hipStreamSynchronize(ctx->main.stream);
     drop_graphs(ctx, 0, 0);
@@ -778,31 +841,20 @@ int split_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, bool use_graph, uint6
     // a wave's chunk: an eighth of its share, so that few slots stay empty
     const uint64_t chunk = std::min<uint64_t>(std::max<uint64_t>(recs * 64 / (lanes * 8), 16), 256);
     recs = (recs + kXcds * chunk - 1) / (kXcds * chunk) * (kXcds * chunk);
-    const struct {
-        const char* name;
-        size_t bytes;
-    } want[9] = {{"peel_rec", peel_record_bytes(mixed) * recs},
-                 {"peel_next", sizeof(uint32_t) * recs},
-                 {"peel_f", sizeof(double) * n_out * recs},
-                 {"peel_head", sizeof(uint32_t) * T},
-                 {"peel_ctl", sizeof(uint32_t) * kPeelCtl},
-                 {"peel_cross", sizeof(uint32_t) * T},
-                 {"peel_nx", sizeof(uint32_t) * n_out * recs},
-                 {"peel_park_d", sizeof(double) * kParkD * lanes},
-                 {"peel_park_u", sizeof(uint32_t) * kParkU * lanes}};
-    uint64_t more = 0;
-    for (const auto& w : want) {
-        const size_t have = sl.scratch[w.name].bytes;
-        if (w.bytes > have) more += w.bytes - have;
-    }
-    {
-        std::lock_guard<std::mutex> mk(ctx->mem_mu);
-        if (held_locked(ctx) + more > ctx->budget) return MCRT_OK;
-    }
+    const Want want[9] = {{"peel_rec", peel_record_bytes(mixed) * recs},
+                          {"peel_next", sizeof(uint32_t) * recs},
+                          {"peel_f", sizeof(double) * n_out * recs},
+                          {"peel_head", sizeof(uint32_t) * T},
+                          {"peel_ctl", sizeof(uint32_t) * kPeelCtl},
+                          {"peel_cross", sizeof(uint32_t) * T},
+                          {"peel_nx", sizeof(uint32_t) * n_out * recs},
+                          {"peel_park_d", sizeof(double) * kParkD * lanes},
+                          {"peel_park_u", sizeof(uint32_t) * kParkU * lanes}};
     void* p[9];
-    for (int i = 0; i < 9; ++i)
-        if (int rc = slot_scratch(ctx, sl, st, want[i].name, want[i].bytes, &p[i]))
-            return rc == MCRT_EBUDGET || rc == MCRT_ENOMEM ? MCRT_OK : rc;
+    bool there = false;
+    if (int rc = spare_scratch(ctx, sl, st, want, 9, p, there)) return rc;
+    if (!there) return MCRT_OK;
+    sl.spare_busy = true;
     if (!sl.flag) HIPTRY(hipHostMalloc((void**)&sl.flag, sizeof(uint32_t)));
     q.next = (uint32_t*)p[1];
     q.f = (double*)p[2];
@@ -947,17 +999,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
         batch = serving_batch(ctx, p->max_batch, nsolve, per_solve, gs ? N / ng + 1 : N);  // as admitted
     } else {
         batch = p->max_batch > 0 ? p->max_batch : nsolve;
-        uint64_t room;
-        {
-            // the slot's own scratch is regrown in place (each buffer freed
-            // before its larger successor is allocated), so it counts as room:
-            // repeated calls then plan the same launches as the first
-            uint64_t own = 0;
-            for (const auto& kv : sl.scratch) own += kv.second.bytes;
-            std::lock_guard<std::mutex> mk(ctx->mem_mu);
-            const uint64_t held = held_locked(ctx);
-            room = ctx->budget - std::min(ctx->budget, held - std::min(held, own));
-        }
+        const uint64_t room = slot_room(ctx, sl);
         uint64_t cap = room / 2;  // half of what the budget leaves: fewer launches, fewer drain tails
         int fit = (int)std::max<uint64_t>(1, cap / std::max<size_t>(per_solve, 1));
         batch = std::max(1, std::min(std::min(batch, fit), nsolve));
@@ -1333,8 +1375,201 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     return MCRT_OK;
 }
 
-// Transmission: chord geometry once, then per block of up to 64 spectral
-// rows: alpha gather -> chord optical depths -> fixed-order tally.
+// Device bytes that a served transmission request is admitted with.
+uint64_t chord_estimate(const GridRes* g, int n_b, int n_alpha, int nrow)
+{
+    const uint64_t nch = (uint64_t)n_b * n_alpha, ncell = (uint64_t)g->ncell, nslot = std::min(64, nrow);
+    const uint64_t segs = nch * (2ULL * g->dev.nlay + 2ULL * g->dev.nlat + g->dev.nlon + 8ULL);
+    return nch * 24 + 8 + ncell * nslot * 8 + (nch + 31) / 32 * 2 * nslot * 8 + (uint64_t)nrow * 20 + ncell * 48 + segs * 12 +
+           (1ULL << 20);
+}
+
+// Transmission: in batches of groups of chords, the geometry, then per block of
+// up to 64 spectral rows the crossed cells' extinction, the groups' optical
+// depths and their tallies.  Fills hs (two sums per row) and the result's
+// timing and number of segments.  A tally is summed in chunks of kGroupChunk
+// groups, and batches are whole chunks, so results do not depend on how many
+// there are: all groups at once where the scratch for it fits (in a quarter of
+// what the budget leaves, or in what a served request was admitted with), else
+// as few batches as do.
+template <typename R>
+int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op, const SolvePlan& pl, const mcrt_solve_params* p,
+               std::vector<double>& hs, mcrt_result* res)
+{
+    const bool hires = op->kind == MCRT_OPAC_HIRES;
+    const int ncell = g->ncell, ns = (int)pl.specs.size(), ng = pl.ng, nrow = ns * ng;
+    const int nblk = (nrow + 63) / 64, ntp = op->nT * op->nP;
+    const int stride = chord_stride(std::min(nrow, 64));
+    // ln kappa is summed in FP32 only for the mixed form's line-by-line tables
+    const bool single = hires && sizeof(R) == sizeof(float);
+    // Blocking solves alternate the blocks of rows between two streams with
+    // their own extinction and tallies, so that one block's extinction is
+    // formed while the previous block's chords are summed; served requests use
+    // their one stream.
+    const int nbuf = !sl.stream_ordered && nblk > 1 ? 2 : 1;
+    if (nbuf == 2 && !sl.stream2)  // made on first use, so that slots that never need it hold no queue
+        if (int rc = own_queue_stream(&sl.stream2, ctx->n_cu)) return rc;
+    ChordDev q;
+    chord_shape(q, g->dev, ncell, p->n_b, p->n_alpha);
+    const int n_chunk = (q.n_total + kGroupChunk - 1) / kGroupChunk;
+    int* specs;
+    double *part, *chunks, *sums, *ck_tab, *ck_ray;
+    // arrays one after another in one allocation at base; their bytes
+    auto taker = [](char* base, size_t& at) {
+        return [base, &at](auto*& x, size_t n) {
+            x = (std::remove_reference_t<decltype(x)>)(base + at);
+            at += (n * sizeof(*x) + 255) & ~(size_t)255;
+        };
+    };
+    auto carve_all = [&](char* base) {
+        size_t at = 0;
+        auto take = taker(base, at);
+        take(specs, (size_t)ns);
+        take(chunks, 256 * (size_t)n_chunk * nblk);
+        take(sums, 2 * (size_t)nrow);
+        take(ck_tab, hires ? 0 : 64 * (size_t)nblk * ntp);
+        take(ck_ray, hires ? 0 : 64 * (size_t)nblk);
+        return at;
+    };
+    auto carve_batch = [&](ChordDev& b, int n, char* base) {
+        size_t at = 0;
+        auto take = taker(base, at);
+        chord_batch(b, 0, n);
+        const size_t slots = (size_t)b.n_wave * 64, segs = slots * b.cap;
+        R* len;
+        take(b.seg_cell, segs);
+        take(b.seg_row, segs);
+        take(len, segs);
+        b.seg_len = len;
+        take(b.chord_n, slots);
+        take(b.chord_b, slots);
+        take(b.chord_ok, slots);
+        take(b.touched, 16 * (size_t)b.n_flag_words);
+        take(b.comp, 16 * (size_t)b.n_flag_words);
+        take(b.group_n, (size_t)n);
+        take(b.group_at, (size_t)n);
+        take(b.bsum, 3 * (size_t)chord_scan_blocks(b));
+        take(b.totals, 4);
+        take(part, 2 * (size_t)stride * n * nbuf);
+        return at;
+    };
+    auto chunked = [](int n) { return std::max(1, n / kGroupChunk) * kGroupChunk; };
+    auto no_room = [](int rc) { return rc == MCRT_EBUDGET || rc == MCRT_ENOMEM; };
+    const uint64_t limit = sl.stream_ordered ? chord_estimate(g, p->n_b, p->n_alpha, nrow) : slot_room(ctx, sl) / 4;
+    void* v;
+    if (int rc = slot_scratch(ctx, sl, st, "chord_sums", carve_all(nullptr), &v)) return rc;
+    carve_all((char*)v);
+    int batch = n_chunk * kGroupChunk;
+    {
+        ChordDev b = q;
+        while (batch > kGroupChunk && carve_batch(b, batch, nullptr) > limit / 2) batch = chunked(batch / 2);
+    }
+    size_t held = 0;
+    // a batch's arrays: of fewer groups where they do not fit, and never at the
+    // cost of an optional form's (which are given back first)
+    auto hold = [&]() -> int {
+        for (;; batch = chunked(batch / 2)) {
+            held = carve_batch(q, batch, nullptr);
+            int rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
+            if (no_room(rc) && !sl.spare.empty()) {
+                HIPTRY(hipStreamSynchronize(st));
+                release_spare(ctx, sl);
+                rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
+            }
+            if (rc == MCRT_OK) carve_batch(q, batch, (char*)v);
+            if (!no_room(rc) || batch == kGroupChunk) return rc;
+        }
+    };
+    if (int rc = hold()) return rc;
+    sl.spare_busy = true;
+    const LimbDark ld{p->ld_law, p->ld_c1, p->ld_c2, p->transit_y, p->transit_z, p->r_star};
+    const bool prof = p->profile != 0;
+    size_t n_prof = 0;
+    res->n_segments = 0;
+    HIPTRY(hipEventRecord(sl.ev0, st));
+    HIPTRY(hipMemcpyAsync(specs, pl.specs.data(), sizeof(int) * ns, hipMemcpyHostToDevice, st));
+    if (!hires) launch_ck_rows(op->lnk, op->ng, ntp, specs, ng, nrow, op->k_ray_dev, ck_tab, ck_ray, st);
+    for (int g0 = 0; g0 < q.n_total;) {
+        chord_batch(q, g0, std::min(batch, q.n_total - g0));
+        launch_chord_geometry<R>(g->dev, p->n_b, p->n_alpha, p->seed, 0, q, ld, st);
+        unsigned long long tot[4];
+        HIPTRY(hipMemcpyAsync(tot, q.totals, sizeof tot, hipMemcpyDeviceToHost, st));
+        HIPTRY(hipStreamSynchronize(st));
+        if (tot[3] != 0) {  // more steps than a line's crossings: rounding at an edge
+            q.cap = std::min(2 * q.cap, q.cap_max);
+            if (int rc = hold()) return rc;
+            continue;
+        }
+        const size_t rows = (size_t)tot[0], cells = (size_t)tot[1], alpha_n = cells * stride;
+        void* v_cells;
+        R *alpha, *len;
+        CellRow<double>* cr;
+        auto carve_rows = [&](char* base) {
+            size_t at = 0;
+            auto take = taker(base, at);
+            take(q.row_cell, rows);
+            take(len, 16 * rows);
+            take(alpha, alpha_n * nbuf);
+            take(cr, cells);  // (CellRow<float> is the smaller)
+            q.row_len = len;
+            v_cells = cr;
+            return at;
+        };
+        const size_t need = carve_rows(nullptr);
+        const bool small = q.n_group <= kGroupChunk;
+        int rc = !small && held + need > limit ? MCRT_EBUDGET : slot_scratch(ctx, sl, st, "chord_rows", need, &v, true);
+        if (no_room(rc) && !small) {
+            batch = chunked(q.n_group / 2);
+            HIPTRY(hipStreamSynchronize(st));
+            release_spare(ctx, sl);
+            if ((rc = hold())) return rc;
+            continue;
+        }
+        if (rc) return rc;
+        carve_rows((char*)v);
+        if (single)
+            launch_cell_rows(g->dev, ncell, q, hires, op->nT, op->nP, op->T_grid, op->lnP_grid, op->dlnlam,
+                             (CellRow<float>*)v_cells, st);
+        else
+            launch_cell_rows(g->dev, ncell, q, hires, op->nT, op->nP, op->T_grid, op->lnP_grid, op->dlnlam, cr, st);
+        launch_chord_rows<R>(q, st);
+        hipStream_t st2 = nbuf == 2 ? sl.stream2 : st;
+        if (nbuf == 2) {
+            HIPTRY(hipEventRecord(sl.fork, st));
+            HIPTRY(hipStreamWaitEvent(st2, sl.fork, 0));
+        }
+        if (prof && (rc = prof_events(ctx, sl, n_prof + nblk))) return rc;
+        for (int blk = 0; blk < nblk; ++blk, ++n_prof) {
+            const int r0 = 64 * blk, nslot = std::min(64, nrow - r0), b = blk % nbuf;
+            hipStream_t sb = b ? st2 : st;
+            R* al = alpha + alpha_n * b;
+            if (!hires)
+                launch_row_alpha<R, double>(cr, (int)cells, false, ck_tab + (size_t)r0 * ntp, 0, ck_ray + r0, nullptr, nslot, al,
+                                            sb);
+            else if constexpr (sizeof(R) == sizeof(float))
+                launch_row_alpha<R, float>((CellRow<float>*)v_cells, (int)cells, true, op->lnk_f32, op->nspec, op->k_ray_dev,
+                                           specs + r0, nslot, al, sb);
+            else
+                launch_row_alpha<R, double>(cr, (int)cells, true, op->lnk, op->nspec, op->k_ray_dev, specs + r0, nslot, al, sb);
+            if (prof) (void)hipEventRecord(sl.prof_ev[2 * n_prof], sb);
+            launch_group_tau<R>(q, al, nslot, part + 2 * (size_t)stride * batch * b, chunks + 256 * (size_t)n_chunk * blk, sb);
+            if (prof) (void)hipEventRecord(sl.prof_ev[2 * n_prof + 1], sb);
+        }
+        if (nbuf == 2) {  // the first stream waits for the second's last block
+            HIPTRY(hipEventRecord(sl.join, st2));
+            HIPTRY(hipStreamWaitEvent(st, sl.join, 0));
+        }
+        res->n_segments += (int64_t)tot[2];
+        g0 += q.n_group;
+    }
+    launch_group_final(chunks, n_chunk, nrow, sums, st);
+    HIPTRY(hipGetLastError());
+    hs.resize((size_t)nrow * 2);
+    HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
+    if (int rc = finish_timing(ctx, sl, st, res)) return rc;
+    return prof ? prof_collect(ctx, sl, n_prof, res) : MCRT_OK;
+}
+
 int solve_chords(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, int32_t oid,
                  const mcrt_solve_params* p, mcrt_result* res)
 {
@@ -1352,112 +1587,15 @@ int solve_chords(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, i
                                  "albedo and emission");
     HIPTRY(hipSetDevice(ctx->device));
     hipStream_t st = pl.stream;
-    const int ncell = g->ncell;
     const int nch = p->n_b * p->n_alpha;
     const int ns = (int)pl.specs.size(), ng = pl.ng;
     const int nrow = ns * ng;
-    const int kSlot = 64;
-    const int nslot_max = std::min(kSlot, nrow);
-    void *v_cnt, *v_off, *v_b, *v_ok, *v_alpha, *v_part, *v_sums, *v_shift = nullptr, *v_nl = nullptr;
-    if ((rc = slot_scratch(ctx, sl, st, "chord_cnt", sizeof(int) * (size_t)nch, &v_cnt))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "chord_off", sizeof(long long) * ((size_t)nch + 1), &v_off))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "chord_b", sizeof(double) * (size_t)nch, &v_b))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "chord_ok", sizeof(int) * (size_t)nch, &v_ok))) return rc;
-    // Blocking solves with more than one block of rows alternate the blocks
-    // between two streams with their own extinction and partial-sum buffers,
-    // so that one block's extinction rows are formed while the previous
-    // block's chords are summed; served requests use their one stream.
-    const int nbuf = (!sl.stream_ordered && nrow > kSlot) ? 2 : 1;
-    if (nbuf == 2 && !sl.stream2)  // made on first use, so that slots that never need it hold no queue
-        if ((rc = own_queue_stream(&sl.stream2, ctx->n_cu))) return rc;
-    const size_t alpha_n = (size_t)ncell * nslot_max;
-    int tblocks = chord_tau_blocks(nch);
-    const size_t part_n = (size_t)tblocks * 2 * nslot_max;
-    if ((rc = slot_scratch(ctx, sl, st, "alpha_blk", sizeof(double) * alpha_n * nbuf, &v_alpha))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "chord_part", sizeof(double) * part_n * nbuf, &v_part))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "chord_sums", sizeof(double) * (size_t)nrow * 2, &v_sums))) return rc;
-    void* v_tp = nullptr;
-    if (op->kind == MCRT_OPAC_HIRES) {
-        if ((rc = slot_scratch(ctx, sl, st, "shift", sizeof(double) * (size_t)ncell, &v_shift))) return rc;
-        if ((rc = slot_scratch(ctx, sl, st, "nlist", sizeof(int) * (size_t)ns, &v_nl))) return rc;
-        if ((rc = slot_scratch(ctx, sl, st, "cell_tp", sizeof(CellTP) * (size_t)ncell, &v_tp))) return rc;
-    }
-    const uint32_t tag = 0;  // chords are common to all spectral points
-    const bool prof = p->profile != 0;
-    const int nblk_rows = (nrow + kSlot - 1) / kSlot;
-    if (prof && (rc = prof_events(ctx, sl, (size_t)nblk_rows))) return rc;
     res->kernel_ms = 0.0;
     res->kernel_launches = 0;
-    HIPTRY(hipEventRecord(sl.ev0, st));
-    launch_chord_count(g->dev, p->n_b, p->n_alpha, p->seed, tag, (int*)v_cnt, st);
-    launch_exclusive_scan_int((int*)v_cnt, (long long*)v_off, nch, nullptr, st);
-    long long nseg = 0;
-    HIPTRY(hipMemcpyAsync(&nseg, (long long*)v_off + nch, sizeof(long long), hipMemcpyDeviceToHost, st));
-    HIPTRY(hipStreamSynchronize(st));
-    res->n_segments = nseg;
-    void *v_sc, *v_sl;
-    if ((rc = slot_scratch(ctx, sl, st, "seg_cell", sizeof(uint32_t) * (size_t)std::max(nseg, 1LL), &v_sc))) return rc;
-    if ((rc = slot_scratch(ctx, sl, st, "seg_len", sizeof(double) * (size_t)std::max(nseg, 1LL), &v_sl))) return rc;
-    const LimbDark ld{p->ld_law, p->ld_c1, p->ld_c2, p->transit_y, p->transit_z, p->r_star};
-    const bool mixed = p->precision == MCRT_MIXED;
-    if (mixed)
-        launch_chord_fill(g->dev, p->n_b, p->n_alpha, p->seed, tag, (long long*)v_off, (uint32_t*)v_sc, (float*)v_sl,
-                          (double*)v_b, (int*)v_ok, ld, st);
-    else
-        launch_chord_fill(g->dev, p->n_b, p->n_alpha, p->seed, tag, (long long*)v_off, (uint32_t*)v_sc, (double*)v_sl,
-                          (double*)v_b, (int*)v_ok, ld, st);
-    if (op->kind == MCRT_OPAC_HIRES) {
-        launch_doppler_shift(g->dev, -1.0, 0.0, 0.0, op->dlnlam, (double*)v_shift, st);
-        launch_cell_tp(g->dev, ncell, op->nT, op->nP, op->T_grid, op->lnP_grid, (CellTP*)v_tp, st);
-        HIPTRY(hipMemcpyAsync(v_nl, pl.specs.data(), sizeof(int) * ns, hipMemcpyHostToDevice, st));
-    }
-    // Per block of up to 64 spectral rows: extinction of every cell (FP64, or
-    // FP32 in the mixed form: half the bytes the chords gather), then the
-    // chords' optical depths, accumulated in FP64 either way.
-    auto rows_block = [&](auto* alpha, int r0, int nslot, hipStream_t st, double* part) {
-        using R = std::remove_pointer_t<decltype(alpha)>;
-        if (op->kind == MCRT_OPAC_CK) {
-            for (int q = 0; q < nslot; ++q) {
-                int rr = r0 + q, b = pl.specs[rr / ng], gi = rr % ng;
-                const double* tab = op->lnk + ((size_t)b * op->ng + gi) * op->nT * op->nP;
-                OpticsDev<R> od{alpha + q, nullptr, nullptr, nullptr, nullptr};
-                launch_ck_optics(g->dev, ncell, tab, op->nT, op->nP, op->T_grid, op->lnP_grid, op->k_ray[b], od, nslot,
-                                 st);
-            }
-        } else {
-            const R* tab;
-            if constexpr (sizeof(R) == sizeof(float)) tab = op->lnk_f32;
-            else tab = op->lnk;
-            launch_hires_alpha_block(g->dev, ncell, tab, op->nspec, op->nP, (const CellTP*)v_tp, op->k_ray_dev,
-                                     (double*)v_shift, (int*)v_nl + r0, nslot, nslot, alpha, st);
-        }
-        if (prof) (void)hipEventRecord(sl.prof_ev[2 * (r0 / kSlot)], st);
-        launch_chord_tau(p->n_b, p->n_alpha, (long long*)v_off, (uint32_t*)v_sc, (const R*)v_sl, (double*)v_b, (int*)v_ok,
-                         (const R*)alpha, nslot, part, tblocks, st);
-        if (prof) (void)hipEventRecord(sl.prof_ev[2 * (r0 / kSlot) + 1], st);
-        launch_reduce_partials(part, tblocks, 2 * nslot, (double*)v_sums + 2 * (size_t)r0, st);
-    };
-    hipStream_t st2 = nbuf == 2 ? sl.stream2 : st;
-    if (nbuf == 2) {  // the second stream starts after the common work above
-        HIPTRY(hipEventRecord(sl.fork, st));
-        HIPTRY(hipStreamWaitEvent(st2, sl.fork, 0));
-    }
-    for (int r0 = 0; r0 < nrow; r0 += kSlot) {
-        const int nslot = std::min(kSlot, nrow - r0), b = (r0 / kSlot) % nbuf;
-        hipStream_t sb = b ? st2 : st;
-        double* part = (double*)v_part + part_n * b;
-        if (mixed) rows_block((float*)v_alpha + alpha_n * b, r0, nslot, sb, part);
-        else rows_block((double*)v_alpha + alpha_n * b, r0, nslot, sb, part);
-    }
-    if (nbuf == 2) {  // the first stream waits for the second's last block
-        HIPTRY(hipEventRecord(sl.join, st2));
-        HIPTRY(hipStreamWaitEvent(st, sl.join, 0));
-    }
-    HIPTRY(hipGetLastError());
-    std::vector<double> hs((size_t)nrow * 2);
-    HIPTRY(hipMemcpyAsync(hs.data(), v_sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
-    if ((rc = finish_timing(ctx, sl, st, res))) return rc;
-    if (prof && (rc = prof_collect(ctx, sl, (size_t)nblk_rows, res))) return rc;
+    std::vector<double> hs;
+    rc = p->precision == MCRT_MIXED ? chord_sums<float>(ctx, sl, st, g, op, pl, p, hs, res)
+                                    : chord_sums<double>(ctx, sl, st, g, op, pl, p, hs, res);
+    if (rc) return rc;
 
     // (R_p/R*)^2 = (R0^2 + 2 <I>)/R*^2, <I> = (R_TOA - R0)/N sum (1 - e^-tau) b  (Sect. 5.1)
     const double dr = g->r_toa - g->r0, Nd = (double)nch, rs2 = p->r_star * p->r_star;
@@ -1486,6 +1624,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
                 const mcrt_solve_params* common, mcrt_result* results)
 {
     if (n_items < 1 || !items || !common || !results) return fail(MCRT_EINVAL, "batch needs items, params, results");
+    sl.spare_busy = false;
     if (common->contrib || common->image_npix || common->g_sampling)
         return fail(MCRT_EINVAL, "contribution functions, images and g-ordinate sampling are single-solve options");
     struct Item {
@@ -1926,6 +2065,7 @@ struct Request {
 int run_solve(mcrt_ctx* ctx, Slot& sl, hipStream_t st, int mode, int32_t gid, int32_t oid,
               const mcrt_solve_params* p, mcrt_result* res)
 {
+    sl.spare_busy = false;
     if (mode == MCRT_MODE_TRANSMISSION && !p->ms_transmission) return solve_chords(ctx, sl, st, gid, oid, p, res);
     if (mode == MCRT_MODE_ALBEDO || mode == MCRT_MODE_EMISSION || mode == MCRT_MODE_TRANSMISSION)
         return solve_packets(ctx, sl, st, gid, oid, p, res, mode);
@@ -1945,14 +2085,7 @@ uint64_t estimate_bytes(mcrt_ctx* ctx, const Request& r, GridRes* g, OpacRes* op
 {
     const uint64_t ncell = (uint64_t)g->ncell;
     const uint64_t nsolve = (uint64_t)r.ns * r.ng;
-    if (r.mode == MCRT_MODE_TRANSMISSION && !r.p.ms_transmission) {
-        const uint64_t nch = (uint64_t)r.p.n_b * r.p.n_alpha;
-        const uint64_t nrow = nsolve, nslot = std::min<uint64_t>(64, nrow);
-        const uint64_t tblocks = (uint64_t)chord_tau_blocks((int)nch);
-        const uint64_t segs = nch * (2ULL * g->dev.nlay + 2ULL * g->dev.nlat + g->dev.nlon + 8ULL);
-        return nch * (4 + 8 + 8 + 4) + 8 + ncell * nslot * 8 + tblocks * 2 * nslot * 8 + nrow * 16 + ncell * 8 +
-               ncell * sizeof(CellTP) + nrow * 4 + segs * 12 + (1ULL << 20);
-    }
+    if (r.mode == MCRT_MODE_TRANSMISSION && !r.p.ms_transmission) return chord_estimate(g, r.p.n_b, r.p.n_alpha, (int)nsolve);
     const bool mixed = r.p.precision == MCRT_MIXED;
     const uint64_t N = r.p.n_packets;
     const uint64_t no = (uint64_t)r.no;

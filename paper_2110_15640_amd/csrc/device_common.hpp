@@ -177,15 +177,6 @@ __host__ __device__ inline double limb_weight(const LimbDark& ld, double y, doub
 }
 
 // ---------------------------------------------------------------- geometry
-enum { F_NONE = -1, F_OUT = 0, F_IN = 1, F_LATLO = 2, F_LATHI = 3, F_LONLO = 4, F_LONHI = 5 };
-enum { T_INTERACT = 0, T_ESCAPE = 1, T_SURFACE = 2, T_LOST = 3 };
-
-struct Ray {
-    double x, y, z;
-    int i, j, k;
-    int ef;
-};
-
 __host__ __device__ __forceinline__ int find_edge(const double* e, int n, double x)
 {
     // largest m in [0, n-1] with e[m] <= x, 0 if none (edges increasing)
@@ -198,199 +189,10 @@ __host__ __device__ __forceinline__ int find_edge(const double* e, int n, double
     return lo;
 }
 
-// Distance to the latitude cone (the equatorial plane when tb == 0) of an
-// edge with cos^2 = c2, sin^2 = s2; roots below lo ignored; hits must be on
-// the nappe whose z has the sign of tb.
-__host__ __device__ __forceinline__ double cone_distance(const Ray& p, double dx, double dy, double dz, double tb,
-                                                double c2, double s2, double lo)
+__host__ __device__ __forceinline__ void locate_column(const GridDev& g, double x, double y, double z, int& i, int& j)
 {
-    double best = INFINITY;
-    if (tb == 0.0) {
-        if (dz != 0.0) {
-            double s = -p.z / dz;
-            if (s >= lo) best = s;
-        }
-        return best;
-    }
-    double a = dz * dz * c2 - (dx * dx + dy * dy) * s2;
-    double b = p.z * dz * c2 - (p.x * dx + p.y * dy) * s2;
-    double c = p.z * p.z * c2 - (p.x * p.x + p.y * p.y) * s2;
-    double r0 = -1.0, r1 = -1.0;
-    bool h0 = false, h1 = false;
-    if (a == 0.0) {
-        if (b != 0.0) {
-            r0 = -c / (2.0 * b);
-            h0 = true;
-        }
-    } else {
-        double disc = b * b - a * c;
-        if (disc >= 0.0) {
-            double sq = sqrt(disc);
-            double q = -(b + (b >= 0.0 ? sq : -sq));
-            r0 = q / a;
-            h0 = true;
-            if (q != 0.0) {
-                r1 = c / q;
-                h1 = true;
-            }
-        }
-    }
-    if (h0 && r0 >= lo) {
-        double zh = p.z + r0 * dz;
-        bool ok = tb > 0.0 ? (zh > 0.0) : (zh < 0.0);
-        if (ok && r0 < best) best = r0;
-    }
-    if (h1 && r1 >= lo) {
-        double zh = p.z + r1 * dz;
-        bool ok = tb > 0.0 ? (zh > 0.0) : (zh < 0.0);
-        if (ok && r1 < best) best = r1;
-    }
-    return best;
-}
-
-// Distance to leave the current cell along d; returns the face (ties in the
-// order outer, inner, lat-low, lat-high, lon-low, lon-high).
-__host__ __device__ __forceinline__ int exit_distance(const GridDev& g, const Ray& p, double dx, double dy,
-                                             double dz, double& s_out)
-{
-    if (g.geom == 1) {
-        if (dz > 0.0) {
-            double s = (g.r[p.k + 1] - p.z) / dz;
-            s_out = s < 0.0 ? 0.0 : s;
-            return F_OUT;
-        }
-        if (dz < 0.0) {
-            double s = (g.r[p.k] - p.z) / dz;
-            s_out = s < 0.0 ? 0.0 : s;
-            return F_IN;
-        }
-        s_out = INFINITY;
-        return F_NONE;
-    }
-    double rr = p.x * p.x + p.y * p.y + p.z * p.z;
-    double B = p.x * dx + p.y * dy + p.z * dz;
-    double best;
-    int face;
-    {
-        double ro = g.r[p.k + 1];
-        double C = rr - ro * ro;
-        double D = B * B - C;
-        if (D < 0.0) D = 0.0;
-        double s = (B <= 0.0) ? (-B + sqrt(D)) : (-C / (B + sqrt(D)));
-        if (s < 0.0) s = 0.0;
-        best = s;
-        face = F_OUT;
-    }
-    if (B < 0.0) {
-        double ri = g.r[p.k];
-        double C = rr - ri * ri;
-        double D = B * B - C;
-        if (D >= 0.0) {
-            double s = C / (-B + sqrt(D));
-            if (s < 0.0) s = 0.0;
-            if (s < best) {
-                best = s;
-                face = F_IN;
-            }
-        }
-    }
-    double tol = 1e-9 * sqrt(rr);
-    if (p.j > 0) {
-        int e = p.j;
-        double s = cone_distance(p, dx, dy, dz, g.lat[e], g.lat_c2[e], g.lat_s2[e],
-                                 p.ef == F_LATLO ? tol : 0.0);
-        if (s < best) {
-            best = s;
-            face = F_LATLO;
-        }
-    }
-    if (p.j < g.nlat - 1) {
-        int e = p.j + 1;
-        double s = cone_distance(p, dx, dy, dz, g.lat[e], g.lat_c2[e], g.lat_s2[e],
-                                 p.ef == F_LATHI ? tol : 0.0);
-        if (s < best) {
-            best = s;
-            face = F_LATHI;
-        }
-    }
-    if (g.nlon > 1) {
-        {
-            double sb = g.lon_s[p.i], cb = g.lon_c[p.i];
-            double nx = -sb, ny = cb;
-            double dn = dx * nx + dy * ny;
-            if (dn < 0.0) {
-                double s = -(p.x * nx + p.y * ny) / dn;
-                if (s < 0.0) s = 0.0;
-                double hx = p.x + s * dx, hy = p.y + s * dy;
-                if (cb * hx + sb * hy > 0.0 && s < best) {
-                    best = s;
-                    face = F_LONLO;
-                }
-            }
-        }
-        {
-            int iu = p.i + 1 == g.nlon ? 0 : p.i + 1;
-            double sb = g.lon_s[iu], cb = g.lon_c[iu];
-            double nx = -sb, ny = cb;
-            double dn = dx * nx + dy * ny;
-            if (dn > 0.0) {
-                double s = -(p.x * nx + p.y * ny) / dn;
-                if (s < 0.0) s = 0.0;
-                double hx = p.x + s * dx, hy = p.y + s * dy;
-                if (cb * hx + sb * hy > 0.0 && s < best) {
-                    best = s;
-                    face = F_LONHI;
-                }
-            }
-        }
-    }
-    s_out = best;
-    return face;
-}
-
-__host__ __device__ __forceinline__ void advance(const GridDev& g, Ray& p, double dx, double dy, double dz, double s)
-{
-    if (g.geom == 1) {
-        p.z = p.z + s * dz;
-    } else {
-        p.x = p.x + s * dx;
-        p.y = p.y + s * dy;
-        p.z = p.z + s * dz;
-    }
-}
-
-__host__ __device__ __forceinline__ void cross(const GridDev& g, Ray& p, int f)
-{
-    switch (f) {
-    case F_OUT:
-        p.k += 1;
-        p.ef = F_IN;
-        if (g.geom == 1 && p.k <= g.nlay) p.z = g.r[p.k];
-        break;
-    case F_IN:
-        p.k -= 1;
-        p.ef = F_OUT;
-        if (g.geom == 1 && p.k >= -1) p.z = g.r[p.k + 1];
-        break;
-    case F_LATLO: p.j -= 1; p.ef = F_LATHI; break;
-    case F_LATHI: p.j += 1; p.ef = F_LATLO; break;
-    case F_LONLO: p.i = p.i == 0 ? g.nlon - 1 : p.i - 1; p.ef = F_LONHI; break;
-    case F_LONHI: p.i = p.i + 1 == g.nlon ? 0 : p.i + 1; p.ef = F_LONLO; break;
-    default: break;
-    }
-}
-
-__host__ __device__ __forceinline__ int cell_of(const GridDev& g, const Ray& p)
-{
-    return (p.k * g.nlat + p.j) * g.nlon + p.i;
-}
-
-__host__ __device__ __forceinline__ void locate_column(const GridDev& g, Ray& p)
-{
-    double lat = atan2(p.z, sqrt(p.x * p.x + p.y * p.y));
-    double lon = atan2(p.y, p.x);
-    p.j = find_edge(g.lat, g.nlat, lat);
-    p.i = find_edge(g.lon, g.nlon, lon);
+    j = find_edge(g.lat, g.nlat, atan2(z, sqrt(x * x + y * y)));
+    i = find_edge(g.lon, g.nlon, atan2(y, x));
 }
 
 // ---------------------------------------------------------------- opacity interpolation
@@ -434,6 +236,38 @@ __device__ __forceinline__ double interp_tp(F lnk, const Bracket& bt, const Brac
     if (w2 > 0.0) { double l = lnk(bt.i1, bp.i0); if (isinf(l)) return 0.0; acc = acc + w2 * l; }
     if (w3 > 0.0) { double l = lnk(bt.i1, bp.i1); if (isinf(l)) return 0.0; acc = acc + w3 * l; }
     return exp(acc);
+}
+
+// Doppler shift of cell c's table position for light along o (Sect. 7):
+// ln(lambda_eff / lambda) by its velocity towards the observer, in table steps.
+__device__ __forceinline__ double los_shift(const GridDev& g, int c, double ox, double oy, double oz, double dlnlam)
+{
+    int i = c % g.nlon, j = (c / g.nlon) % g.nlat, k = c / (g.nlon * g.nlat);
+    double rc = 0.5 * (g.r[k] + g.r[k + 1]);
+    double th = 0.5 * (g.lat[j] + g.lat[j + 1]);
+    double ph = 0.5 * (g.lon[i] + g.lon[i + 1]);
+    double sth = sin(th), cth = cos(th), sph = sin(ph), cph = cos(ph);
+    double eE0 = -sph, eE1 = cph, eE2 = 0.0;
+    double eN0 = -sth * cph, eN1 = -sth * sph, eN2 = cth;
+    double eR0 = cth * cph, eR1 = cth * sph, eR2 = sth;
+    double uu = g.u ? (double)g.u[c] : 0.0, vv = g.v ? (double)g.v[c] : 0.0, ww = g.w ? (double)g.w[c] : 0.0;
+    double ue = uu + g.omega_rot * rc * cth;
+    double v0 = ue * eE0 + vv * eN0 + ww * eR0;
+    double v1 = ue * eE1 + vv * eN1 + ww * eR1;
+    double v2 = ue * eE2 + vv * eN2 + ww * eR2;
+    double vlos = -(v0 * ox + v1 * oy + v2 * oz);
+    return log1p(-vlos / kC) / dlnlam;
+}
+
+// Table position n + shift split into the lower neighbour n0 and the
+// fraction fr, clamped at the table ends.
+__device__ __forceinline__ void hires_pos(int nlam, int n, double shift, int& n0, double& fr)
+{
+    const double x = (double)n + shift;
+    if (nlam == 1) { n0 = 0; fr = 0.0; }
+    else if (x <= 0.0) { n0 = 0; fr = 0.0; }
+    else if (x >= (double)(nlam - 1)) { n0 = nlam - 2; fr = 1.0; }
+    else { n0 = (int)floor(x); fr = x - (double)n0; }
 }
 
 

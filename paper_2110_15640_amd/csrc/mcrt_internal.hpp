@@ -48,16 +48,6 @@ struct GridDev {
     double omega_rot;
 };
 
-// Per-cell optical properties of one (spectral point, g) solve.
-template <typename R>
-struct OpticsDev {
-    R* a_ext;   // extinction coefficient [1/cm]
-    R* a_abs;   // absorption coefficient [1/cm]
-    R* omega;   // single-scattering albedo
-    R* p_gas;   // probability that a scattering is by gas (Rayleigh)
-    R* g_cld;   // cloud HG asymmetry
-};
-
 // One (spectral point, g) solve inside a persistent transport launch.
 // Optical-property arrays are double (FP64) or float (MIXED).
 struct SolveDev {
@@ -207,43 +197,62 @@ void launch_fill_f64(double* p, size_t n, double v, hipStream_t stream);
 void launch_births(const GridDev& g, const BatchArgs& a, bool multi, hipStream_t stream);
 
 // Launchers (kernels.hip).  All run on `stream`; none synchronises.
-// R = double, or float for the mixed transmission form (stored once rounded).
-template <typename R>
-void launch_ck_optics(const GridDev& g, int ncell, const double* lnk_tab, int nT, int nP,
-                      const double* T_grid, const double* lnP_grid, double k_ray,
-                      OpticsDev<R> out, int ext_stride, hipStream_t stream);
 void launch_doppler_shift(const GridDev& g, double ox, double oy, double oz, double dlnlam,
                           double* shift, hipStream_t stream);
-// A cell's place in the opacity table's (T, ln P) grid: bracketing nodes
-// and fractions, the same for every wavelength of a transmission solve.
-struct CellTP {
-    int ti0, ti1, pi0, pi1;
-    double tt, pt;
+// Transmission chords in groups of 16 (chords.hip).  A launch takes the n_group
+// groups from g0; their arrays count from there, and a chord's slot in them is
+// 16 group + its place in the group.
+constexpr uint32_t kChordOver = 0xffffffffu;  // a group with a chord that its strip does not hold
+constexpr int kGroupChunk = 64;               // groups of one chunk of the tallies
+struct ChordDev {
+    int nbg, n_total;            // groups along the impact parameter, in all
+    int g0, n_group, n_wave;     // groups of the launch and waves of their walk
+    int cap, cap_max;            // steps that a chord's strip holds; steps after which a chord is given up
+    int n_flag_words, n_fblk;    // 16-byte words of touched, and their blocks in the scans
+    int share;                   // four waves share a group's optical depths (else one each)
+    uint32_t* seg_cell;          // [n_wave][cap][64] cell, bit 31: outgoing half
+    uint32_t* seg_row;           // ... row within the group, bit 31: the row's first segment
+    void* seg_len;               // ... length, FP64 or FP32
+    uint32_t* chord_n;           // per chord slot: steps (> cap: more than the strip holds)
+    double* chord_b;             // ... weight
+    uint32_t* chord_ok;          // ... 0: opaque
+    uint8_t* touched;            // per cell: crossed by a chord
+    uint32_t* comp;              // per crossed cell: its place among the crossed
+    uint2* group_n;              // per group: rows, segments
+    uint32_t* group_at;          // ... its first row
+    unsigned long long* bsum;    // scan blocks' sums, 3 each
+    unsigned long long* totals;  // rows, crossed cells, segments, groups not held
+    uint32_t* row_cell;          // per row: place of its cell among the crossed
+    void* row_len;               // per row: 16 lengths
 };
-void launch_cell_tp(const GridDev& g, int ncell, int nT, int nP, const double* T_grid, const double* lnP_grid,
-                    CellTP* out, hipStream_t stream);
-// lnk_tpl: the [T][P][lambda] ln-kappa table in the extinction's own type
-// (FP64, or its FP32 copy for the mixed form).
+// W: type in which ln kappa is summed.
+template <typename W>
+struct CellRow {
+    int row[4];  // T, P corners in the table
+    W w[4];      // their weights
+    double rho, shift;
+    float ks, ka;  // cloud scattering and absorption
+};
+// Slots of an extinction row: the next of 16, 32, 64.
+__host__ __device__ inline int chord_stride(int nslot) { return nslot <= 16 ? 16 : nslot <= 32 ? 32 : 64; }
+void chord_shape(ChordDev& q, const GridDev& g, int ncell, int n_b, int n_alpha);
+void chord_batch(ChordDev& q, int g0, int n_group);
+int chord_scan_blocks(const ChordDev& q);
 template <typename R>
-void launch_hires_alpha_block(const GridDev& g, int ncell, const R* lnk_tpl, int nlam, int nP,
-                              const CellTP* tp, const double* k_ray, const double* shift, const int* nlist,
-                              int nslot, int slot_stride, R* alpha, hipStream_t stream);
-void launch_reduce_partials(const double* partials, int nblocks, int width, double* out,
-                            hipStream_t stream);
-void launch_chord_count(const GridDev& g, int n_b, int n_alpha, uint64_t seed, uint32_t tag,
-                        int* counts, hipStream_t stream);
-void launch_exclusive_scan_int(const int* in, long long* out, int n, long long* total_dev,
-                               hipStream_t stream);
-// R = double, or float for the mixed form (segment lengths and extinction rows).
+void launch_chord_geometry(const GridDev& g, int n_b, int n_alpha, uint64_t seed, uint32_t tag, const ChordDev& q,
+                           const LimbDark& ld, hipStream_t stream);
 template <typename R>
-void launch_chord_fill(const GridDev& g, int n_b, int n_alpha, uint64_t seed, uint32_t tag,
-                       const long long* offsets, uint32_t* seg_cell, R* seg_len,
-                       double* chord_b, int* chord_ok, const LimbDark& ld, hipStream_t stream);
+void launch_chord_rows(const ChordDev& q, hipStream_t stream);
+template <typename W>
+void launch_cell_rows(const GridDev& g, int ncell, const ChordDev& q, bool hires, int nT, int nP, const double* T_grid,
+                      const double* lnP_grid, double dlnlam, CellRow<W>* out, hipStream_t stream);
+void launch_ck_rows(const double* lnk, int ng_tab, int ntp, const int* specs, int ng, int nrow, const double* k_ray, double* tab,
+                    double* kray_row, hipStream_t stream);
+template <typename R, typename W>
+void launch_row_alpha(const CellRow<W>* cells, int n_cells, bool hires, const W* tab, int nlam, const double* k_ray,
+                      const int* nlist, int nslot, R* alpha, hipStream_t stream);
 template <typename R>
-void launch_chord_tau(int n_b, int n_alpha, const long long* offsets, const uint32_t* seg_cell,
-                      const R* seg_len, const double* chord_b, const int* chord_ok,
-                      const R* alpha, int nslot, double* partials, int nblocks,
-                      hipStream_t stream);
-int chord_tau_blocks(int nch);
+void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part, double* chunks, hipStream_t stream);
+void launch_group_final(const double* chunks, int n_chunk, int nrow, double* sums, hipStream_t stream);
 
 }  // namespace mcrt

@@ -404,12 +404,11 @@ __device__ __forceinline__ void birth_record(const GridDev& g1, const BatchArgs&
             double a = 2.0 * kPi * u.b;
             double y = rho * cos(a), z = rho * sin(a);
             double x = sqrt(fmax(r_toa * r_toa - y * y - z * z, 0.0));
-            Ray rs;
-            rs.x = x; rs.y = y; rs.z = z;
-            locate_column(g, rs);
+            int i, j;
+            locate_column(g, x, y, z, i, j);
             b[B_X] = x; b[B_Y] = y; b[B_Z] = z;
             b[B_DX] = -1.0; b[B_DY] = 0.0; b[B_DZ] = 0.0;
-            b[B_CELL] = (double)pack_ijk(rs.i, rs.j, g.nlay - 1);
+            b[B_CELL] = (double)pack_ijk(i, j, g.nlay - 1);
         }
         b[B_W] = wmul;
         return;
@@ -421,15 +420,13 @@ __device__ __forceinline__ void birth_record(const GridDev& g1, const BatchArgs&
         const double r0 = g.r[0];
         const double bi = r0 + u.a * (r_toa - r0);
         const double al = 2.0 * kPi * u.b;
-        Ray rs;
-        rs.x = sqrt(fmax(r_toa * r_toa - bi * bi, 0.0));
-        rs.y = bi * cos(al);
-        rs.z = bi * sin(al);
-        locate_column(g, rs);
-        b[B_X] = rs.x; b[B_Y] = rs.y; b[B_Z] = rs.z;
+        const double x = sqrt(fmax(r_toa * r_toa - bi * bi, 0.0)), y = bi * cos(al), z = bi * sin(al);
+        int i, j;
+        locate_column(g, x, y, z, i, j);
+        b[B_X] = x; b[B_Y] = y; b[B_Z] = z;
         b[B_DX] = -1.0; b[B_DY] = 0.0; b[B_DZ] = 0.0;
-        b[B_CELL] = (double)pack_ijk(rs.i, rs.j, g.nlay - 1);
-        b[B_W] = bi * limb_weight(A.ld, rs.y, rs.z) * wmul;
+        b[B_CELL] = (double)pack_ijk(i, j, g.nlay - 1);
+        b[B_W] = bi * limb_weight(A.ld, y, z) * wmul;
         return;
     }
     const int ncell = g.nlon * g.nlat * g.nlay;
