@@ -42,9 +42,9 @@ __device__ __forceinline__ size_t strip(int group, int c, int n, int cap)
 
 // ---------------------------------------------------------------- geometry
 // One thread per chord, by the transport's walk in its exact form; one pass
-// into strips of `cap` steps (what a straight line can cross), where a count
-// and a fill pass by per-face root finding took 274 + 305 us on the 64 x 32 x
-// 50 grid with 256 x 360 chords.  A wave holds 4 groups; its time is the serial
+// into strips of `cap` steps (what a straight line can cross): 110 us on a 64 x
+// 32 x 50 grid with 256 x 360 chords, where a count and a fill pass by per-face
+// root finding took 274 + 305.  A wave holds 4 groups; its time is the serial
 // chain of its longest chord.  Bit 31 of a cell tells the outgoing half of the
 // chord, on which a cell crossed on the way in counts anew: within a half the
 // distance from the centre is monotonic and no cell is met twice.
@@ -332,6 +332,11 @@ __global__ void __launch_bounds__(256) k_cell_rows(GridDev g, int ncell, ChordDe
     r.w[1] = (one - t) * u;
     r.w[2] = t * (one - u);
     r.w[3] = t * u;
+    int used = r.row[0];  // a corner with weight
+#pragma unroll
+    for (int k = 0; k < 4; ++k) used = r.w[k] > (W)0 ? r.row[k] : used;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r.row[k] = r.w[k] > (W)0 ? r.row[k] : used;
     r.rho = g.rho[c];
     r.shift = HIRES ? los_shift(g, c, -1.0, 0.0, 0.0, dlnlam) : 0.0;
     r.ks = g.cld_ksca ? g.cld_ksca[c] : 0.0f;
@@ -354,20 +359,31 @@ __global__ void __launch_bounds__(256) k_ck_rows(const double* __restrict__ lnk,
     if (blockIdx.y == 0 && threadIdx.x < 64) kray_row[(size_t)blockIdx.x * 64 + s] = k_ray[spec];
 }
 
-// kappa = exp(sum of w l), a corner of weight zero left out (its l may be -inf;
-// one with weight gives zero).
+// Table position n + shift split into the lower neighbour n0 and the
+// fraction fr, clamped at the table ends.
+__device__ __forceinline__ void hires_pos(int nlam, int n, double shift, int& n0, double& fr)
+{
+    const double x = wk_min(wk_max((double)n + shift, 0.0), (double)(nlam - 1));
+    n0 = min((int)x, nlam > 1 ? nlam - 2 : 0);
+    fr = x - (double)n0;
+}
+
+// kappa = exp(sum of w l).  l is finite or -inf; a corner with weight and -inf
+// gives zero.  (A corner without weight stands for one with weight, k_cell_rows,
+// so 0 times -inf, the only NaN here, is that case too.)
 template <typename W>
 __device__ __forceinline__ W corner_sum(const W* l, const CellRow<W>& q)
 {
     W acc = 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const W x = q.w[k] > (W)0 ? l[k] : (W)0;
-        if constexpr (sizeof(W) == 4) acc = fmaf(q.w[k], x, acc);
-        else acc = acc + q.w[k] * x;
+        if constexpr (sizeof(W) == 4) acc = fmaf(q.w[k], l[k], acc);
+        else acc = acc + q.w[k] * l[k];
     }
-    if constexpr (sizeof(W) == 4) return __expf(acc);
-    else return exp(acc);
+    W e;
+    if constexpr (sizeof(W) == 4) e = __expf(acc);
+    else e = exp(acc);
+    return acc == acc ? e : (W)0;
 }
 
 template <typename R>
@@ -388,6 +404,9 @@ __device__ __forceinline__ R below_inf(double a)
 // lower one whenever that lane has the next table wavelength, so each kappa is
 // evaluated once; for the last slot they are evaluated beforehand, one cell per
 // lane.  Lanes past the last slot repeat it.
+// 30 us for 64 rows of the 223000 crossed cells of a 128 x 64 x 60 grid in FP32,
+// two thirds of it vector instructions (50 a cell); every cell of that grid with
+// each value evaluated twice took 210.
 constexpr int kRowCells = 8;
 
 template <typename R, typename W, bool HIRES>
@@ -412,7 +431,7 @@ __global__ void __launch_bounds__(256) k_row_alpha(const CellRow<W>* __restrict_
         hires_pos(nlam, nlist[nslot - 1], q.shift, n0, fr);
         W l[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) l[k] = tab[(size_t)q.row[k] * nlam + n0 + 1];
+        for (int k = 0; k < 4; ++k) l[k] = tab[(size_t)q.row[k] * nlam + (unsigned)(n0 + 1)];
         k_end = corner_sum<W>(l, q);
     }
     constexpr int U = 4;  // cells whose loads are in flight together
@@ -426,7 +445,10 @@ __global__ void __launch_bounds__(256) k_row_alpha(const CellRow<W>* __restrict_
             const CellRow<W>& q = cells[min(c0 + u0 + u, n_cells - 1)];
             if constexpr (HIRES) hires_pos(nlam, n, q.shift, n0[u], fr[u]);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) l[u][k] = HIRES ? tab[(size_t)q.row[k] * nlam + n0[u]] : tab[(size_t)q.row[k] * 64 + s];
+            for (int k = 0; k < 4; ++k) {
+                const W* row = tab + (size_t)q.row[k] * (HIRES ? nlam : 64);
+                l[u][k] = row[(unsigned)(HIRES ? n0[u] : s)];
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -445,7 +467,7 @@ __global__ void __launch_bounds__(256) k_row_alpha(const CellRow<W>* __restrict_
                     if (!end && !take) {
                         W m[4];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) m[k] = tab[(size_t)q.row[k] * nlam + n0[u] + 1];
+                        for (int k = 0; k < 4; ++k) m[k] = tab[(size_t)q.row[k] * nlam + (unsigned)(n0[u] + 1)];
                         k1 = corner_sum<W>(m, q);
                     }
                     if constexpr (sizeof(W) == 4) {
@@ -459,134 +481,111 @@ __global__ void __launch_bounds__(256) k_row_alpha(const CellRow<W>* __restrict_
             } else {
                 kext = (k0 + (double)q.ka) + (kr + (double)q.ks);
             }
-            if (lane < stride) alpha[(size_t)c * stride + lane] = below_inf<R>(q.rho * kext);
+            R* row = alpha + (size_t)c * stride;
+            if (lane < stride) row[(unsigned)lane] = below_inf<R>(q.rho * kext);
         }
     }
 }
 
 // ---------------------------------------------------------------- optical depths
 typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int kTauBlocks = 2;   // 16-slot blocks of a wave (of 16 slots in all: 1)
+constexpr int kTauBytes = 64;   // bytes of extinction that a lane has in flight
+constexpr int kRuns = 16;       // runs of groups of each XCD
 template <typename R, int NB>
 struct __attribute__((aligned(sizeof(R) * NB))) RowVec {
     R v[NB];
 };
 
 // One group's optical depths by FP64 matrix instructions of 16 chords x 16
-// slots x 4 cells, NB of them for 16 NB slots (lane & 15 holds the NB
-// neighbouring slots at NB (lane & 15)), and its sums of (1 - e^-tau) b and of
-// their squares.  W waves share a group, every W-th quad of cells each.
-template <typename R, int NB, int W>
-__global__ void __launch_bounds__(256) k_group_tau(ChordDev q, const R* __restrict__ alpha, double* __restrict__ part)
+// slots x 4 cells, and its sums of (1 - e^-tau) b and of their squares.  A wave
+// takes 16 NB slots of a group (lane & 15 holds NB neighbouring ones) and all
+// of its cells, so nothing is shared between waves and the accumulators stay
+// small enough for eight waves a SIMD: a group has few cells (some 200, at the
+// poles 800) and the time goes on waiting for their rows.  Of a 128 x 64 x 60
+// grid's 256 x 360 chords and 64 rows in FP32 the matrix instructions alone are
+// 33 us, and the kernel takes 65 to 70 (a wave per segment's row, without
+// groups: 420).  One or four blocks a wave instead of two, and four waves that
+// share a group's cells, are 10 to 15 % slower there; twice the loads in flight
+// are no faster.
+template <typename R, int NB>
+__global__ void __launch_bounds__(256) k_group_tau(ChordDev q, const R* __restrict__ alpha, int stride,
+                                                   double* __restrict__ part)
 {
-    constexpr int G = 4 / W;  // groups of a block
-    __shared__ double sh[W > 1 ? 4 * NB * 4 * 64 : 1];
     const int lane = threadIdx.x & 63, n = lane & 15, kq = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    // XCD x takes the x-th run of groups, which follow the limb angle: the
-    // cells of an angle are then read into one L2 only
-    const int units = (q.n_group + G - 1) / G, per = (units + kXcds - 1) / kXcds;
-    const int unit = ((int)blockIdx.x % kXcds) * per + (int)blockIdx.x / kXcds;
-    if ((int)blockIdx.x / kXcds >= per || unit >= units) return;
-    const int group = unit * G + (W > 1 ? 0 : wave);
-    if (group >= q.n_group) return;  // (W = 1: no barrier follows)
+    // XCD x takes runs x, x + 8, ... of kRuns x 8 runs of the groups, which
+    // follow the limb angle: the cells of an angle are then read into one L2
+    // only, and each XCD has its share of the poles, whose chords cross more
+    // cells (of the 256 x 360 chords on 128 x 64 x 60 cells the largest share is
+    // 1.05 of the mean; with one run each 1.29)
+    const int parts = stride / (16 * NB);  // waves of a group
+    const int n_blk = (q.n_group * parts + 3) / 4, per = (n_blk + kRuns * kXcds - 1) / (kRuns * kXcds);
+    const int turn = (int)blockIdx.x / kXcds;
+    const int blk = ((turn / per) * kXcds + (int)blockIdx.x % kXcds) * per + turn % per;
+    const int id = blk * 4 + wave, group = id / parts;
+    if (group >= q.n_group) return;
+    const int s0 = (id % parts) * (16 * NB) + n * NB;
     const size_t r0 = q.group_at[group];
     const int nq = (int)(quads(q.group_n[group].x) / 4);
     const uint32_t* __restrict__ rc = q.row_cell + r0 + kq;
     const R* __restrict__ rl = (const R*)q.row_len + r0 * kGC + lane;
-    const R* __restrict__ al = alpha + n * NB;
+    const R* __restrict__ al = alpha + s0;
+    // register r of an accumulator holds chord 4 r + kq
+    double wb[4];
+    bool ok[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        wb[r] = q.chord_b[group * kGC + 4 * r + kq];
+        ok[r] = q.chord_ok[group * kGC + 4 * r + kq] != 0;
+    }
     d4 acc[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) acc[b] = d4{0.0, 0.0, 0.0, 0.0};
-    constexpr int U = 4;  // quads whose loads are in flight together
-    int i = W > 1 ? wave : 0;
-    for (; i + (U - 1) * W < nq; i += U * W) {
-        uint32_t cell[U];
+    // U quads at a time, their loads in flight together (a quad past the end
+    // repeats the last one with length zero); the cells of the next U are
+    // fetched before the products
+    constexpr int U = kTauBytes / (NB * (int)sizeof(R));
+    uint32_t cell[U];
+    auto cells = [&](int at) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) cell[u] = rc[(unsigned)min(at + u, nq - 1) * 4];
+    };
+    if (nq > 0) cells(0);
+    for (int i = 0; i < nq; i += U) {
         R len[U];
         RowVec<R, NB> a[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) cell[u] = rc[(size_t)(i + u * W) * 4];
+        for (int u = 0; u < U; ++u) a[u] = *(const RowVec<R, NB>*)(al + (size_t)cell[u] * stride);
 #pragma unroll
-        for (int u = 0; u < U; ++u) len[u] = rl[(size_t)(i + u * W) * 64];
-#pragma unroll
-        for (int u = 0; u < U; ++u) a[u] = *(const RowVec<R, NB>*)(al + (size_t)cell[u] * (16 * NB));
+        for (int u = 0; u < U; ++u) {
+            const R x = rl[(unsigned)min(i + u, nq - 1) * 64];
+            len[u] = i + u < nq ? x : (R)0;
+        }
+        cells(i + U);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)len[u], (double)a[u].v[b], acc[b], 0, 0, 0);
     }
-    for (; i < nq; i += W) {
-        const R len = rl[(size_t)i * 64];
-        const RowVec<R, NB> a = *(const RowVec<R, NB>*)(al + (size_t)rc[(size_t)i * 4] * (16 * NB));
+    double* out = part + (size_t)group * (2 * stride) + s0;
 #pragma unroll
-        for (int b = 0; b < NB; ++b) acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)len, (double)a.v[b], acc[b], 0, 0, 0);
-    }
-    // register r of a lane holds chord 4 r + kq
-    double s1[NB], s2[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) s1[b] = s2[b] = 0.0;
-    auto tally = [&](int r, const double* tau) {
-        const int ch = group * kGC + 4 * r + kq;
-        const bool ok = q.chord_ok[ch] != 0;
-        const double wb = q.chord_b[ch];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const double v = (1.0 - (ok ? exp(-tau[b]) : 0.0)) * wb;
-            s1[b] = s1[b] + v;
-            s2[b] = s2[b] + v * v;
-        }
-    };
-    if constexpr (W == 1) {
+    for (int b = 0; b < NB; ++b) {
+        double s1 = 0.0, s2 = 0.0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            double tau[NB];
-#pragma unroll
-            for (int b = 0; b < NB; ++b) tau[b] = acc[b][r];
-            tally(r, tau);
+            const double v = (1.0 - (ok[r] ? exp(-acc[b][r]) : 0.0)) * wb[r];
+            s1 = s1 + v;
+            s2 = s2 + v * v;
         }
-    } else {
-        static_assert(W == 1 || W == 4, "a wave tallies one register");
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sh[((wave * NB + b) * 4 + r) * 64 + lane] = acc[b][r];
-        __syncthreads();
-        double tau[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            tau[b] = sh[(b * 4 + wave) * 64 + lane];
-            for (int w = 1; w < 4; ++w) tau[b] = tau[b] + sh[((w * NB + b) * 4 + wave) * 64 + lane];
-        }
-        tally(wave, tau);
-    }
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
         for (int o = 16; o < 64; o <<= 1) {
-            s1[b] = s1[b] + __shfl_xor(s1[b], o);
-            s2[b] = s2[b] + __shfl_xor(s2[b], o);
+            s1 = s1 + __shfl_xor(s1, o);
+            s2 = s2 + __shfl_xor(s2, o);
         }
-    double* out = part + (size_t)group * (2 * 16 * NB);
-    if constexpr (W > 1) {
-        __syncthreads();
-        if (lane < 16)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                sh[(wave * 2 + 0) * 64 + n * NB + b] = s1[b];
-                sh[(wave * 2 + 1) * 64 + n * NB + b] = s2[b];
-            }
-        __syncthreads();
-        const int t = threadIdx.x;
-        if (t < 2 * 16 * NB) {
-            const int j = t / (16 * NB), s = t % (16 * NB);
-            double v = sh[j * 64 + s];
-            for (int w = 1; w < 4; ++w) v = v + sh[(w * 2 + j) * 64 + s];
-            out[t] = v;
-        }
-    } else if (lane < 16) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            out[n * NB + b] = s1[b];
-            out[16 * NB + n * NB + b] = s2[b];
+        if (kq == 0) {
+            out[b] = s1;
+            out[stride + b] = s2;
         }
     }
 }
@@ -600,16 +599,23 @@ __device__ __forceinline__ void comp_add(double& s, double& c, double x, double 
     s = t;
 }
 
-// Groups [64 blockIdx.x, + 64): chunk sums of each column, threads over
-// columns and, where there are fewer than 128, over every k-th group.
-__global__ void __launch_bounds__(128) k_group_sums(const double* __restrict__ part, int n_group, int width,
-                                                    double2* __restrict__ out)
+// Chunk sums of each column over groups [64 blockIdx.x, + 64): threads over the
+// columns, and over every k-th group, eight loads in flight in each.
+constexpr int kSumThreads = 512;
+__global__ void __launch_bounds__(kSumThreads) k_group_sums(const double* __restrict__ part, int n_group, int width,
+                                                            double2* __restrict__ out)
 {
-    __shared__ double2 sh[128];
-    const int col = threadIdx.x % width, k = threadIdx.x / width, nk = 128 / width;
+    __shared__ double2 sh[kSumThreads];
+    const int col = threadIdx.x % width, k = threadIdx.x / width, nk = kSumThreads / width;
     const int g1 = min(n_group, ((int)blockIdx.x + 1) * kGroupChunk);
     double s = 0.0, c = 0.0;
-    for (int gr = blockIdx.x * kGroupChunk + k; gr < g1; gr += nk) comp_add(s, c, part[(size_t)gr * width + col], 0.0);
+    for (int gr = blockIdx.x * kGroupChunk + k; gr < g1; gr += 8 * nk) {
+        double x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = gr + e * nk < g1 ? part[(size_t)(gr + e * nk) * width + col] : 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) comp_add(s, c, x[e], 0.0);
+    }
     sh[threadIdx.x] = double2{s, c};
     __syncthreads();
     if (k == 0) {
@@ -627,12 +633,15 @@ __global__ void __launch_bounds__(64) k_group_final(const double2* __restrict__ 
     if (s >= nslot) return;
     const double2* src = chunks + (size_t)blk * n_chunk * 128 + j * chord_stride(nslot) + s;
     double a = 0.0, c = 0.0;
-    for (int e = 0; e < n_chunk; ++e) comp_add(a, c, src[(size_t)e * 128].x, src[(size_t)e * 128].y);
+    for (int e = 0; e < n_chunk; e += 8) {
+        double2 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = e + u < n_chunk ? src[(size_t)(e + u) * 128] : double2{0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 8; ++u) comp_add(a, c, x[u].x, x[u].y);
+    }
     sums[2 * ((size_t)blk * 64 + s) + j] = a + c;
 }
-
-// Fewer groups than this share their cells among four waves (see k_group_tau).
-constexpr int kShareGroups = 4096;
 
 inline int nblk(long long n, int b) { return (int)((n + b - 1) / b); }
 
@@ -647,7 +656,6 @@ void chord_shape(ChordDev& q, const GridDev& g, int ncell, int n_b, int n_alpha)
     // a straight line meets every shell and cone at most twice and every half plane once
     q.cap = 2 * g.nlay + 2 * g.nlat + g.nlon + 8;
     q.cap_max = 64 * (g.nlay + g.nlat + g.nlon) + 64;
-    q.share = q.n_total < kShareGroups;
     chord_batch(q, 0, q.n_total);
     q.n_flag_words = nblk(ncell, 16);
     q.n_fblk = nblk(q.n_flag_words, 256);
@@ -733,19 +741,12 @@ template <typename R>
 void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part, double* chunks, hipStream_t stream)
 {
     const int stride = chord_stride(nslot);
-    const bool share = q.share;
-    const int units = share ? q.n_group : nblk(q.n_group, 4);
-    const dim3 grid(nblk(units, kXcds) * kXcds), block(256);
-#define MCRT_TAU(NB)                                                                                                 \
-    do {                                                                                                             \
-        if (share) hipLaunchKernelGGL((k_group_tau<R, NB, 4>), grid, block, 0, stream, q, alpha, part);              \
-        else hipLaunchKernelGGL((k_group_tau<R, NB, 1>), grid, block, 0, stream, q, alpha, part);                    \
-    } while (0)
-    if (stride == 64) MCRT_TAU(4);
-    else if (stride == 32) MCRT_TAU(2);
-    else MCRT_TAU(1);
-#undef MCRT_TAU
-    hipLaunchKernelGGL(k_group_sums, dim3(nblk(q.n_group, kGroupChunk)), dim3(128), 0, stream, part, q.n_group, 2 * stride,
+    const int nb = std::min(stride / 16, kTauBlocks);
+    const int n_blk = nblk((long long)q.n_group * (stride / (16 * nb)), 4);
+    const dim3 grid(nblk(n_blk, kRuns * kXcds) * kRuns * kXcds), block(256);
+    if (nb == kTauBlocks) hipLaunchKernelGGL((k_group_tau<R, kTauBlocks>), grid, block, 0, stream, q, alpha, stride, part);
+    else hipLaunchKernelGGL((k_group_tau<R, 1>), grid, block, 0, stream, q, alpha, stride, part);
+    hipLaunchKernelGGL(k_group_sums, dim3(nblk(q.n_group, kGroupChunk)), dim3(kSumThreads), 0, stream, part, q.n_group, 2 * stride,
                        (double2*)chunks + 128 * (size_t)(q.g0 / kGroupChunk));
 }
 template void launch_group_tau<double>(const ChordDev&, const double*, int, double*, double*, hipStream_t);

@@ -259,18 +259,6 @@ __device__ __forceinline__ double los_shift(const GridDev& g, int c, double ox, 
     return log1p(-vlos / kC) / dlnlam;
 }
 
-// Table position n + shift split into the lower neighbour n0 and the
-// fraction fr, clamped at the table ends.
-__device__ __forceinline__ void hires_pos(int nlam, int n, double shift, int& n0, double& fr)
-{
-    const double x = (double)n + shift;
-    if (nlam == 1) { n0 = 0; fr = 0.0; }
-    else if (x <= 0.0) { n0 = 0; fr = 0.0; }
-    else if (x >= (double)(nlam - 1)) { n0 = nlam - 2; fr = 1.0; }
-    else { n0 = (int)floor(x); fr = x - (double)n0; }
-}
-
-
 // Arithmetic of a walk.  The exact form rounds every product and sum on its
 // own and divides and takes roots correctly rounded, as the FP64 oracle; the
 // fast form, taken by the FP32-mixed transport, contracts a product and a sum

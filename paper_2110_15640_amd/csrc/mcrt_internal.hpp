@@ -209,7 +209,6 @@ struct ChordDev {
     int g0, n_group, n_wave;     // groups of the launch and waves of their walk
     int cap, cap_max;            // steps that a chord's strip holds; steps after which a chord is given up
     int n_flag_words, n_fblk;    // 16-byte words of touched, and their blocks in the scans
-    int share;                   // four waves share a group's optical depths (else one each)
     uint32_t* seg_cell;          // [n_wave][cap][64] cell, bit 31: outgoing half
     uint32_t* seg_row;           // ... row within the group, bit 31: the row's first segment
     void* seg_len;               // ... length, FP64 or FP32
