@@ -403,6 +403,12 @@ __host__ __device__ __forceinline__ double2 wk_face(const GridDev& g, int e)
     return *(const double2*)((const char*)g.faces + (uint32_t)e * (uint32_t)sizeof(double2));
 }
 
+// The outer (out) or inner radius of layer k.
+__host__ __device__ __forceinline__ double wk_edge(const GridDev& g, int k, bool out)
+{
+    return *(const double*)((const char*)g.faces + ((uint32_t)k * 16u + (out ? 8u : 0u)));
+}
+
 __host__ __device__ __forceinline__ int wk_cell(const GridDev& g, const Walker& w) { return (w.k * g.nlat + w.j) * g.nlon + w.i; }
 
 // The latitude edge a walk in row j meets next, rising (dj = 1) or falling
@@ -607,9 +613,25 @@ __host__ __device__ __forceinline__ CrossIn wk_cross_begin(const GridDev& g, Wal
     return in;
 }
 
-// The face that replaces the one just crossed.
-template <bool FAST, int GEO = GEO_ANY>
-__host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& w, const CrossKind& x, const CrossIn& in)
+// The next shell of a ray (a walk whose end nothing is made of: peel-off) that
+// has just crossed one into a layer of edge R ahead: its roots lie at -+sqrt(R^2
+// - q2) from the ray's nearest point (q2: that point's distance from the centre,
+// squared), which needs no division.  The difference loses some 1e-13 of a
+// layer's thickness, which a packet's path would amplify and an optical depth
+// does not.  sq: the root (0 where there is none).
+__host__ __device__ __forceinline__ double wk_ray_q2(const Walker& w) { return fma(-w.B0, w.B0, w.C0); }
+__host__ __device__ __forceinline__ void wk_ray_shell(Walker& w, double D, double sq)
+{
+    const bool out = w.dk > 0, miss = !out & !(D >= 0.0);
+    const double u = out ? sq : (miss ? -(w.t + w.B0) : -sq);
+    w.ts = wk_max(u - w.B0, w.t);
+    w.dk = miss ? 1 : w.dk;
+}
+
+// The face that replaces the one just crossed.  RAYS: the walk may be a ray.
+template <bool FAST, int GEO = GEO_ANY, bool RAYS = false>
+__host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& w, const CrossKind& x, const CrossIn& in,
+                                                      bool ray = false)
 {
     const bool outward = w.dk > 0;
     const double R = outward ? in.f.y : in.f.x;
@@ -620,6 +642,7 @@ __host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& 
     // shell: t^2 + 2 B0 t + c; cone: ca t^2 + 2 cb t + cc
     const double c = wk_mad<FAST>(-R, R, w.C0);
     double D = wk_mad<FAST>(w.B0, w.B0, -c);
+    if (RAYS && ray) D = fma(R, R, -wk_ray_q2(w));
     double ca, cb, cc;
     ConePick p;
     if (x.cone) {
@@ -649,7 +672,9 @@ __host__ __device__ __forceinline__ void wk_cross_end(const GridDev& g, Walker& 
     }
     const bool finite = den != 0.0;
     double r = wk_root<FAST>(num, den);
-    if (x.shell) {
+    if (RAYS && x.shell && ray) {
+        wk_ray_shell(w, D, sq);
+    } else if (x.shell) {
         if constexpr (!FAST) r = mfar ? m : r;
         const bool hit = outward | ((D >= 0.0) & ((r >= w.t) | (c < 0.0)));
         w.ts = wk_max(hit ? (finite ? r : 0.0) : w.far, w.t);

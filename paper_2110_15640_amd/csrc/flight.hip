@@ -256,7 +256,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
         if (GEO != GEO_SLAB && L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
-        if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO>(L, g, aext, aabs, ae, A);
+        if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO, false>(L, g, aext, aabs, ae, A);
         const unsigned long long walking = __ballot(L.mode <= M_PROBE);
         const unsigned long long waits = __ballot(L.mode == M_EVENT || (L.mode == M_DEAD && !exhausted));
         // ev_threshold of 64 lanes, in proportion where fewer carry packets
@@ -434,10 +434,10 @@ __device__ __forceinline__ double peel_weight(const BatchArgs& A, double w, doub
 
 // One peel-off ray per lane: ray q of region x is observer q % n_out of its
 // record q / n_out, taken by waves of the region's XCD first (whose L2 holds the optics the region's flights used).
-enum { P_IDLE = 0, P_WALK = 1, P_DONE = 2 };
+enum { P_IDLE = 0, P_WALK = 1, P_ANGLE = 2, P_DONE = 3 };
 // Lanes without a ray that trigger the handing out of new ones: a start costs
 // about two steps.  8: 50.5 ms, 16: 46.1, 24: 45.9, 32: 47.3 (25 x 8 x 1e5 emission packets, mixed)
-constexpr int kPeelThreshold = 24;
+constexpr int kPeelThreshold = 24, kAngleThreshold = 16, kShellSteps = 3;
 
 template <bool MIXED, bool MULTI, int GEO>
 __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
@@ -449,9 +449,9 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const EvRec<MIXED>* recs = (const EvRec<MIXED>*)Q.rec;
     const uint32_t n_out = (uint32_t)A.n_out;
-    int state = P_IDLE, lgrid = 0, ncw = 0, kind = 0, solve = 0;
+    int state = P_IDLE, lgrid = 0, lcol = 0, ncw = 0, kind = 0, solve = 0, cell = 0;
     Walker w;
-    double tau = 0.0, wt = 0.0;
+    double tau = 0.0, wt = 0.0, q2 = 0.0;
     uint32_t fi = 0;  // the ray's place in Q.f and Q.nx
     Prop<MIXED> ae = 0;
     const void* aext = nullptr;
@@ -468,26 +468,68 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     if (share < 64u) share = 64u;
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
-        if (state == P_WALK) {
-            if (GEO != GEO_SLAB && g.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(g, w);
-            // (a slab ray that meets no face was dark from the start)
-            const CrossKind x = wk_next<GEO>(w);
-            const double s = x.t - w.t, a = (double)ae;
-            const CrossIn in = wk_cross_begin<GEO>(g, w, x);
-            ae = (Prop<MIXED>)ld<MIXED>(aext, in.inside ? wk_cell(g, w) : 0);
-            tau = wk_mad<MIXED>(a, s, tau);
+        const int ncol = MULTI ? lcol : g1.nlat * g1.nlon;
+        // a ray ends at the top; beyond tau_peel_max, on the planet or after too
+        // many cells nothing of it arrives
+        auto through = [&](double t, double a, bool inside) {
+            tau = wk_mad<MIXED>(a, t - w.t, tau);
+            w.t = t;
             ncw++;
-            // the ray ends at the top; beyond tau_peel_max, on the planet or
-            // after too many cells nothing of it arrives
             const bool dark = tau > A.tau_peel_max;
-            if (!in.inside | dark | (ncw >= g.max_cross)) {
-                if (dark | in.inside | (w.k < 0)) tau = INFINITY;
+            const bool end = !inside | dark | (ncw >= g.max_cross);
+            if (end) {
+                if (dark | inside | (w.k < 0)) tau = INFINITY;
                 state = P_DONE;
+            }
+            return !end;
+        };
+#pragma unroll
+        for (int m = 0; m < kShellSteps; ++m) {
+            if (state != P_WALK) continue;
+            if (GEO != GEO_SLAB && wk_min(w.tc, w.tp) < w.ts) {
+                state = P_ANGLE;
             } else {
-                wk_cross_end<MIXED, GEO>(g, w, x, in);
+                const bool out = w.dk > 0;
+                w.k += w.dk;
+                cell += out ? ncol : -ncol;
+                const bool inside = (unsigned)w.k < (unsigned)g.nlay;
+                const double a = (double)ae;
+                const double R = wk_edge(g, inside ? w.k : 0, out);
+                ae = (Prop<MIXED>)ld<MIXED>(aext, inside ? cell : 0);
+                if (through(w.ts, a, inside)) {
+                    if constexpr (GEO == GEO_SLAB) {
+                        w.ts = wk_max(wk_div<MIXED>(R - w.pz, w.dz), w.t);
+                    } else {
+                        const double D = fma(R, R, -q2);
+                        wk_ray_shell(w, D, wk_sqrt<MIXED>(D));
+                    }
+                }
             }
         }
-        const unsigned long long walking = __ballot(state == P_WALK);
+        unsigned long long walking = __ballot(state == P_WALK);
+        if constexpr (GEO != GEO_SLAB) {
+            const unsigned long long angle = __ballot(state == P_ANGLE);
+            if (angle != 0 && (walking == 0 || __popcll(angle) >= (more ? kAngleThreshold : 1))) {
+                if (state == P_ANGLE) {
+                    CrossKind x;
+                    x.t = wk_min(w.tc, w.tp);
+                    x.shell = x.none = false;
+                    x.cone = w.tc <= x.t;
+                    const double a = (double)ae, t0 = w.t;
+                    const CrossIn in = wk_cross_begin<GEO>(g, w, x);
+                    w.t = t0;
+                    cell = wk_cell(g, w);
+                    ae = (Prop<MIXED>)ld<MIXED>(aext, cell);
+                    if (through(x.t, a, true)) {
+                        wk_cross_end<MIXED, GEO>(g, w, x, in);
+                        if (g.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(g, w);
+                        state = P_WALK;
+                    }
+                }
+                walking = __ballot(state == P_WALK);
+            }
+            walking |= __ballot(state == P_ANGLE);
+        }
         if (walking != 0 && ((!more && res_next >= res_end) || 64 - __popcll(walking) < kPeelThreshold)) continue;
         if (state == P_DONE) {
             state = P_IDLE;
@@ -584,8 +626,12 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
                 tau = 0.0;
                 ncw = 0;
                 const int i = (int)(v.ijk & 0x7FFu), j = (int)((v.ijk >> 11) & 0x3FFu), k = (int)(v.ijk >> 21);
-                ae = (Prop<MIXED>)ld<MIXED>(aext, (k * gs.nlat + j) * gs.nlon + i);
+                cell = (k * gs.nlat + j) * gs.nlon + i;
+                if (MULTI) lcol = gs.nlat * gs.nlon;
+                ae = (Prop<MIXED>)ld<MIXED>(aext, cell);
                 wk_start<MIXED, GEO>(gs, w, px, py, v.z, dx, dy, dz, i, j, k);
+                q2 = wk_ray_q2(w);
+                if (GEO != GEO_SLAB && gs.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(gs, w);
                 if (dark) {
                     tau = INFINITY;
                     state = P_DONE;

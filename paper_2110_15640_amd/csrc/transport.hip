@@ -594,7 +594,7 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
     for (;;) {
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
         if (L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
-        if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO_ANY>(L, g, aext, aabs, ae, A);
+        if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO_ANY, true>(L, g, aext, aabs, ae, A);
         unsigned long long evm = __ballot(L.mode == M_EVENT);
         unsigned long long walking = __ballot(L.mode <= M_PROBE);
         if (__popcll(evm) < A.ev_threshold && walking != 0) continue;

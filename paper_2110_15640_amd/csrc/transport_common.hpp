@@ -80,7 +80,7 @@ using Prop = typename std::conditional<MIXED, float, double>::type;
 // the walk's cell, gathered when the cell was entered (wk_start's first cell:
 // by the caller), so that a step's end and the next one's start cover the
 // gather's latency.
-template <bool MIXED, bool EXT, int GEO, class LaneT>
+template <bool MIXED, bool EXT, int GEO, bool RAYS, class LaneT>
 __device__ __forceinline__ void walk_step(LaneT& L, const GridDev& g, const void* aext, const void* aabs,
                                           Prop<MIXED>& ae, const BatchArgs& A)
 {
@@ -133,7 +133,7 @@ __device__ __forceinline__ void walk_step(LaneT& L, const GridDev& g, const void
         L.mode = M_EVENT;
         return;
     }
-    wk_cross_end<MIXED, GEO>(g, L.w, x, in);
+    wk_cross_end<MIXED, GEO, RAYS>(g, L.w, x, in, L.mode == M_PEEL);
 }
 
 // Pending actions of a lane after an event; each is executed at exactly one
