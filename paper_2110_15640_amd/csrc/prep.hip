@@ -24,10 +24,11 @@ using namespace dev;
 constexpr int kScanPer = 8;
 constexpr int kScanBlock = 256 * kScanPer;
 
-__device__ __forceinline__ double planck_bl(double lam_cm, double T)
+// B_lambda(T); lam5 = pow(lam_cm, 5.0).
+__device__ __forceinline__ double planck_bl(double lam_cm, double lam5, double T)
 {
     double x = kH * kC / (lam_cm * kKB * T);
-    return 2.0 * kH * kC * kC / pow(lam_cm, 5.0) / expm1(x);
+    return 2.0 * kH * kC * kC / lam5 / expm1(x);
 }
 
 __device__ __forceinline__ double hires_kappa_at(const double* __restrict__ lnk_tpl, int nlam, int nP,
@@ -46,55 +47,79 @@ __device__ __forceinline__ double hires_kappa_at(const double* __restrict__ lnk_
     return (1.0 - fr) * k0 + fr * k1;
 }
 
+// Optics of a cell for `per` slots: its brackets in the opacity table (a
+// logarithm and two searches) are found once for them.  The FP64 form's
+// transport reads all five properties in FP64, the mixed form's only their FP32
+// copies: there FP64 extinction is kept for the emission sources alone.  Those
+// start here (L_i, in cdf).  Bound by the bytes written (of 200 mixed slots of
+// 128 x 64 x 50 cells 2.9 GB in 0.95 ms; one slot a thread and all properties in
+// both types: 4.9 GB in 1.4 ms, and 0.5 ms for L_i by columns).
+constexpr int kOpticsSlots = 8;  // slots of a thread, at most
 __global__ void __launch_bounds__(256) k_prep_optics(GridDev g, int ncell, const PrepSlot* __restrict__ slots,
-                                                     int hires, int nT, int nP, const double* __restrict__ T_grid,
+                                                     int nslots, int per, int hires, int nT, int nP,
+                                                     const double* __restrict__ T_grid,
                                                      const double* __restrict__ lnP_grid,
                                                      const double* __restrict__ lnk_tpl, int nlam,
                                                      const double* __restrict__ shift, int draine, double alpha)
 {
+    __shared__ double lam5[kOpticsSlots];
+    const int s0 = blockIdx.y * per, s1 = min(nslots, s0 + per);
+    if ((int)threadIdx.x < s1 - s0) lam5[threadIdx.x] = pow(slots[s0 + threadIdx.x].lam_cm, 5.0);
+    __syncthreads();
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= ncell) return;
-    const PrepSlot S = slots[blockIdx.y];
-    Bracket bt = bracket(T_grid, nT, (double)g.T[c]);
-    Bracket bp = bracket(lnP_grid, nP, log((double)g.P[c]));
+    const Bracket bt = bracket(T_grid, nT, (double)g.T[c]);
+    const Bracket bp = bracket(lnP_grid, nP, log((double)g.P[c]));
     const double rho = g.rho[c];
-    double ae, aa, om, pg, gc;
+    const double ks = g.cld_ksca ? (double)g.cld_ksca[c] : 0.0;
+    const double ka = g.cld_kabs ? (double)g.cld_kabs[c] : 0.0;
+    const int ncol = g.nlon * g.nlat, k = c / ncol, j = (c - k * ncol) / g.nlon, i = c - k * ncol - j * g.nlon;
+    const double dsl = g.lat_sin[j + 1] - g.lat_sin[j];
+    const double dph = g.lon[i + 1] - g.lon[i];
+    const double vol = g.vol_r[k] * dsl * dph;
+    double gc = 0.0;
     if (!hires) {
-        const double* tab = S.lnk;
-        double kg = interp_tp([&](int a, int b) { return tab[a * nP + b]; }, bt, bp);
-        double ks = g.cld_ksca ? (double)g.cld_ksca[c] : 0.0;
-        double ka = g.cld_kabs ? (double)g.cld_kabs[c] : 0.0;
-        double kab = kg + ka;
-        double ksc = S.k_ray + ks;
-        double kext = kab + ksc;
-        ae = rho * kext;
-        aa = rho * kab;
-        om = kext > 0.0 ? ksc / kext : 0.0;
-        pg = ksc > 0.0 ? S.k_ray / ksc : 1.0;
         gc = g.cld_g ? (double)g.cld_g[c] : 0.0;
         if (draine) gc = draine_G(gc, alpha);  // Draine clouds carry G in place of g
-    } else {
-        double kl = hires_kappa_at(lnk_tpl, nlam, nP, bt, bp, S.n, shift ? shift[c] : 0.0);
-        double kext = kl + S.k_ray;
-        ae = rho * kext;
-        aa = rho * kl;
-        om = kext > 0.0 ? S.k_ray / kext : 0.0;
-        pg = 1.0;
-        gc = 0.0;
     }
-    double* o = S.opt;
-    o[c] = ae;
-    o[ncell + c] = aa;
-    o[2 * (size_t)ncell + c] = om;
-    o[3 * (size_t)ncell + c] = pg;
-    o[4 * (size_t)ncell + c] = gc;
-    if (S.optf) {
-        float* f = S.optf;
-        f[c] = (float)ae;
-        f[ncell + c] = (float)aa;
-        f[2 * (size_t)ncell + c] = (float)om;
-        f[3 * (size_t)ncell + c] = (float)pg;
-        f[4 * (size_t)ncell + c] = (float)gc;
+    for (int sl = s0; sl < s1; ++sl) {
+        const PrepSlot S = slots[sl];
+        double ae, aa, om, pg;
+        if (!hires) {
+            const double* tab = S.lnk;
+            double kg = interp_tp([&](int a, int b) { return tab[a * nP + b]; }, bt, bp);
+            double kab = kg + ka;
+            double ksc = S.k_ray + ks;
+            double kext = kab + ksc;
+            ae = rho * kext;
+            aa = rho * kab;
+            om = kext > 0.0 ? ksc / kext : 0.0;
+            pg = ksc > 0.0 ? S.k_ray / ksc : 1.0;
+        } else {
+            double kl = hires_kappa_at(lnk_tpl, nlam, nP, bt, bp, S.n, shift ? shift[c] : 0.0);
+            double kext = kl + S.k_ray;
+            ae = rho * kext;
+            aa = rho * kl;
+            om = kext > 0.0 ? S.k_ray / kext : 0.0;
+            pg = 1.0;
+        }
+        if (!S.optf) {
+            double* o = S.opt;
+            o[c] = ae;
+            o[ncell + c] = aa;
+            o[2 * (size_t)ncell + c] = om;
+            o[3 * (size_t)ncell + c] = pg;
+            o[4 * (size_t)ncell + c] = gc;
+        } else {
+            float* f = S.optf;
+            f[c] = (float)ae;
+            f[ncell + c] = (float)aa;
+            f[2 * (size_t)ncell + c] = (float)om;
+            f[3 * (size_t)ncell + c] = (float)pg;
+            f[4 * (size_t)ncell + c] = (float)gc;
+            if (S.cdf) S.opt[c] = ae;
+        }
+        if (S.cdf) S.cdf[c] = 4.0 * kPi * vol * aa * planck_bl(S.lam_cm, lam5[sl - s0], (double)g.T[c]);
     }
 }
 
@@ -104,53 +129,42 @@ __global__ void __launch_bounds__(256) k_prep_L(GridDev g, const PrepSlot* __res
     const int col = blockIdx.x * blockDim.x + threadIdx.x;
     if (col >= g.nlon * g.nlat) return;
     const PrepSlot S = slots[blockIdx.y];
-    const int ncell = g.nlon * g.nlat * g.nlay;
     const double* a_ext = S.opt;
-    const double* a_abs = S.opt + ncell;
     double* L = S.cdf;
     const int i = col % g.nlon, j = col / g.nlon;
     double tau = 0.0;
-    const double dsl = g.lat_sin[j + 1] - g.lat_sin[j];
-    const double dph = g.lon[i + 1] - g.lon[i];
-    for (int k = g.nlay - 1; k >= 0; --k) {
-        int c = (k * g.nlat + j) * g.nlon + i;
-        double vol = g.vol_r[k] * dsl * dph;
-        double Li = 4.0 * kPi * vol * a_abs[c] * planck_bl(S.lam_cm, (double)g.T[c]);
-        L[c] = (tau > tau_vert) ? 0.0 : Li;
-        tau = tau + a_ext[c] * (g.r[k + 1] - g.r[k]);
-    }
-}
-
-template <int NT>
-__device__ __forceinline__ double bsum(double v, double* sh)
-{
-    sh[threadIdx.x] = v;
-    __syncthreads();
+    // (eight layers' loads in flight)
+    for (int k0 = g.nlay - 1; k0 >= 0; k0 -= 8) {
+        double a[8];
 #pragma unroll
-    for (int s = NT / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] = sh[threadIdx.x] + sh[threadIdx.x + s];
-        __syncthreads();
+        for (int u = 0; u < 8; ++u) a[u] = k0 >= u ? a_ext[((k0 - u) * g.nlat + j) * g.nlon + i] : 0.0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int k = k0 - u;
+            if (k < 0) break;
+            if (tau > tau_vert) L[(k * g.nlat + j) * g.nlon + i] = 0.0;
+            tau = tau + a[u] * (g.r[k + 1] - g.r[k]);
+        }
     }
-    double r = sh[0];
-    __syncthreads();
-    return r;
 }
 
 // (sum L, count L > 0) per 256 cells -> part[slot][block][2]
 __global__ void __launch_bounds__(256) k_prep_sumL(const PrepSlot* __restrict__ slots, int n, double* __restrict__ part)
 {
-    __shared__ double sh[256];
+    __shared__ double sh[2][256];
     const PrepSlot S = slots[blockIdx.y];
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    double v = c < n ? S.cdf[c] : 0.0;
-    double cnt = (c < n && v > 0.0) ? 1.0 : 0.0;
-    double s = bsum<256>(v, sh);
-    double m = bsum<256>(cnt, sh);
-    if (threadIdx.x == 0) {
-        double* p = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 2;
-        p[0] = s;
-        p[1] = m;
-    }
+    const int c = blockIdx.x * 256 + threadIdx.x, t = threadIdx.x;
+    const double v = c < n ? S.cdf[c] : 0.0;
+    sh[0][t] = v;
+    sh[1][t] = (c < n && v > 0.0) ? 1.0 : 0.0;
+    __syncthreads();
+    if (t >= 128) return;
+    // waves 0 and 1: the two sums, each a tree of 128, 64, .. 1 apart
+    const double* x = sh[t >> 6];
+    const int l = t & 63;
+    double s = (x[l] + x[l + 128]) + (x[l + 64] + x[l + 192]);
+    for (int o = 32; o > 0; o >>= 1) s = s + __shfl_down(s, o);
+    if (l == 0) part[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 2 + (t >> 6)] = s;
 }
 
 // Neumaier-compensated sum of the block partials -> slot stats (L_tot, N_emit).
@@ -185,37 +199,37 @@ __global__ void __launch_bounds__(256) k_prep_stats(const PrepSlot* __restrict__
     if (threadIdx.x == 0) S.stats[col] = sh[0] + shc[0];
 }
 
-// q_i into cdf (in place of L), birth weights (L_i/L_tot)/q_i.
-__global__ void __launch_bounds__(256) k_prep_bias(const PrepSlot* __restrict__ slots, int n, double xi)
-{
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= n) return;
-    const PrepSlot S = slots[blockIdx.y];
-    const double Ltot = S.stats[0], nemit = S.stats[1];
-    const double Lc = S.cdf[c];
-    double qc = 0.0;
-    if (Lc > 0.0) qc = (1.0 - xi) * Lc / Ltot + xi / nemit;
-    S.cdf[c] = qc;
-    S.wbirth[c] = (Lc > 0.0) ? (Lc / Ltot) / qc : 0.0;
-}
-
-// In-place inclusive scan of cdf per slot: runs of 8 per thread, a
-// Hillis-Steele scan over the 256 thread totals, block totals scanned by one
-// block per slot, then the block offsets added.
+// q_i and the birth weights (L_i / L_tot) / q_i of L_i (in cdf), and in its place
+// the inclusive scan of q_i: runs of 8 per thread, a Hillis-Steele scan over the
+// 256 thread totals, block totals scanned by one block per slot, then the block
+// offsets added.
 __global__ void __launch_bounds__(256) k_prep_scan_local(const PrepSlot* __restrict__ slots, int n,
-                                                         double* __restrict__ blocksum)
+                                                         double xi, double* __restrict__ blocksum)
 {
+    // (thread t scans elements 8 t .. 8 t + 7; they pass through LDS so that
+    // memory is read and written in whole lines)
     __shared__ double sh[256];
+    __shared__ double el[kScanBlock + kScanBlock / kScanPer];
     const PrepSlot S = slots[blockIdx.y];
     double* io = S.cdf;
-    const int base = blockIdx.x * kScanBlock + threadIdx.x * kScanPer;
-    double loc[kScanPer];
+    const double Ltot = S.stats[0], nemit = S.stats[1];
+    const int base = blockIdx.x * kScanBlock;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+        const int e = q * 256 + threadIdx.x;
+        const double Lc = base + e < n ? io[base + e] : 0.0;
+        double x = 0.0;
+        if (Lc > 0.0) x = (1.0 - xi) * Lc / Ltot + xi / nemit;
+        if (base + e < n) S.wbirth[base + e] = (Lc > 0.0) ? (Lc / Ltot) / x : 0.0;
+        el[e + e / kScanPer] = x;
+    }
+    __syncthreads();
+    double* mine = el + threadIdx.x * (kScanPer + 1);
     double run = 0.0;
 #pragma unroll
     for (int q = 0; q < kScanPer; ++q) {
-        double x = (base + q < n) ? io[base + q] : 0.0;
-        run = run + x;
-        loc[q] = run;
+        run = run + mine[q];
+        mine[q] = run;
     }
     sh[threadIdx.x] = run;
     __syncthreads();
@@ -225,10 +239,15 @@ __global__ void __launch_bounds__(256) k_prep_scan_local(const PrepSlot* __restr
         sh[threadIdx.x] = sh[threadIdx.x] + v;
         __syncthreads();
     }
-    double pre = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0.0;
+    const double pre = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0.0;
 #pragma unroll
-    for (int q = 0; q < kScanPer; ++q)
-        if (base + q < n) io[base + q] = pre + loc[q];
+    for (int q = 0; q < kScanPer; ++q) mine[q] = pre + mine[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+        const int e = q * 256 + threadIdx.x;
+        if (base + e < n) io[base + e] = el[e + e / kScanPer];
+    }
     if (threadIdx.x == 255) blocksum[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = sh[255];
 }
 
@@ -284,8 +303,11 @@ void launch_prep_optics(const GridDev& g, int ncell, const PrepSlot* slots, int 
                         const double* T_grid, const double* lnP_grid, const double* lnk_tpl, int nlam,
                         const double* shift, int draine, double alpha, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_prep_optics, dim3(nb(ncell, 256), nslots), dim3(256), 0, stream, g, ncell, slots, hires, nT,
-                       nP, T_grid, lnP_grid, lnk_tpl, nlam, shift, draine, alpha);
+    // up to eight slots a thread, of launches that leave eight blocks a CU
+    const unsigned blocks = nb(ncell, 256);
+    const int per = std::min(std::max((int)((long long)blocks * nslots / 2048), 1), kOpticsSlots);
+    hipLaunchKernelGGL(k_prep_optics, dim3(blocks, nb(nslots, per)), dim3(256), 0, stream, g, ncell, slots, nslots, per, hires,
+                       nT, nP, T_grid, lnP_grid, lnk_tpl, nlam, shift, draine, alpha);
 }
 
 void launch_prep_sources(const GridDev& g, int ncell, const PrepSlot* slots, int nslots, double tau_vert, double xi,
@@ -297,8 +319,7 @@ void launch_prep_sources(const GridDev& g, int ncell, const PrepSlot* slots, int
     hipLaunchKernelGGL(k_prep_L, dim3(ncol, nslots), dim3(256), 0, stream, g, slots, tau_vert);
     hipLaunchKernelGGL(k_prep_sumL, dim3(b256, nslots), dim3(256), 0, stream, slots, ncell, lpart);
     hipLaunchKernelGGL(k_prep_stats, dim3(2, nslots), dim3(256), 0, stream, slots, lpart, (int)b256);
-    hipLaunchKernelGGL(k_prep_bias, dim3(b256, nslots), dim3(256), 0, stream, slots, ncell, xi);
-    hipLaunchKernelGGL(k_prep_scan_local, dim3(bs, nslots), dim3(256), 0, stream, slots, ncell, bsum);
+    hipLaunchKernelGGL(k_prep_scan_local, dim3(bs, nslots), dim3(256), 0, stream, slots, ncell, xi, bsum);
     if (bs > 1) {
         hipLaunchKernelGGL(k_prep_scan_blocksums, dim3(1, nslots), dim3(256), 0, stream, bsum, (int)bs);
         hipLaunchKernelGGL(k_prep_scan_add, dim3(b256, nslots), dim3(256), 0, stream, slots, ncell, bsum, (int)bs);
