@@ -841,29 +841,28 @@ int split_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, bool use_graph, uint6
     // a wave's chunk: an eighth of its share, so that few slots stay empty
     const uint64_t chunk = std::min<uint64_t>(std::max<uint64_t>(recs * 64 / (lanes * 8), 16), 256);
     recs = (recs + kXcds * chunk - 1) / (kXcds * chunk) * (kXcds * chunk);
-    const Want want[9] = {{"peel_rec", peel_record_bytes(mixed) * recs},
+    const Want want[8] = {{"peel_rec", peel_record_bytes(mixed) * recs},
+                          {"peel_out", sizeof(PeelOut) * n_out * recs},
                           {"peel_next", sizeof(uint32_t) * recs},
-                          {"peel_f", sizeof(double) * n_out * recs},
                           {"peel_head", sizeof(uint32_t) * T},
                           {"peel_ctl", sizeof(uint32_t) * kPeelCtl},
                           {"peel_cross", sizeof(uint32_t) * T},
-                          {"peel_nx", sizeof(uint32_t) * n_out * recs},
                           {"peel_park_d", sizeof(double) * kParkD * lanes},
                           {"peel_park_u", sizeof(uint32_t) * kParkU * lanes}};
-    void* p[9];
+    void* p[8];
     bool there = false;
-    if (int rc = spare_scratch(ctx, sl, st, want, 9, p, there)) return rc;
+    if (int rc = spare_scratch(ctx, sl, st, want, 8, p, there)) return rc;
     if (!there) return MCRT_OK;
     sl.spare_busy = true;
     if (!sl.flag) HIPTRY(hipHostMalloc((void**)&sl.flag, sizeof(uint32_t)));
-    q.next = (uint32_t*)p[1];
-    q.f = (double*)p[2];
+    q.out = (PeelOut*)p[1];
+    q.next = (uint32_t*)p[2];
     q.head = (uint32_t*)p[3];
     q.ctl = (uint32_t*)p[4];
     q.peel_cross = (uint32_t*)p[5];
-    q.nx = (uint32_t*)p[6];
-    q.park_d = (double*)p[7];
-    q.park_u = (uint32_t*)p[8];
+    q.park_d = (double*)p[6];
+    q.park_u = (uint32_t*)p[7];
+    q.scarce = 8 * T > recs;
     q.cap = (uint32_t)(recs / kXcds);
     q.chunk = (uint32_t)chunk;
     q.n_lanes = (int)lanes;
@@ -1146,10 +1145,10 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
         launch_reduce_rows(A, nb, (double*)v_part, chunks, sums + (size_t)s0 * row_w, row_w, dump, st);
     };
     // Waits for batch bt; further rounds of a split launch whose records ran
-    // out, then the reduction again.
+    // out, then the reduction (again, unless rounds were expected).
     auto complete = [&](int bt, int nb) -> int {
         HIPTRY(hipStreamSynchronize(st));
-        if (!split || *sl.flag == 0) return MCRT_OK;
+        if (!split || (*sl.flag == 0 && !Q.scarce)) return MCRT_OK;
         Q.resume = 1;
         while (*sl.flag != 0) {
             launch_peel_reset(Q, st);
@@ -1260,7 +1259,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
                                             sl.stream_ordered ? serving_blocks(ctx, bpc) : pblocks, st);
             }
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * bt + 1], st));
-            reduce(bt, nb);
+            if (!Q.scarce) reduce(bt, nb);  // (scarce records: after the rounds)
             // the next batch reuses the slots: in eager form its pageable host tables are
             // copied only after this batch ran
             if (!use_graph && bt + 1 < nbatches) {
@@ -1292,6 +1291,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
         if ((rc = enqueue())) return rc;
     }
     HIPTRY(hipGetLastError());
+    if (Q.scarce && (rc = complete(nbatches - 1, nsolve - (nbatches - 1) * batch))) return rc;
     std::vector<double> hs((size_t)nsolve * row_w);
     HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
     if ((rc = finish_timing(ctx, sl, st, res))) return rc;
@@ -1864,7 +1864,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
     // Waits for launch li; further rounds of a split launch, as in solve_packets.
     auto complete = [&](size_t li) -> int {
         HIPTRY(hipStreamSynchronize(st));
-        if (!split || *sl.flag == 0) return MCRT_OK;
+        if (!split || (*sl.flag == 0 && !Q.scarce)) return MCRT_OK;
         Q.resume = 1;
         while (*sl.flag != 0) {
             launch_peel_reset(Q, st);
@@ -1966,7 +1966,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
                 launch_transport_persistent(hgrids[0], A, mixed, true, pblocks, st);
             }
             if (prof) HIPTRY(hipEventRecord(sl.prof_ev[2 * li + 1], st));
-            reduce(li);
+            if (!Q.scarce) reduce(li);  // (scarce records: after the rounds)
             // in eager form the next launch's pageable tables are copied only after
             // this launch ran; stream order alone protects the reused device buffers
             if (!use_graph && li + 1 < launches.size()) {
@@ -1997,6 +1997,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
         if ((rc = enqueue())) return rc;
     }
     HIPTRY(hipGetLastError());
+    if (Q.scarce && (rc = complete(launches.size() - 1))) return rc;
     std::vector<double> hs((size_t)nsolve * row_w);
     HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
     mcrt_result tr{};

@@ -452,7 +452,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     int state = P_IDLE, lgrid = 0, lcol = 0, ncw = 0, kind = 0, solve = 0, cell = 0;
     Walker w;
     double tau = 0.0, wt = 0.0, q2 = 0.0;
-    uint32_t fi = 0;  // the ray's place in Q.f and Q.nx
+    uint32_t fi = 0;  // the ray's place in Q.out
     Prop<MIXED> ae = 0;
     const void* aext = nullptr;
     uint32_t res_next = 0, res_end = 0, region = 0;  // the wave's rays
@@ -545,8 +545,8 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
             // scattered light of a transmission packet: per steradian, over the
             // stellar beam's solid angle (peel_w = 1 otherwise)
             if (kind != R_BIRTH) f = f * A.peel_w;
-            Q.f[fi] = f;
-            Q.nx[fi] = (uint32_t)ncw;
+            Q.out[fi].f = f;
+            Q.out[fi].nx = (uint32_t)ncw;
             const SolveDev& S = A.solves[solve];
             if ((S.cf || S.img) && f > 0.0) {
                 const uint32_t o = fi % n_out, ijk = recs[fi / n_out].ijk;
@@ -658,13 +658,18 @@ __global__ void __launch_bounds__(256) k_peel_sum(BatchArgs A, PeelArgs Q)
     for (int o = 0; o < kMaxObs; ++o)
         if (o < A.n_out) F[o] = row[o];
     while (r != kNoRecord) {
-        const uint32_t n = Q.next[r];
-        const double* f = Q.f + (size_t)r * A.n_out;
+        const PeelOut* out = Q.out + (size_t)r * A.n_out;
+        PeelOut x[kMaxObs];
 #pragma unroll
         for (int o = 0; o < kMaxObs; ++o)
-            if (o < A.n_out) F[o] += f[o];
-        for (int o = 0; o < A.n_out; ++o) nx += Q.nx[(size_t)r * A.n_out + o];
-        r = n;
+            if (o < A.n_out) x[o] = out[o];
+        r = Q.next[r];
+#pragma unroll
+        for (int o = 0; o < kMaxObs; ++o)
+            if (o < A.n_out) {
+                F[o] += x[o].f;
+                nx += x[o].nx;
+            }
     }
 #pragma unroll
     for (int o = 0; o < kMaxObs; ++o)

@@ -141,13 +141,18 @@ struct BatchArgs {
 // that peels off, a second kernel walks the peel-off rays of all records, a
 // third adds their contributions to the packets' rows in the order of events.
 constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
+// What a record's ray towards one observer gives: its contribution and number of
+// crossings.  One cache line holds those of four observers.
+struct alignas(16) PeelOut {
+    double f;
+    uint32_t nx;
+};
 struct PeelArgs {
     void* rec;        // records, one region per XCD
     uint32_t* head;   // BatchArgs.head and peel_cross
     uint32_t* peel_cross;
     uint32_t* next;   // the packet's next record
-    double* f;        // [record][n_out]: the rays' contributions and crossings
-    uint32_t* nx;
+    PeelOut* out;     // [record][n_out]: the rays
     uint32_t cap;     // records per region (a multiple of chunk)
     uint32_t chunk;   // records a wave takes at once
     uint32_t* ctl;    // counters a cache line apart: records and dispensed rays per region, parked lanes
@@ -155,6 +160,7 @@ struct PeelArgs {
     uint32_t* park_u;
     int n_lanes;      // lanes of the flight kernel (the same in every round of a launch)
     int resume;       // not the first round
+    int scarce;       // fewer records than packets usually need: further rounds are likely
 };
 constexpr int kPeelCtl = (2 * kXcds + 1) * kCtrStride;
 constexpr int kParkD = 10, kParkU = 9;
