@@ -623,8 +623,8 @@ __host__ __device__ __forceinline__ double wk_ray_q2(const Walker& w) { return f
 __host__ __device__ __forceinline__ void wk_ray_shell(Walker& w, double D, double sq)
 {
     const bool out = w.dk > 0, miss = !out & !(D >= 0.0);
-    const double u = out ? sq : (miss ? -(w.t + w.B0) : -sq);
-    w.ts = wk_max(u - w.B0, w.t);
+    const double v = miss ? w.t + w.B0 : sq;
+    w.ts = wk_max(wk_flip(v, w.dk) - w.B0, w.t);
     w.dk = miss ? 1 : w.dk;
 }
 

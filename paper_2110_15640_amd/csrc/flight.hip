@@ -443,7 +443,10 @@ template <bool MIXED, bool MULTI, int GEO>
 __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
 {
     __shared__ double sobs[2 * 3 * kMaxObs];
+    extern __shared__ double radii[];  // the grid's (of one grid): a shell step then waits for no load but the last one's
     if (threadIdx.x < 2 * 3 * kMaxObs) sobs[threadIdx.x] = A.obs[threadIdx.x / (3 * kMaxObs)][threadIdx.x % (3 * kMaxObs)];
+    if (!MULTI)
+        for (int e = threadIdx.x; e <= g1.nlay; e += kTPB) radii[e] = g1.r[e];
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -494,7 +497,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
                 cell += out ? ncol : -ncol;
                 const bool inside = (unsigned)w.k < (unsigned)g.nlay;
                 const double a = (double)ae;
-                const double R = wk_edge(g, inside ? w.k : 0, out);
+                const double R = MULTI ? wk_edge(g, inside ? w.k : 0, out) : radii[inside ? w.k + (out ? 1 : 0) : 0];
                 ae = (Prop<MIXED>)ld<MIXED>(aext, inside ? cell : 0);
                 if (through(w.ts, a, inside)) {
                     if constexpr (GEO == GEO_SLAB) {
@@ -721,8 +724,9 @@ void launch_flight(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool
 void launch_peel(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool mixed, bool multi, int blocks,
                  hipStream_t stream)
 {
+    const size_t lds = multi ? 0 : sizeof(double) * (g.nlay + 1);
     const int geo = multi ? GEO_SPHERE : g.geom;
-#define MCRT_K(MX, MU, GE) hipLaunchKernelGGL((k_peel<MX, MU, GE>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q)
+#define MCRT_K(MX, MU, GE) hipLaunchKernelGGL((k_peel<MX, MU, GE>), dim3(blocks), dim3(kTPB), lds, stream, g, a, q)
     if (geo == GEO_SLAB) {
         if (mixed) MCRT_K(true, false, GEO_SLAB);
         else MCRT_K(false, false, GEO_SLAB);
