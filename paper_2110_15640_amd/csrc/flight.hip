@@ -254,9 +254,11 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
         if (MULTI) lgrid = S.grid;
     }
     for (;;) {
+        on_grid<MULTI>(g1, A.grids, lgrid, L.mode <= M_PROBE, [&](const GridDev& g) {
+            if (GEO != GEO_SLAB && L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
+            if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO, false>(L, g, aext, aabs, ae, A);
+        });
         const GridDev& g = MULTI ? A.grids[lgrid] : g1;
-        if (GEO != GEO_SLAB && L.mode <= M_PROBE && g.eq_edge > 0 && L.w.eq != 0) wk_row_roots<MIXED>(g, L.w);
-        if (L.mode <= M_PROBE) walk_step<MIXED, EXT, GEO, false>(L, g, aext, aabs, ae, A);
         const unsigned long long walking = __ballot(L.mode <= M_PROBE);
         const unsigned long long waits = __ballot(L.mode == M_EVENT || (L.mode == M_DEAD && !exhausted));
         // ev_threshold of 64 lanes, in proportion where fewer carry packets
@@ -440,7 +442,7 @@ enum { P_IDLE = 0, P_WALK = 1, P_ANGLE = 2, P_DONE = 3 };
 constexpr int kPeelThreshold = 24, kAngleThreshold = 16, kShellSteps = 3;
 
 template <bool MIXED, bool MULTI, int GEO>
-__global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
+__global__ void __launch_bounds__(kTPB, MULTI ? 4 : 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
 {
     __shared__ double sobs[2 * 3 * kMaxObs];
     extern __shared__ double radii[];  // the grid's (of one grid): a shell step then waits for no load but the last one's
@@ -452,7 +454,7 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const EvRec<MIXED>* recs = (const EvRec<MIXED>*)Q.rec;
     const uint32_t n_out = (uint32_t)A.n_out;
-    int state = P_IDLE, lgrid = 0, lcol = 0, ncw = 0, kind = 0, solve = 0, cell = 0;
+    int state = P_IDLE, lgrid = 0, ncw = 0, kind = 0, solve = 0, cell = 0;
     Walker w;
     double tau = 0.0, wt = 0.0, q2 = 0.0;
     uint32_t fi = 0;  // the ray's place in Q.out
@@ -470,69 +472,72 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
     uint32_t share = __shfl(rays, (int)(blockIdx.x % kXcds)) / (gridDim.x / kXcds * (kTPB / 64) * 8u + 1u) & ~63u;
     if (share < 64u) share = 64u;
     for (;;) {
-        const GridDev& g = MULTI ? A.grids[lgrid] : g1;
-        const int ncol = MULTI ? lcol : g1.nlat * g1.nlon;
-        // a ray ends at the top; beyond tau_peel_max, on the planet or after too
-        // many cells nothing of it arrives
-        auto through = [&](double t, double a, bool inside) {
-            tau = wk_mad<MIXED>(a, t - w.t, tau);
-            w.t = t;
-            ncw++;
-            const bool dark = tau > A.tau_peel_max;
-            const bool end = !inside | dark | (ncw >= g.max_cross);
-            if (end) {
-                if (dark | inside | (w.k < 0)) tau = INFINITY;
-                state = P_DONE;
-            }
-            return !end;
-        };
+        unsigned long long walking;
+        on_grid<MULTI>(g1, A.grids, lgrid, state == P_WALK || state == P_ANGLE, [&](const GridDev& g) {
+            const int ncol = g.nlat * g.nlon;
+            // a ray ends at the top; beyond tau_peel_max, on the planet or after too
+            // many cells nothing of it arrives
+            auto through = [&](double t, double a, bool inside) {
+                tau = wk_mad<MIXED>(a, t - w.t, tau);
+                w.t = t;
+                ncw++;
+                const bool dark = tau > A.tau_peel_max;
+                const bool end = !inside | dark | (ncw >= g.max_cross);
+                if (end) {
+                    if (dark | inside | (w.k < 0)) tau = INFINITY;
+                    state = P_DONE;
+                }
+                return !end;
+            };
 #pragma unroll
-        for (int m = 0; m < kShellSteps; ++m) {
-            if (state != P_WALK) continue;
-            if (GEO != GEO_SLAB && wk_min(w.tc, w.tp) < w.ts) {
-                state = P_ANGLE;
-            } else {
-                const bool out = w.dk > 0;
-                w.k += w.dk;
-                cell += out ? ncol : -ncol;
-                const bool inside = (unsigned)w.k < (unsigned)g.nlay;
-                const double a = (double)ae;
-                const double R = MULTI ? wk_edge(g, inside ? w.k : 0, out) : radii[inside ? w.k + (out ? 1 : 0) : 0];
-                ae = (Prop<MIXED>)ld<MIXED>(aext, inside ? cell : 0);
-                if (through(w.ts, a, inside)) {
-                    if constexpr (GEO == GEO_SLAB) {
-                        w.ts = wk_max(wk_div<MIXED>(R - w.pz, w.dz), w.t);
-                    } else {
-                        const double D = fma(R, R, -q2);
-                        wk_ray_shell(w, D, wk_sqrt<MIXED>(D));
+            for (int m = 0; m < kShellSteps; ++m) {
+                if (state != P_WALK) continue;
+                if (GEO != GEO_SLAB && wk_min(w.tc, w.tp) < w.ts) {
+                    state = P_ANGLE;
+                } else {
+                    const bool out = w.dk > 0;
+                    w.k += w.dk;
+                    cell += out ? ncol : -ncol;
+                    const bool inside = (unsigned)w.k < (unsigned)g.nlay;
+                    const double a = (double)ae;
+                    const double R = MULTI ? wk_edge(g, inside ? w.k : 0, out) : radii[inside ? w.k + (out ? 1 : 0) : 0];
+                    ae = (Prop<MIXED>)ld<MIXED>(aext, inside ? cell : 0);
+                    if (through(w.ts, a, inside)) {
+                        if constexpr (GEO == GEO_SLAB) {
+                            w.ts = wk_max(wk_div<MIXED>(R - w.pz, w.dz), w.t);
+                        } else {
+                            const double D = fma(R, R, -q2);
+                            wk_ray_shell(w, D, wk_sqrt<MIXED>(D));
+                        }
                     }
                 }
             }
-        }
-        unsigned long long walking = __ballot(state == P_WALK);
-        if constexpr (GEO != GEO_SLAB) {
-            const unsigned long long angle = __ballot(state == P_ANGLE);
-            if (angle != 0 && (walking == 0 || __popcll(angle) >= (more ? kAngleThreshold : 1))) {
-                if (state == P_ANGLE) {
-                    CrossKind x;
-                    x.t = wk_min(w.tc, w.tp);
-                    x.shell = x.none = false;
-                    x.cone = w.tc <= x.t;
-                    const double a = (double)ae, t0 = w.t;
-                    const CrossIn in = wk_cross_begin<GEO>(g, w, x);
-                    w.t = t0;
-                    cell = wk_cell(g, w);
-                    ae = (Prop<MIXED>)ld<MIXED>(aext, cell);
-                    if (through(x.t, a, true)) {
-                        wk_cross_end<MIXED, GEO>(g, w, x, in);
-                        if (g.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(g, w);
-                        state = P_WALK;
+            walking = __ballot(state == P_WALK);
+            if constexpr (GEO != GEO_SLAB) {
+                const unsigned long long angle = __ballot(state == P_ANGLE);
+                if (angle != 0 && (walking == 0 || __popcll(angle) >= (more ? kAngleThreshold : 1))) {
+                    if (state == P_ANGLE) {
+                        CrossKind x;
+                        x.t = wk_min(w.tc, w.tp);
+                        x.shell = x.none = false;
+                        x.cone = w.tc <= x.t;
+                        const double a = (double)ae, t0 = w.t;
+                        const CrossIn in = wk_cross_begin<GEO>(g, w, x);
+                        w.t = t0;
+                        cell = wk_cell(g, w);
+                        ae = (Prop<MIXED>)ld<MIXED>(aext, cell);
+                        if (through(x.t, a, true)) {
+                            wk_cross_end<MIXED, GEO>(g, w, x, in);
+                            if (g.eq_edge > 0 && w.eq != 0) wk_row_roots<MIXED>(g, w);
+                            state = P_WALK;
+                        }
                     }
+                    walking = __ballot(state == P_WALK);
                 }
-                walking = __ballot(state == P_WALK);
+                walking |= __ballot(state == P_ANGLE);
             }
-            walking |= __ballot(state == P_ANGLE);
-        }
+        });
+        const GridDev& g = MULTI ? A.grids[lgrid] : g1;
         if (walking != 0 && ((!more && res_next >= res_end) || 64 - __popcll(walking) < kPeelThreshold)) continue;
         if (state == P_DONE) {
             state = P_IDLE;
@@ -630,7 +635,6 @@ __global__ void __launch_bounds__(kTPB, 5) k_peel(GridDev g1, BatchArgs A, PeelA
                 ncw = 0;
                 const int i = (int)(v.ijk & 0x7FFu), j = (int)((v.ijk >> 11) & 0x3FFu), k = (int)(v.ijk >> 21);
                 cell = (k * gs.nlat + j) * gs.nlon + i;
-                if (MULTI) lcol = gs.nlat * gs.nlon;
                 ae = (Prop<MIXED>)ld<MIXED>(aext, cell);
                 wk_start<MIXED, GEO>(gs, w, px, py, v.z, dx, dy, dz, i, j, k);
                 q2 = wk_ray_q2(w);
