@@ -1065,15 +1065,17 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     const int bpc = p->tune_blocks_per_cu > 0 ? p->tune_blocks_per_cu : 4;
     const int pblocks = ctx->n_cu * bpc;
     const uint64_t t_max = (uint64_t)(gs ? batch / ng : batch) * N;  // packets of a launch
-    PeelArgs Q;
+    PeelArgs Q{};
     // a split launch of few packets spreads them over all waves
     A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
     const int fblocks = (int)std::min<uint64_t>(pblocks, (t_max + 4 * A.lanes - 1) / (4 * A.lanes));
-    if ((rc = split_scratch(ctx, sl, st, p->graph != 0, t_max, no, mixed, fblocks, Q))) return rc;
+    A.slab = g->dev.geom == 1 && mode == MCRT_MODE_ALBEDO && !p->contrib && !npix && !gs && p->absorption != 1 &&
+             p->cloud_phase != 2 && p->forced == 0 && !(p->surface_albedo > 0.0);
+    if (!A.slab && (rc = split_scratch(ctx, sl, st, p->graph != 0, t_max, no, mixed, fblocks, Q))) return rc;
     const bool split = Q.rec != nullptr;
     A.head = Q.head;
     A.peel_cross = Q.peel_cross;
-    if (split && A.lanes < 64) A.batch = A.lanes;
+    if ((split || A.slab) && A.lanes < 64) A.batch = A.lanes;
     if (split && p->tune_ev_threshold <= 0) A.ev_threshold = 32;  // (flights only: 3 % faster than 16 at full launches)
     if (npix) {
         A.npix = npix;
@@ -1217,6 +1219,7 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
                 S.mode = mode == MCRT_MODE_EMISSION ? 1 : (mode == MCRT_MODE_TRANSMISSION ? 2 : 0);
                 S.grid = 0;
                 S.cdf = P.cdf;
+                S.depth = A.slab ? P.opt + ncell : nullptr;  // (in place of the absorption, which such a launch does not read)
                 S.wbirth = P.wbirth;
                 if (v_cf || v_img) {  // scaled as the band value: w_g pi / N, or w_g L_tot / (N R_TOA^2)
                     const double wg = op->kind == MCRT_OPAC_CK ? op->g_weights[gi] : 1.0;
@@ -1766,7 +1769,7 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
         for (int s = L.first; s < L.second; ++s) t += it[fl[s].item]->p.n_packets;
         t_max = std::max(t_max, t);
     }
-    PeelArgs Q;
+    PeelArgs Q{};
     // a split launch of few packets spreads them over all waves
     A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
     const int fblocks = (int)std::min<uint64_t>(pblocks, (t_max + 4 * A.lanes - 1) / (4 * A.lanes));

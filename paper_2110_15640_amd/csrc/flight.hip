@@ -393,47 +393,6 @@ __global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, Pee
     if (lane == 0 && left != 0) atomicAdd(Q.ctl + 2 * kXcds * kCtrStride, (uint32_t)__popcll(left));
 }
 
-// The phase-function weight of a ray at cosine mu of its record, times 1/(4 pi).
-template <bool MIXED>
-__device__ __forceinline__ double peel_weight(const BatchArgs& A, double w, double mu, double pg, double gc)
-{
-    // normalised mixture of the Rayleigh and cloud phase functions toward the
-    // observer, weighted by the gas scattering probability
-    if (MIXED) {
-        const float m = (float)mu, pgf = (float)pg, gcf = (float)gc;
-        const float pr = 0.75f * (1.0f + m * m);
-        auto hgf = [m](float gg) {
-            if (!(fabsf(gg) >= 1e-6f)) return 1.0f;
-            const float den = 1.0f + gg * gg - 2.0f * gg * m;
-            return (1.0f - gg * gg) / (den * sqrtf(den));
-        };
-        float ph;
-        if (A.cloud_phase == 1) {
-            const float g2 = -0.5f * gcf, af = 1.0f - g2 * g2;
-            ph = af * hgf(gcf) + (1.0f - af) * hgf(g2);
-        } else if (A.cloud_phase == 2) {  // Draine (gcf is G)
-            const float al = (float)A.draine_alpha;
-            ph = hgf(gcf) * (1.0f + al * m * m) / (1.0f + al * (1.0f + 2.0f * gcf * gcf) / 3.0f);
-        } else {
-            ph = hgf(gcf);
-        }
-        const float theta = (pgf * pr + (1.0f - pgf) * ph) * (float)(0.25 / kPi);
-        return (double)((float)w * theta);
-    }
-    double pc;
-    if (A.cloud_phase == 1) {
-        const double g2 = -0.5 * gc, a = 1.0 - g2 * g2;
-        pc = a * p_hg(mu, gc) + (1.0 - a) * p_hg(mu, g2);
-    } else if (A.cloud_phase == 2) {  // Draine (gc is G)
-        const double al = A.draine_alpha;
-        pc = p_hg(mu, gc) * (1.0 + al * mu * mu) / (1.0 + al * (1.0 + 2.0 * gc * gc) / 3.0);
-    } else {
-        pc = p_hg(mu, gc);
-    }
-    const double theta = (pg * p_rayleigh(mu) + (1.0 - pg) * pc) / (4.0 * kPi);
-    return w * theta;
-}
-
 // One peel-off ray per lane: ray q of region x is observer q % n_out of its
 // record q / n_out, taken by waves of the region's XCD first (whose L2 holds the optics the region's flights used).
 enum { P_IDLE = 0, P_WALK = 1, P_ANGLE = 2, P_DONE = 3 };

@@ -78,6 +78,7 @@ struct SolveDev {
     int gs_scheme;
     const double* gs_w;    // g-ordinate weights of the table
     const double* ltot;    // emission: L_tot of this solve (written by the preparation)
+    double* depth;         // slab launches: optical depth from the top, [nlay]
 };
 
 // Stellar limb darkening of transmission chords and packets: law (0 none,
@@ -112,6 +113,7 @@ struct BatchArgs {
     double mu0;
     double r_toa;
     double obs[2][3 * kMaxObs];  // observer directions for albedo [0] and emission [1] solves
+    int slab;          // scattered light of a slab without what slab.hip leaves to the general kernels
     int batch;         // packets a wave takes from the dispenser at once
     int lanes;         // lanes of a wave that carry packets (split launches)
     int ev_threshold;  // waiting lanes that trigger event handling
@@ -192,6 +194,7 @@ void launch_prep_sources(const GridDev& g, int ncell, const PrepSlot* slots, int
                          double xi, double* scratch, hipStream_t stream);
 size_t prep_scratch_doubles(int ncell, int nslots);
 
+void launch_slab(const GridDev& g, const BatchArgs& a, bool mixed, int blocks, hipStream_t stream);
 void launch_transport_persistent(const GridDev& g, const BatchArgs& a, bool mixed, bool multi, int blocks,
                                  hipStream_t stream);
 void launch_reduce_rows(const BatchArgs& a, int n_solves, double* partials, int chunks, double* sums, int sums_w,

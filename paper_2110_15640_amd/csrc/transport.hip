@@ -768,6 +768,10 @@ void launch_births(const GridDev& g, const BatchArgs& a, bool multi, hipStream_t
 void launch_transport_persistent(const GridDev& g, const BatchArgs& a, bool mixed, bool multi, int blocks,
                                  hipStream_t stream)
 {
+    if (a.slab) {
+        launch_slab(g, a, mixed, blocks, stream);
+        return;
+    }
     // the extended form only when a launch uses one of its features
     const bool ext = a.surface_albedo > 0.0 || a.cloud_phase == 2 || a.forced != 0 || a.trans_ms != 0 ||
                      a.absorption == 1;
