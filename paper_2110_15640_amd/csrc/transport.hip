@@ -655,47 +655,73 @@ __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, Ba
 // sums the chunks.  Optional copy of F to a packet dump.
 //
 // Thread t of a chunk block owns column t % w of the rows t / w, t / w + R,
-// ... (w the row width, R = 256 / w rows per pass), so each pass of the
-// block reads R whole rows as one contiguous, coalesced range; the R
-// per-thread sums of a column are then added in row-slot order.
+// ... (w the row width, R = 1024 / w rows per pass), so each pass of the
+// block reads R whole rows as one contiguous, coalesced range, four passes'
+// loads in flight; the R per-thread sums of a column are then added by eight
+// threads and theirs by one.  Latency-bound where solves are small: 40 solves of
+// 40000 packets 104 us with 256 threads and one load at a time, 40 here; 16
+// of 1000 21 and 10.
 constexpr int kChunk = 4096;
-constexpr int kRT = 256;
+constexpr int kRT = 256, kPT = 1024, kPJ = 8;
 
-__global__ void __launch_bounds__(kRT) k_rows_partial(BatchArgs A, double* __restrict__ partials, int chunks,
+__global__ void __launch_bounds__(kPT) k_rows_partial(BatchArgs A, double* __restrict__ partials, int chunks,
                                                       double* __restrict__ dump)
 {
-    __shared__ double sh[2 * kRT];
+    __shared__ double sh[2 * kPT];
     const int s = blockIdx.y;
-    const SolveDev S = A.solves[s];
+    const SolveDev& S = A.solves[s];
+    const unsigned long long begin = S.begin, n = S.n;
     const int w = A.row_w;  // n_out peel-off sums + the counters
-    const int R = kRT / w;
+    const int R = kPT / w;
     const int t = threadIdx.x;
     const int c = t % w, r0 = t / w;
     const unsigned long long q0 = (unsigned long long)blockIdx.x * kChunk;
-    const unsigned long long qe = q0 + kChunk < S.n ? q0 + kChunk : S.n;
-    const double* rows = A.rows + S.begin * (unsigned long long)w + c;
+    const unsigned long long qe = q0 + kChunk < n ? q0 + kChunk : n;
+    const double* rows = A.rows + begin * (unsigned long long)w + c;
+    // the rows of a split launch hold F itself also for transmission, and the
+    // crossings of the flights only
+    const bool more = A.head && c == A.n_out + K_NCROSS, from_w0 = A.head && A.trans_ms && c < A.n_out;
     double acc = 0.0, acc2 = 0.0;
     if (r0 < R) {
-#pragma unroll 4
-        for (unsigned long long q = q0 + r0; q < qe; q += R) {
-            double v = rows[q * (unsigned long long)w];
-            // the rows of a split launch hold F itself also for transmission,
-            // and the crossings of the flights only
-            if (A.head && c == A.n_out + K_NCROSS) v += (double)A.peel_cross[S.begin + q];
-            if (A.head && A.trans_ms && c < A.n_out) v = rows[q * (unsigned long long)w + A.n_out + K_W0 - c] - v;
-            acc = acc + v;
-            acc2 = acc2 + v * v;
-            if (dump && c < A.n_out) dump[(S.begin + q) * (unsigned long long)A.n_out + c] = v;
+        for (unsigned long long q = q0 + r0; q < qe; q += 4 * R) {
+            double v[4], x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long p = q + (unsigned)(u * R) < qe ? q + (unsigned)(u * R) : q;
+                v[u] = rows[p * (unsigned long long)w];
+                x[u] = 0.0;
+                if (more) x[u] = (double)A.peel_cross[begin + p];
+                if (from_w0) x[u] = rows[p * (unsigned long long)w + A.n_out + K_W0 - c];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned long long p = q + (unsigned)(u * R);
+                if (p >= qe) break;
+                const double y = more ? v[u] + x[u] : (from_w0 ? x[u] - v[u] : v[u]);
+                acc = acc + y;
+                acc2 = acc2 + y * y;
+                if (dump && c < A.n_out) dump[(begin + p) * (unsigned long long)A.n_out + c] = y;
+            }
         }
     }
     sh[t] = acc;
-    sh[kRT + t] = acc2;
+    sh[kPT + t] = acc2;
+    __syncthreads();
+    double tot = 0.0, tot2 = 0.0;
+    if (r0 < kPJ) {
+        for (int j = r0; j < R; j += kPJ) {
+            tot = tot + sh[c + j * w];
+            tot2 = tot2 + sh[kPT + c + j * w];
+        }
+    }
+    __syncthreads();
+    sh[t] = tot;
+    sh[kPT + t] = tot2;
     __syncthreads();
     if (t < w) {
-        double tot = 0.0, tot2 = 0.0;
-        for (int j = 0; j < R; ++j) {
+        for (int j = 1; j < kPJ; ++j) {
             tot = tot + sh[t + j * w];
-            tot2 = tot2 + sh[kRT + t + j * w];
+            tot2 = tot2 + sh[kPT + t + j * w];
         }
         const int pw = 2 * A.n_out + kNCounters;
         double* out = partials + ((size_t)s * chunks + blockIdx.x) * pw;
@@ -792,7 +818,7 @@ void launch_reduce_rows(const BatchArgs& a, int n_solves, double* partials, int 
                         double* dump, hipStream_t stream)
 {
     const int pw = 2 * a.n_out + kNCounters;
-    hipLaunchKernelGGL(k_rows_partial, dim3(chunks, n_solves), dim3(kRT), 0, stream, a, partials, chunks, dump);
+    hipLaunchKernelGGL(k_rows_partial, dim3(chunks, n_solves), dim3(kPT), 0, stream, a, partials, chunks, dump);
     hipLaunchKernelGGL(k_rows_final, dim3(pw, n_solves), dim3(kRT), 0, stream, partials, chunks, pw, sums, sums_w);
 }
 
