@@ -209,34 +209,20 @@ def transmission_leg(M, I):
             torch.cuda.synchronize()
             wall = time.perf_counter() - t0
             res[name] = r
-            # K5: per (segment, wavelength) one alpha gather (4 B mixed, 8 B FP64),
-            # plus once per 64-wavelength launch the segment record (cell and length:
-            # 8 B mixed, 12 B FP64) and the chord record (offset, impact weight, flag: 20 B)
+            # K5: two FP64 flops per (segment, wavelength), over the summed launch times of
+            # the optical depths (the tallies' sums with them)
             nseg, nl, nblk = r["n_segments"], table.nlam, r["kernel_launches"]
-            ab = 4.0 if prec == M.MCRT_MIXED else 8.0
-            k5_bytes = nseg * nl * ab + nseg * nblk * (ab + 4.0) + nch * nblk * 20.0
-            ncell_tr = grid.nlon * grid.nlat * grid.nlay
-            k5_gbps = k5_bytes / (r["kernel_ms"] * 1e-3) / 1e9
-            P = K5_PROFILE
-            same = kernel_sha("kernels.hip") == P["sha"] and nseg == P["n_segments"] and nl == P["n_lambda"]
+            k5_tflops = 2.0 * nseg * nl / (r["kernel_ms"] * 1e-3) / 1e12
             out[name] = {"ms": wall * 1e3, "chord_wavelengths_per_s": nch * nl / wall,
                          "chord_tau_kernel_ms": r["kernel_ms"], "chord_tau_launches": nblk, "segments": nseg,
-                         # the extinction blocks of one launch are formed while the previous launch's
-                         # chords are summed (two streams), so launches overlap: the same bytes over
+                         # the extinction of one launch's rows is formed while the previous launch's
+                         # chords are summed (two streams), so launches overlap: the same flops over
                          # the whole leg's wall time
-                         "chord_tau_bytes_over_leg_GBps": k5_bytes / wall / 1e9,
-                         "roofline": {"bound": "hbm", "kernel": f"k_chord_tau<{'float' if ab == 4 else 'double'}>",
-                                      "achieved": k5_gbps, "peak": PEAK_HBM, "unit": "GB/s",
-                                      "frac": k5_gbps / PEAK_HBM,
-                                      "traffic": (P["bytes_per_seg_wl"][prec] * nseg * nl / max(nblk, 1)
-                                                  if same else None),
-                                      "traffic_unit": "bytes per launch (mean)",
-                                      "bytes_per_segment_wavelength": ab,
-                                      # one launch's extinction block (cells x 64 wavelengths) is 126 MB in
-                                      # FP32, 252 MB in FP64: it stays in the 256 MB Infinity Cache, so the
-                                      # gathers can pass the HBM rate (frac > 1); the bytes that do leave
-                                      # L2 are the traffic above
-                                      "block_MB": ncell_tr * 64 * ab / 1e6}}
+                         "chord_tau_over_leg_TFLOPs": 2.0 * nseg * nl / wall / 1e12,
+                         "roofline": {"bound": "alu",
+                                      "kernel": f"k_group_tau<{'float' if prec == M.MCRT_MIXED else 'double'}>",
+                                      "achieved": k5_tflops, "peak": PEAK_FP64_VECTOR, "unit": "TFLOP/s",
+                                      "frac": k5_tflops / PEAK_FP64_VECTOR, "traffic": None}}
         depth = res["mixed"]["value"][:, 0]
         d64 = res["fp64"]["value"][:, 0]
         excess = np.abs(res["mixed"]["sums"][..., 0] - res["fp64"]["sums"][..., 0]) / \
@@ -471,7 +457,7 @@ def main():
                   "packets_per_band_for_1e-3_max": float(need.max()),
                   "seconds_per_band_for_1e-3_median_batched": float(np.median(need)) / value,
                   "seconds_per_band_for_1e-3_max_batched": float(need.max()) / value},
-        "roofline": {"bound": "alu", "kernel": "k_transport_persistent<MIXED>", "achieved": ach,
+        "roofline": {"bound": "alu", "kernel": "k_flight + k_peel + k_peel_sum", "achieved": ach,
                      "peak": PEAK_FP64_VECTOR, "unit": "TFLOP/s", "frac": ach / PEAK_FP64_VECTOR, "traffic": traffic,
                      "traffic_unit": "bytes per launch", "avg_launch_ms": avg_s * 1e3, "launches": launches,
                      "solves_per_launch": solves_per_launch, "crossings": cross,

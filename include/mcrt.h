@@ -209,7 +209,8 @@ int mcrt_opacity_free(mcrt_ctx* ctx, int32_t opac_id);
  *   disk term R0^2 is not weighted.  Other laws: EINVAL.
  * transit_y, transit_z: planet centre on the stellar disk [cm] (sky plane). 
  * precision: MCRT_FP64 or MCRT_MIXED.  The FP64 form rounds every operation
- *   on its own (no contraction) and divides correctly rounded, so per-packet
+ *   of a packet's path on its own (no contraction) and divides correctly rounded
+ *   (a slab's path goes by tabulated optical depths in FP64), so per-packet
  *   results agree with an independent FP64 evaluation to ~1e-12; the mixed
  *   form keeps optical properties, phase functions and directions in FP32 and
  *   computes crossings in FP64 with multiply-adds and a refined-reciprocal
