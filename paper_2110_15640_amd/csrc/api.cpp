@@ -824,8 +824,9 @@ int serving_blocks(mcrt_ctx* ctx, int bpc)
 }
 
 // Scratch of the split form of the transport (flight.hip) for launches of up
-// to T packets: records for eight events per packet, 2^19
-// to 2^24 of them in all (a launch whose events need more repeats its kernels:
+// to T packets: records for sixteen events per packet, 2^19
+// to 2^24 of them in all (a launch whose events need more repeats its kernels; with
+// eight per packet 20 solves of 5e4 in clouds took a second round: 7.7 ms, 6.4;
 // at 2^24 a round is tens of milliseconds of the whole device, so the
 // 50 us it costs do not show, and the records stay near 2 GB).  q.rec stays
 // null where the one-kernel form is taken: recorded solves (a graph cannot
@@ -836,7 +837,7 @@ int split_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, bool use_graph, uint6
 {
     q = PeelArgs{};
     if (use_graph || sl.arena || sl.stream_ordered || T >= kNoRecord) return MCRT_OK;
-    uint64_t recs = std::min<uint64_t>(std::max<uint64_t>(8 * T, 1ull << 19), 1ull << 24);
+    uint64_t recs = std::min<uint64_t>(std::max<uint64_t>(16 * T, 1ull << 19), 1ull << 24);
     const size_t lanes = (size_t)blocks * 256;
     // a wave's chunk: an eighth of its share, so that few slots stay empty
     const uint64_t chunk = std::min<uint64_t>(std::max<uint64_t>(recs * 64 / (lanes * 8), 16), 256);
