@@ -1469,8 +1469,8 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
         while (batch > kGroupChunk && carve_batch(b, batch, nullptr) > limit / 2) batch = chunked(batch / 2);
     }
     size_t held = 0;
-    // a batch's arrays: of fewer groups where they do not fit, and never at the
-    // cost of an optional form's (which are given back first)
+    // a batch's arrays: of fewer groups where they do not fit, even once the
+    // scratch that the slot's other solves keep for themselves is given back
     auto hold = [&]() -> int {
         for (;; batch = chunked(batch / 2)) {
             held = carve_batch(q, batch, nullptr);

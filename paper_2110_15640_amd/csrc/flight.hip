@@ -54,7 +54,7 @@ struct FlightLDS {
     uint32_t ijk[kTPB];   // event cell: i | j << 11 | k << 21
     uint32_t st[kTPB];    // forced state:4 | birth:1 | smode:1 | 3 unused | capped:1 | lost:1 | surface:1 | solve:20
     uint32_t e[kTPB];
-    uint32_t last[kTPB];  // the packet's last record of this round
+    uint32_t last[kTPB];  // the packet's last record since the kernels were last launched
     int nint[kTPB];
 };
 
