@@ -212,10 +212,28 @@ __device__ __forceinline__ void start_flight(FLane& L, const GridDev& g, const B
     L.mode = kind;
 }
 
-template <bool MIXED, bool MULTI, bool EXT, int GEO>
-__global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g1, BatchArgs A, PeelArgs Q)
+// LF (here and for the rays): the face table of the launch's one grid lies in LDS
+// (up to kLdsFaces entries), so that a step waits for no load but the last one's
+// extinction.
+constexpr int kLdsFaces = 1024;
+template <bool LF>
+__device__ __forceinline__ GridDev lds_grid(const GridDev& g1, double2* faces)
+{
+    GridDev g = g1;
+    if constexpr (LF) {
+        for (int e = threadIdx.x; e <= g1.lon_base + g1.nlon; e += kTPB) faces[e] = g1.faces[e];
+        __syncthreads();
+        g.faces = faces;
+    }
+    return g;
+}
+
+template <bool MIXED, bool MULTI, bool EXT, int GEO, bool LF>
+__global__ void __launch_bounds__(kTPB, 4) k_flight(GridDev g0, BatchArgs A, PeelArgs Q)
 {
     __shared__ FlightLDS cold;
+    extern __shared__ double2 faces[];
+    const GridDev g1 = lds_grid<LF>(g0, faces);
     int lgrid = 0;
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -400,14 +418,13 @@ enum { P_IDLE = 0, P_WALK = 1, P_ANGLE = 2, P_DONE = 3 };
 // about two steps.  8: 50.5 ms, 16: 46.1, 24: 45.9, 32: 47.3 (25 x 8 x 1e5 emission packets, mixed)
 constexpr int kPeelThreshold = 24, kAngleThreshold = 16, kShellSteps = 3;
 
-template <bool MIXED, bool MULTI, int GEO>
-__global__ void __launch_bounds__(kTPB, MULTI ? 4 : 5) k_peel(GridDev g1, BatchArgs A, PeelArgs Q)
+template <bool MIXED, bool MULTI, int GEO, bool LF>
+__global__ void __launch_bounds__(kTPB, MULTI ? 4 : 5) k_peel(GridDev g0, BatchArgs A, PeelArgs Q)
 {
     __shared__ double sobs[2 * 3 * kMaxObs];
-    extern __shared__ double radii[];  // the grid's (of one grid): a shell step then waits for no load but the last one's
+    extern __shared__ double2 faces[];
     if (threadIdx.x < 2 * 3 * kMaxObs) sobs[threadIdx.x] = A.obs[threadIdx.x / (3 * kMaxObs)][threadIdx.x % (3 * kMaxObs)];
-    if (!MULTI)
-        for (int e = threadIdx.x; e <= g1.nlay; e += kTPB) radii[e] = g1.r[e];
+    const GridDev g1 = lds_grid<LF>(g0, faces);
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -459,7 +476,7 @@ __global__ void __launch_bounds__(kTPB, MULTI ? 4 : 5) k_peel(GridDev g1, BatchA
                     cell += out ? ncol : -ncol;
                     const bool inside = (unsigned)w.k < (unsigned)g.nlay;
                     const double a = (double)ae;
-                    const double R = MULTI ? wk_edge(g, inside ? w.k : 0, out) : radii[inside ? w.k + (out ? 1 : 0) : 0];
+                    const double R = wk_edge(g, inside ? w.k : 0, out);
                     ae = (Prop<MIXED>)ld<MIXED>(aext, inside ? cell : 0);
                     if (through(w.ts, a, inside)) {
                         if constexpr (GEO == GEO_SLAB) {
@@ -664,22 +681,31 @@ void launch_flight(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool
                      a.absorption == 1;
     // (slabs come without a grid table)
     const int geo = multi ? GEO_SPHERE : g.geom;
-#define MCRT_K(MX, MU, EX, GE) hipLaunchKernelGGL((k_flight<MX, MU, EX, GE>), dim3(blocks), dim3(kTPB), 0, stream, g, a, q)
-#define MCRT_KX(MX, MU, GE)                \
-    do {                                   \
-        if (ext) MCRT_K(MX, MU, true, GE); \
-        else MCRT_K(MX, MU, false, GE);    \
+    const bool lf = !multi && g.lon_base + g.nlon < kLdsFaces;
+    const size_t lds = lf ? sizeof(double2) * (g.lon_base + g.nlon + 1) : 0;
+#define MCRT_K(MX, MU, EX, GE, LF) \
+    hipLaunchKernelGGL((k_flight<MX, MU, EX, GE, LF>), dim3(blocks), dim3(kTPB), lds, stream, g, a, q)
+#define MCRT_KX(MX, MU, GE, LF)                \
+    do {                                       \
+        if (ext) MCRT_K(MX, MU, true, GE, LF); \
+        else MCRT_K(MX, MU, false, GE, LF);    \
+    } while (0)
+#define MCRT_KL(MX, GE)                       \
+    do {                                      \
+        if (lf) MCRT_KX(MX, false, GE, true); \
+        else MCRT_KX(MX, false, GE, false);   \
     } while (0)
     if (geo == GEO_SLAB) {
-        if (mixed) MCRT_KX(true, false, GEO_SLAB);
-        else MCRT_KX(false, false, GEO_SLAB);
+        if (mixed) MCRT_KL(true, GEO_SLAB);
+        else MCRT_KL(false, GEO_SLAB);
     } else if (multi) {
-        if (mixed) MCRT_KX(true, true, GEO_SPHERE);
-        else MCRT_KX(false, true, GEO_SPHERE);
+        if (mixed) MCRT_KX(true, true, GEO_SPHERE, false);
+        else MCRT_KX(false, true, GEO_SPHERE, false);
     } else {
-        if (mixed) MCRT_KX(true, false, GEO_SPHERE);
-        else MCRT_KX(false, false, GEO_SPHERE);
+        if (mixed) MCRT_KL(true, GEO_SPHERE);
+        else MCRT_KL(false, GEO_SPHERE);
     }
+#undef MCRT_KL
 #undef MCRT_KX
 #undef MCRT_K
 }
@@ -687,19 +713,26 @@ void launch_flight(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool
 void launch_peel(const GridDev& g, const BatchArgs& a, const PeelArgs& q, bool mixed, bool multi, int blocks,
                  hipStream_t stream)
 {
-    const size_t lds = multi ? 0 : sizeof(double) * (g.nlay + 1);
+    const bool lf = !multi && g.lon_base + g.nlon < kLdsFaces;
+    const size_t lds = lf ? sizeof(double2) * (g.lon_base + g.nlon + 1) : 0;
     const int geo = multi ? GEO_SPHERE : g.geom;
-#define MCRT_K(MX, MU, GE) hipLaunchKernelGGL((k_peel<MX, MU, GE>), dim3(blocks), dim3(kTPB), lds, stream, g, a, q)
+#define MCRT_K(MX, MU, GE, LF) hipLaunchKernelGGL((k_peel<MX, MU, GE, LF>), dim3(blocks), dim3(kTPB), lds, stream, g, a, q)
+#define MCRT_KL(MX, GE)                      \
+    do {                                     \
+        if (lf) MCRT_K(MX, false, GE, true); \
+        else MCRT_K(MX, false, GE, false);   \
+    } while (0)
     if (geo == GEO_SLAB) {
-        if (mixed) MCRT_K(true, false, GEO_SLAB);
-        else MCRT_K(false, false, GEO_SLAB);
+        if (mixed) MCRT_KL(true, GEO_SLAB);
+        else MCRT_KL(false, GEO_SLAB);
     } else if (multi) {
-        if (mixed) MCRT_K(true, true, GEO_SPHERE);
-        else MCRT_K(false, true, GEO_SPHERE);
+        if (mixed) MCRT_K(true, true, GEO_SPHERE, false);
+        else MCRT_K(false, true, GEO_SPHERE, false);
     } else {
-        if (mixed) MCRT_K(true, false, GEO_SPHERE);
-        else MCRT_K(false, false, GEO_SPHERE);
+        if (mixed) MCRT_KL(true, GEO_SPHERE);
+        else MCRT_KL(false, GEO_SPHERE);
     }
+#undef MCRT_KL
 #undef MCRT_K
 }
 
