@@ -427,7 +427,11 @@ __host__ __device__ __forceinline__ ConePick wk_cone_pick(const Walker& w, doubl
     const double M = fma(Pz, Pz, (q2 * w.dz) * w.dz);
     const double sf = up ? su : sl, sb = up ? sl : su;  // the edges in front and behind
     const double mz = wk_flip(w.dz, dj);
-    const bool turn = wk_flip(Pz, dj) > 0.0;  // the extremum is ahead
+    // the extremum is ahead.  |Pz| <= |P|; of a line through the centre both are
+    // noise and q2 may come out negative: no extremum then (and no pole is
+    // picked: Pz^2 + q2 (dz^2 - 4) < 0)
+    const bool off = fma(Pz, Pz, -(q2 + q2)) <= 0.0, toward = wk_flip(Pz, dj) > 0.0;
+    const bool turn = off & toward;
     const double reach = turn ? fma(-(sf * sf), q2, M) : mz - wk_flip(sf, dj);
     const bool front = reach > 0.0;
     const bool back = !front & turn & (mz < wk_flip(sb, dj));
