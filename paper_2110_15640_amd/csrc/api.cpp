@@ -288,14 +288,21 @@ int slot_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const char* name, size
     return MCRT_OK;
 }
 
+// Bytes of the slot's spare scratch.
+uint64_t spare_bytes(const Slot& sl)
+{
+    uint64_t n = 0;
+    for (const auto& kv : sl.spare) n += kv.second.bytes;
+    return n;
+}
+
 // What the budget leaves a blocking slot.  Its own scratch is regrown in place
 // (each buffer freed before its larger successor is allocated), so it counts as
 // room: repeated calls then plan the same launches as the first.
 uint64_t slot_room(mcrt_ctx* ctx, const Slot& sl)
 {
-    uint64_t own = 0;
+    uint64_t own = spare_bytes(sl);
     for (const auto& kv : sl.scratch) own += kv.second.bytes;
-    for (const auto& kv : sl.spare) own += kv.second.bytes;
     std::lock_guard<std::mutex> mk(ctx->mem_mu);
     const uint64_t held = held_locked(ctx);
     return ctx->budget - std::min(ctx->budget, held - std::min(held, own));
@@ -309,13 +316,13 @@ struct Want {
 int spare_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, const Want* want, int n, void** p, bool& there)
 {
     there = false;
-    uint64_t more = 0, all = 0, spare = 0;
+    uint64_t more = 0, all = 0;
     for (int i = 0; i < n; ++i) {
         const size_t have = sl.spare[want[i].name].bytes;
         if (want[i].bytes > have) more += want[i].bytes - have;
         all += want[i].bytes;
     }
-    for (const auto& kv : sl.spare) spare += kv.second.bytes;
+    const uint64_t spare = spare_bytes(sl);
     bool fits, fits_alone;  // beside the spare scratch that is held; in its place
     {
         std::lock_guard<std::mutex> mk(ctx->mem_mu);
@@ -1475,7 +1482,7 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
         for (;; batch = chunked(batch / 2)) {
             held = carve_batch(q, batch, nullptr);
             int rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
-            if (no_room(rc) && !sl.spare.empty()) {
+            if (no_room(rc) && spare_bytes(sl) > 0) {
                 HIPTRY(hipStreamSynchronize(st));
                 release_spare(ctx, sl);
                 rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
@@ -1522,8 +1529,10 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
         const size_t need = carve_rows(nullptr);
         const bool small = q.n_group <= kGroupChunk;
         int rc = !small && held + need > limit ? MCRT_EBUDGET : slot_scratch(ctx, sl, st, "chord_rows", need, &v, true);
-        if (no_room(rc) && !small) {
-            batch = chunked(q.n_group / 2);
+        // fewer groups, or, where that is the least, once the scratch that earlier
+        // solves of the slot kept is given back
+        if (no_room(rc) && (!small || spare_bytes(sl) > held)) {
+            if (!small) batch = chunked(q.n_group / 2);
             HIPTRY(hipStreamSynchronize(st));
             release_spare(ctx, sl);
             if ((rc = hold())) return rc;
