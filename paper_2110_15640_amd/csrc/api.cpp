@@ -1399,10 +1399,13 @@ uint64_t chord_estimate(const GridRes* g, int n_b, int n_alpha, int nrow)
 // up to 64 spectral rows the crossed cells' extinction, the groups' optical
 // depths and their tallies.  Fills hs (two sums per row) and the result's
 // timing and number of segments.  A tally is summed in chunks of kGroupChunk
-// groups, and batches are whole chunks, so results do not depend on how many
-// there are: all groups at once where the scratch for it fits (in a quarter of
-// what the budget leaves, or in what a served request was admitted with), else
-// as few batches as do.
+// groups, whatever the batches, so results do not depend on how many there are:
+// all groups at once where the scratch for it fits (in a quarter of what the
+// budget leaves, or in what a served request was admitted with), else as few
+// batches of whole chunks as do.  What does not fit even so is done with less:
+// the blocks of rows in parts, each with the geometry anew, where the tallies'
+// chunks take too much (one per 64 groups and block), and batches of less than
+// a chunk, down to a wave's four groups.
 template <typename R>
 int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op, const SolvePlan& pl, const mcrt_solve_params* p,
                std::vector<double>& hs, mcrt_result* res)
@@ -1425,6 +1428,9 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
     const int n_chunk = (q.n_total + kGroupChunk - 1) / kGroupChunk;
     int* specs;
     double *part, *chunks, *sums, *ck_tab, *ck_ray;
+    int part_blk = nblk;                                                  // blocks of rows of a part
+    int batch = n_chunk > 1 ? n_chunk * kGroupChunk : q.n_total;         // groups of a batch, at most
+    const int chunk = std::min(kGroupChunk, q.n_total);
     // arrays one after another in one allocation at base; their bytes
     auto taker = [](char* base, size_t& at) {
         return [base, &at](auto*& x, size_t n) {
@@ -1436,16 +1442,16 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
         size_t at = 0;
         auto take = taker(base, at);
         take(specs, (size_t)ns);
-        take(chunks, 256 * (size_t)n_chunk * nblk);
+        take(chunks, 256 * (size_t)n_chunk * part_blk);
         take(sums, 2 * (size_t)nrow);
-        take(ck_tab, hires ? 0 : 64 * (size_t)nblk * ntp);
-        take(ck_ray, hires ? 0 : 64 * (size_t)nblk);
+        take(ck_tab, hires ? 0 : 64 * (size_t)part_blk * ntp);
+        take(ck_ray, hires ? 0 : 64 * (size_t)part_blk);
         return at;
     };
-    auto carve_batch = [&](ChordDev& b, int n, char* base) {
+    auto carve_batch = [&](ChordDev& b, char* base) {
         size_t at = 0;
         auto take = taker(base, at);
-        chord_batch(b, 0, n);
+        chord_batch(b, 0, batch);
         const size_t slots = (size_t)b.n_wave * 64, segs = slots * b.cap;
         R* len;
         take(b.seg_cell, segs);
@@ -1457,41 +1463,57 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
         take(b.chord_ok, slots);
         take(b.touched, 16 * (size_t)b.n_flag_words);
         take(b.comp, 16 * (size_t)b.n_flag_words);
-        take(b.group_n, (size_t)n);
-        take(b.group_at, (size_t)n);
+        take(b.group_n, (size_t)batch);
+        take(b.group_at, (size_t)batch);
         take(b.bsum, 3 * (size_t)chord_scan_blocks(b));
         take(b.totals, 4);
-        take(part, 2 * (size_t)stride * n * nbuf);
+        // (batches of less than a chunk keep all of its groups' sums, of every block)
+        take(part, 2 * (size_t)stride * (batch >= chunk ? (size_t)batch * nbuf : (size_t)chunk * part_blk));
         return at;
     };
     auto chunked = [](int n) { return std::max(1, n / kGroupChunk) * kGroupChunk; };
     auto no_room = [](int rc) { return rc == MCRT_EBUDGET || rc == MCRT_ENOMEM; };
+    // the next smaller plan; false: there is none
+    constexpr int kGroupLeast = 4, kPartLess = 8;
+    auto smaller = [&] {
+        if (batch > kGroupChunk) batch = chunked(batch / 2);
+        else if (batch > kGroupLeast) batch = std::max(kGroupLeast, (batch / 2 + 3) & ~3);
+        else if (part_blk > 1) part_blk = 1;
+        else return false;
+        if (batch < chunk) part_blk = std::min(part_blk, kPartLess);
+        return true;
+    };
     const uint64_t limit = sl.stream_ordered ? chord_estimate(g, p->n_b, p->n_alpha, nrow) : slot_room(ctx, sl) / 4;
     void* v;
-    if (int rc = slot_scratch(ctx, sl, st, "chord_sums", carve_all(nullptr), &v)) return rc;
-    carve_all((char*)v);
-    int batch = n_chunk * kGroupChunk;
+    int rc;
+    while (part_blk > 1 && carve_all(nullptr) > limit / 8) part_blk = (part_blk + 1) / 2;
+    for (;; part_blk = (part_blk + 1) / 2) {
+        rc = slot_scratch(ctx, sl, st, "chord_sums", carve_all(nullptr), &v);
+        if (!no_room(rc) || part_blk == 1) break;
+    }
+    if (rc) return rc;
+    const size_t fixed = carve_all((char*)v);
     {
         ChordDev b = q;
-        while (batch > kGroupChunk && carve_batch(b, batch, nullptr) > limit / 2) batch = chunked(batch / 2);
+        while (batch > kGroupChunk && carve_batch(b, nullptr) > limit / 2) smaller();
     }
     size_t held = 0;
     // a batch's arrays: of fewer groups where they do not fit, even once the
     // scratch that the slot's other solves keep for themselves is given back
     auto hold = [&]() -> int {
-        for (;; batch = chunked(batch / 2)) {
-            held = carve_batch(q, batch, nullptr);
+        for (;;) {
+            held = carve_batch(q, nullptr);
             int rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
             if (no_room(rc) && spare_bytes(sl) > 0) {
                 HIPTRY(hipStreamSynchronize(st));
                 release_spare(ctx, sl);
                 rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
             }
-            if (rc == MCRT_OK) carve_batch(q, batch, (char*)v);
-            if (!no_room(rc) || batch == kGroupChunk) return rc;
+            if (rc == MCRT_OK) carve_batch(q, (char*)v);
+            if (!no_room(rc) || !smaller()) return rc;
         }
     };
-    if (int rc = hold()) return rc;
+    if ((rc = hold())) return rc;
     sl.spare_busy = true;
     const LimbDark ld{p->ld_law, p->ld_c1, p->ld_c2, p->transit_y, p->transit_z, p->r_star};
     const bool prof = p->profile != 0;
@@ -1499,87 +1521,126 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
     res->n_segments = 0;
     HIPTRY(hipEventRecord(sl.ev0, st));
     HIPTRY(hipMemcpyAsync(specs, pl.specs.data(), sizeof(int) * ns, hipMemcpyHostToDevice, st));
-    if (!hires) launch_ck_rows(op->lnk, op->ng, ntp, specs, ng, nrow, op->k_ray_dev, ck_tab, ck_ray, st);
-    for (int g0 = 0; g0 < q.n_total;) {
-        chord_batch(q, g0, std::min(batch, q.n_total - g0));
-        launch_chord_geometry<R>(g->dev, p->n_b, p->n_alpha, p->seed, 0, q, ld, st);
-        unsigned long long tot[4];
-        HIPTRY(hipMemcpyAsync(tot, q.totals, sizeof tot, hipMemcpyDeviceToHost, st));
+    int blk0 = 0, g0 = 0;         // the part's first block, the batch's first group
+    int begun = part_blk;         // the part's blocks when it was begun
+    int64_t segs = 0;             // of the chunk that is not complete
+    bool whole = false;           // the arrays hold all groups
+    size_t rows = 0, cells = 0, alpha_n = 0;
+    void* v_cells = nullptr;
+    R *alpha = nullptr, *len = nullptr;
+    CellRow<double>* cr = nullptr;
+    // after a change of plan: the chunk's arrays anew, or the part's
+    auto again = [&]() -> int {
         HIPTRY(hipStreamSynchronize(st));
-        if (tot[3] != 0) {  // more steps than a line's crossings: rounding at an edge
-            q.cap = std::min(2 * q.cap, q.cap_max);
-            if (int rc = hold()) return rc;
-            continue;
-        }
-        const size_t rows = (size_t)tot[0], cells = (size_t)tot[1], alpha_n = cells * stride;
-        void* v_cells;
-        R *alpha, *len;
-        CellRow<double>* cr;
-        auto carve_rows = [&](char* base) {
-            size_t at = 0;
-            auto take = taker(base, at);
-            take(q.row_cell, rows);
-            take(len, 16 * rows);
-            take(alpha, alpha_n * nbuf);
-            take(cr, cells);  // (CellRow<float> is the smaller)
-            q.row_len = len;
-            v_cells = cr;
-            return at;
-        };
-        const size_t need = carve_rows(nullptr);
-        const bool small = q.n_group <= kGroupChunk;
-        int rc = !small && held + need > limit ? MCRT_EBUDGET : slot_scratch(ctx, sl, st, "chord_rows", need, &v, true);
-        // fewer groups, or, where that is the least, once the scratch that earlier
-        // solves of the slot kept is given back
-        if (no_room(rc) && (!small || spare_bytes(sl) > held)) {
-            if (!small) batch = chunked(q.n_group / 2);
+        if (int rc = hold()) return rc;
+        g0 = part_blk == begun ? g0 - g0 % kGroupChunk : 0;
+        if (g0 == 0 && blk0 == 0) res->n_segments = 0;
+        begun = part_blk;
+        segs = 0;
+        return MCRT_OK;
+    };
+    while (blk0 < nblk) {
+        const int n_blk = std::min(part_blk, nblk - blk0), first = 64 * blk0, n_row = std::min(nrow - first, 64 * n_blk);
+        if (g0 == 0 && !hires)
+            launch_ck_rows(op->lnk, op->ng, ntp, specs, ng, first, n_row, op->k_ray_dev, ck_tab, ck_ray, st);
+        if (!whole) {
+            const int most = batch >= chunk ? batch : std::min(batch, kGroupChunk - g0 % kGroupChunk);
+            chord_batch(q, g0, std::min(most, q.n_total - g0));
+            launch_chord_geometry<R>(g->dev, p->n_b, p->n_alpha, p->seed, 0, q, ld, st);
+            unsigned long long tot[4];
+            HIPTRY(hipMemcpyAsync(tot, q.totals, sizeof tot, hipMemcpyDeviceToHost, st));
             HIPTRY(hipStreamSynchronize(st));
-            release_spare(ctx, sl);
-            if ((rc = hold())) return rc;
-            continue;
+            if (tot[3] != 0) {  // more steps than a line's crossings: rounding at an edge
+                q.cap = std::min(2 * q.cap, q.cap_max);
+                if ((rc = again())) return rc;
+                continue;
+            }
+            rows = (size_t)tot[0];
+            cells = (size_t)tot[1];
+            alpha_n = cells * stride;
+            auto carve_rows = [&](char* base) {
+                size_t at = 0;
+                auto take = taker(base, at);
+                take(q.row_cell, rows);
+                take(len, 16 * rows);
+                take(alpha, alpha_n * nbuf);
+                take(cr, cells);  // (CellRow<float> is the smaller)
+                q.row_len = len;
+                v_cells = cr;
+                return at;
+            };
+            const size_t need = carve_rows(nullptr);
+            rc = batch > kGroupChunk && fixed + held + need > limit ? MCRT_EBUDGET
+                                                                    : slot_scratch(ctx, sl, st, "chord_rows", need, &v, true);
+            if (no_room(rc)) {  // less, or, where there is no less, without the scratch that earlier solves kept
+                const bool kept = spare_bytes(sl) > held;
+                if (kept) {
+                    HIPTRY(hipStreamSynchronize(st));
+                    release_spare(ctx, sl);
+                }
+                if ((batch > kGroupChunk || !kept) && !smaller()) return rc;
+                if ((rc = again())) return rc;
+                continue;
+            }
+            if (rc) return rc;
+            carve_rows((char*)v);
+            if (single)
+                launch_cell_rows(g->dev, ncell, q, hires, op->nT, op->nP, op->T_grid, op->lnP_grid, op->dlnlam,
+                                 (CellRow<float>*)v_cells, st);
+            else
+                launch_cell_rows(g->dev, ncell, q, hires, op->nT, op->nP, op->T_grid, op->lnP_grid, op->dlnlam, cr, st);
+            launch_chord_rows<R>(q, st);
+            segs += (int64_t)tot[2];
+            whole = q.n_group == q.n_total;
         }
-        if (rc) return rc;
-        carve_rows((char*)v);
-        if (single)
-            launch_cell_rows(g->dev, ncell, q, hires, op->nT, op->nP, op->T_grid, op->lnP_grid, op->dlnlam,
-                             (CellRow<float>*)v_cells, st);
-        else
-            launch_cell_rows(g->dev, ncell, q, hires, op->nT, op->nP, op->T_grid, op->lnP_grid, op->dlnlam, cr, st);
-        launch_chord_rows<R>(q, st);
+        const int done = g0 + q.n_group;
+        const bool ends = done % kGroupChunk == 0 || done == q.n_total;  // the batch completes a chunk
         hipStream_t st2 = nbuf == 2 ? sl.stream2 : st;
         if (nbuf == 2) {
             HIPTRY(hipEventRecord(sl.fork, st));
             HIPTRY(hipStreamWaitEvent(st2, sl.fork, 0));
         }
-        if (prof && (rc = prof_events(ctx, sl, n_prof + nblk))) return rc;
-        for (int blk = 0; blk < nblk; ++blk, ++n_prof) {
-            const int r0 = 64 * blk, nslot = std::min(64, nrow - r0), b = blk % nbuf;
+        if (prof && (rc = prof_events(ctx, sl, n_prof + n_blk))) return rc;
+        for (int blk = 0; blk < n_blk; ++blk, ++n_prof) {
+            const int r0 = first + 64 * blk, nslot = std::min(64, nrow - r0), b = blk % nbuf;
             hipStream_t sb = b ? st2 : st;
             R* al = alpha + alpha_n * b;
             if (!hires)
-                launch_row_alpha<R, double>(cr, (int)cells, false, ck_tab + (size_t)r0 * ntp, 0, ck_ray + r0, nullptr, nslot, al,
-                                            sb);
+                launch_row_alpha<R, double>(cr, (int)cells, false, ck_tab + (size_t)64 * blk * ntp, 0, ck_ray + 64 * blk, nullptr,
+                                            nslot, al, sb);
             else if constexpr (sizeof(R) == sizeof(float))
                 launch_row_alpha<R, float>((CellRow<float>*)v_cells, (int)cells, true, op->lnk_f32, op->nspec, op->k_ray_dev,
                                            specs + r0, nslot, al, sb);
             else
                 launch_row_alpha<R, double>(cr, (int)cells, true, op->lnk, op->nspec, op->k_ray_dev, specs + r0, nslot, al, sb);
+            double* sum = part + 2 * (size_t)stride * (batch >= chunk ? (size_t)batch * b : (size_t)chunk * blk);
             if (prof) (void)hipEventRecord(sl.prof_ev[2 * n_prof], sb);
-            launch_group_tau<R>(q, al, nslot, part + 2 * (size_t)stride * batch * b, chunks + 256 * (size_t)n_chunk * blk, sb);
+            launch_group_tau<R>(q, al, nslot, sum + 2 * (size_t)chord_stride(nslot) * (g0 % kGroupChunk), sb);
+            if (ends)
+                launch_group_sums(sum, g0 % kGroupChunk + q.n_group, nslot,
+                                  chunks + 256 * ((size_t)n_chunk * blk + g0 / kGroupChunk), sb);
             if (prof) (void)hipEventRecord(sl.prof_ev[2 * n_prof + 1], sb);
         }
         if (nbuf == 2) {  // the first stream waits for the second's last block
             HIPTRY(hipEventRecord(sl.join, st2));
             HIPTRY(hipStreamWaitEvent(st, sl.join, 0));
         }
-        res->n_segments += (int64_t)tot[2];
-        g0 += q.n_group;
+        g0 = done;
+        if (ends) {
+            if (blk0 == 0) res->n_segments += segs;
+            segs = 0;
+        }
+        if (g0 == q.n_total) {
+            launch_group_final(chunks, n_chunk, n_row, sums + 2 * (size_t)first, st);
+            blk0 += n_blk;
+            g0 = 0;
+            begun = part_blk;
+        }
     }
-    launch_group_final(chunks, n_chunk, nrow, sums, st);
     HIPTRY(hipGetLastError());
     hs.resize((size_t)nrow * 2);
     HIPTRY(hipMemcpyAsync(hs.data(), sums, sizeof(double) * hs.size(), hipMemcpyDeviceToHost, st));
-    if (int rc = finish_timing(ctx, sl, st, res)) return rc;
+    if ((rc = finish_timing(ctx, sl, st, res))) return rc;
     return prof ? prof_collect(ctx, sl, n_prof, res) : MCRT_OK;
 }
 

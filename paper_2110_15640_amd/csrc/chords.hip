@@ -344,14 +344,14 @@ __global__ void __launch_bounds__(256) k_cell_rows(GridDev g, int ncell, ChordDe
     out[q.comp[c]] = r;
 }
 
-// The ck tables of the solve's rows, row fastest in blocks of 64: a cell's 64
+// The ck tables of nrow of the solve's rows from row0, row fastest in blocks of 64: a cell's 64
 // values at a corner are then contiguous.
 __global__ void __launch_bounds__(256) k_ck_rows(const double* __restrict__ lnk, int ng_tab, int ntp,
-                                                 const int* __restrict__ specs, int ng, int nrow,
+                                                 const int* __restrict__ specs, int ng, int row0, int nrow,
                                                  const double* __restrict__ k_ray, double* __restrict__ tab,
                                                  double* __restrict__ kray_row)
 {
-    const int s = threadIdx.x & 63, r = min((int)blockIdx.x * 64 + s, nrow - 1);
+    const int s = threadIdx.x & 63, r = row0 + min((int)blockIdx.x * 64 + s, nrow - 1);
     const int spec = specs[r / ng];
     const double* src = lnk + ((size_t)spec * ng_tab + r % ng) * ntp;
     double* dst = tab + (size_t)blockIdx.x * ntp * 64;
@@ -706,11 +706,11 @@ template void launch_cell_rows<double>(const GridDev&, int, const ChordDev&, boo
 template void launch_cell_rows<float>(const GridDev&, int, const ChordDev&, bool, int, int, const double*, const double*,
                                       double, CellRow<float>*, hipStream_t);
 
-void launch_ck_rows(const double* lnk, int ng_tab, int ntp, const int* specs, int ng, int nrow, const double* k_ray, double* tab,
-                    double* kray_row, hipStream_t stream)
+void launch_ck_rows(const double* lnk, int ng_tab, int ntp, const int* specs, int ng, int row0, int nrow, const double* k_ray,
+                    double* tab, double* kray_row, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_ck_rows, dim3(nblk(nrow, 64), std::min(nblk(ntp, 4), 64)), dim3(256), 0, stream, lnk, ng_tab, ntp, specs,
-                       ng, nrow, k_ray, tab, kray_row);
+                       ng, row0, nrow, k_ray, tab, kray_row);
 }
 
 template <typename R, typename W>
@@ -738,7 +738,7 @@ template void launch_row_alpha<float, float>(const CellRow<float>*, int, bool, c
                                              float*, hipStream_t);
 
 template <typename R>
-void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part, double* chunks, hipStream_t stream)
+void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part, hipStream_t stream)
 {
     const int stride = chord_stride(nslot);
     const int nb = std::min(stride / 16, kTauBlocks);
@@ -746,11 +746,15 @@ void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part
     const dim3 grid(nblk(n_blk, kRuns * kXcds) * kRuns * kXcds), block(256);
     if (nb == kTauBlocks) hipLaunchKernelGGL((k_group_tau<R, kTauBlocks>), grid, block, 0, stream, q, alpha, stride, part);
     else hipLaunchKernelGGL((k_group_tau<R, 1>), grid, block, 0, stream, q, alpha, stride, part);
-    hipLaunchKernelGGL(k_group_sums, dim3(nblk(q.n_group, kGroupChunk)), dim3(kSumThreads), 0, stream, part, q.n_group, 2 * stride,
-                       (double2*)chunks + 128 * (size_t)(q.g0 / kGroupChunk));
 }
-template void launch_group_tau<double>(const ChordDev&, const double*, int, double*, double*, hipStream_t);
-template void launch_group_tau<float>(const ChordDev&, const float*, int, double*, double*, hipStream_t);
+template void launch_group_tau<double>(const ChordDev&, const double*, int, double*, hipStream_t);
+template void launch_group_tau<float>(const ChordDev&, const float*, int, double*, hipStream_t);
+
+void launch_group_sums(const double* part, int n_group, int nslot, double* chunks, hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_group_sums, dim3(nblk(n_group, kGroupChunk)), dim3(kSumThreads), 0, stream, part, n_group,
+                       2 * chord_stride(nslot), (double2*)chunks);
+}
 
 void launch_group_final(const double* chunks, int n_chunk, int nrow, double* sums, hipStream_t stream)
 {

@@ -254,13 +254,15 @@ void launch_chord_rows(const ChordDev& q, hipStream_t stream);
 template <typename W>
 void launch_cell_rows(const GridDev& g, int ncell, const ChordDev& q, bool hires, int nT, int nP, const double* T_grid,
                       const double* lnP_grid, double dlnlam, CellRow<W>* out, hipStream_t stream);
-void launch_ck_rows(const double* lnk, int ng_tab, int ntp, const int* specs, int ng, int nrow, const double* k_ray, double* tab,
-                    double* kray_row, hipStream_t stream);
+void launch_ck_rows(const double* lnk, int ng_tab, int ntp, const int* specs, int ng, int row0, int nrow, const double* k_ray,
+                    double* tab, double* kray_row, hipStream_t stream);
 template <typename R, typename W>
 void launch_row_alpha(const CellRow<W>* cells, int n_cells, bool hires, const W* tab, int nlam, const double* k_ray,
                       const int* nlist, int nslot, R* alpha, hipStream_t stream);
 template <typename R>
-void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part, double* chunks, hipStream_t stream);
+void launch_group_tau(const ChordDev& q, const R* alpha, int nslot, double* part, hipStream_t stream);
+// The chunks' sums of the part of n_group groups from a chunk's first one.
+void launch_group_sums(const double* part, int n_group, int nslot, double* chunks, hipStream_t stream);
 void launch_group_final(const double* chunks, int n_chunk, int nrow, double* sums, hipStream_t stream);
 
 }  // namespace mcrt

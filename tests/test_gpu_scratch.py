@@ -41,3 +41,42 @@ def test_chords_after_packets(torch_dev, precision):
             packets(ctx, gid, oid)
             got = ctx.solve_transmission(gid, oid, table, **kw)
         assert np.array_equal(got["sums"], ref["sums"]), extra
+
+
+@pytest.mark.parametrize("kind,shape,nrow,n_b,n_alpha", [
+    ("ck", (32, 16, 20), 12, 1, 1),        # one group
+    ("ck", (32, 16, 20), 12, 7, 31),       # 16 groups, less than a chunk of the tallies
+    ("ck", (32, 16, 20), 12, 32, 32),      # one chunk
+    ("ck", (16, 8, 10), 130, 33, 41),      # two chunks; three blocks of rows on two streams
+    ("hires", (16, 8, 10), 70, 33, 41),
+    ("ck", (128, 64, 40), 2, 32, 32),      # most of it the segments
+])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_chords_in_little_scratch(torch_dev, kind, shape, nrow, n_b, n_alpha, precision):
+    """Raytrace transmission in as much scratch as the extinction of all cells for
+    up to 64 rows (for two streams where there are more) and 12 bytes a segment
+    take, and in less as long as it fits: the same sums bit for bit."""
+    from paper_2110_15640_amd import mcrt as M
+    if kind == "ck":
+        grid, table, _ = I.make_emission_3d(*shape, nband=nrow, ng=1)
+    else:
+        grid, table = I.make_transmission_hires(*shape, nlam=nrow, nT=5, nP=6)
+    kw = dict(n_b=n_b, n_alpha=n_alpha, seed=3, r_star=I.R_SUN, precision=M.MCRT_MIXED if precision == "mixed" else M.MCRT_FP64)
+    with M.Context(0) as ctx:
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        resident = ctx.memory_in_use
+        ref = ctx.solve_transmission(gid, oid, table, **kw)
+    most = shape[0] * shape[1] * shape[2] * min(nrow, 64) * (2 if nrow > 64 else 1) * 8 + 12 * ref["n_segments"] + \
+        24 * n_b * n_alpha + (1 << 16)
+    for q in range(8):
+        extra = int(most * 0.7 ** q)
+        print(f"chords in little scratch: {kind} {shape}, {nrow} rows, {n_b} x {n_alpha}, {precision}, {extra} bytes", flush=True)
+        with M.Context(0, hbm_budget_bytes=resident + extra) as ctx:
+            gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+            try:
+                got = ctx.solve_transmission(gid, oid, table, **kw)
+            except M.McrtError as e:
+                assert e.name == "EBUDGET" and q > 0, (e, extra)
+                break
+            assert ctx.memory_in_use <= resident + extra
+        assert np.array_equal(got["sums"], ref["sums"]) and got["n_segments"] == ref["n_segments"], extra
