@@ -1386,12 +1386,13 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     return MCRT_OK;
 }
 
-// Device bytes that a served transmission request is admitted with.
+// Device bytes that a served transmission request is admitted with: it plans its
+// batches to hold no more.
 uint64_t chord_estimate(const GridRes* g, int n_b, int n_alpha, int nrow)
 {
     const uint64_t nch = (uint64_t)n_b * n_alpha, ncell = (uint64_t)g->ncell, nslot = std::min(64, nrow);
     const uint64_t segs = nch * (2ULL * g->dev.nlay + 2ULL * g->dev.nlat + g->dev.nlon + 8ULL);
-    return nch * 24 + 8 + ncell * nslot * 8 + (nch + 31) / 32 * 2 * nslot * 8 + (uint64_t)nrow * 20 + ncell * 48 + segs * 12 +
+    return nch * 24 + 8 + ncell * nslot * 8 + (nch + 31) / 32 * 2 * nslot * 8 + (uint64_t)nrow * 20 + ncell * 40 + segs * 12 +
            (1ULL << 20);
 }
 
@@ -1401,7 +1402,8 @@ uint64_t chord_estimate(const GridRes* g, int n_b, int n_alpha, int nrow)
 // timing and number of segments.  A tally is summed in chunks of kGroupChunk
 // groups, whatever the batches, so results do not depend on how many there are:
 // all groups at once where the scratch for it fits (in a quarter of what the
-// budget leaves, or in what a served request was admitted with), else as few
+// budget leaves; a served request holds no more than it was admitted with, since
+// its allocations are not checked one by one), else as few
 // batches of whole chunks as do.  What does not fit even so is done with less:
 // the blocks of rows in parts, each with the geometry anew, where the tallies'
 // chunks take too much (one per 64 groups and block), and batches of less than
@@ -1503,6 +1505,7 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
     auto hold = [&]() -> int {
         for (;;) {
             held = carve_batch(q, nullptr);
+            if (sl.stream_ordered && fixed + held > limit && smaller()) continue;
             int rc = slot_scratch(ctx, sl, st, "chords", held, &v, true);
             if (no_room(rc) && spare_bytes(sl) > 0) {
                 HIPTRY(hipStreamSynchronize(st));
@@ -1570,8 +1573,18 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
                 return at;
             };
             const size_t need = carve_rows(nullptr);
-            rc = batch > kGroupChunk && fixed + held + need > limit ? MCRT_EBUDGET
-                                                                    : slot_scratch(ctx, sl, st, "chord_rows", need, &v, true);
+            const bool least = batch <= kGroupLeast && part_blk == 1;
+            if (fixed + held + need > limit && (batch > kGroupChunk || (sl.stream_ordered && !least))) {
+                rc = MCRT_EBUDGET;
+            } else {
+                if (sl.stream_ordered && fixed + held + need > limit) {  // more than admitted: where the budget has it
+                    std::lock_guard<std::mutex> mk(ctx->mem_mu);
+                    if (held_locked(ctx) + (fixed + held + need - limit) > ctx->budget)
+                        return fail(MCRT_EBUDGET, "request needs %zu bytes of scratch; it was admitted with %llu",
+                                    fixed + held + need, (unsigned long long)limit);
+                }
+                rc = slot_scratch(ctx, sl, st, "chord_rows", need, &v, true);
+            }
             if (no_room(rc)) {  // less, or, where there is no less, without the scratch that earlier solves kept
                 const bool kept = spare_bytes(sl) > held;
                 if (kept) {

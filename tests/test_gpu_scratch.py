@@ -80,3 +80,51 @@ def test_chords_in_little_scratch(torch_dev, kind, shape, nrow, n_b, n_alpha, pr
                 break
             assert ctx.memory_in_use <= resident + extra
         assert np.array_equal(got["sums"], ref["sums"]) and got["n_segments"] == ref["n_segments"], extra
+
+
+def _needs(grid, table, **kw):
+    """What a served transmission says it needs, where the budget has nothing left."""
+    from paper_2110_15640_amd import mcrt as M
+    with M.Context(0) as ctx:
+        ctx.upload_grid(grid), ctx.upload_opacity(table)
+        resident = ctx.memory_in_use
+    with M.Context(0, hbm_budget_bytes=resident) as ctx:
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        with pytest.raises(M.McrtError) as e:
+            ctx.submit("transmission", gid, oid, table, **kw)
+    assert e.value.name == "EBUDGET"
+    return resident, int(str(e.value).split("needs ")[1].split()[0])
+
+
+@pytest.mark.parametrize("kind,shape,nrow,n_b,n_alpha", [
+    ("hires", (16, 8, 10), 20000, 64, 80),  # 3 MB of chunk sums if all rows are taken at once
+    ("ck", (32, 16, 20), 12, 100, 90),
+    ("ck", (128, 64, 40), 2, 3, 5),
+])
+def test_served_chords_stay_in_what_they_were_admitted_with(torch_dev, kind, shape, nrow, n_b, n_alpha):
+    print(f"served chords and their scratch: {kind} {shape}, {nrow} rows, {n_b} x {n_alpha}", flush=True)
+    from paper_2110_15640_amd import mcrt as M
+    if kind == "ck":
+        grid, table, _ = I.make_emission_3d(*shape, nband=nrow, ng=1)
+    else:
+        grid, table = I.make_transmission_hires(*shape, nlam=nrow, nT=5, nP=6)
+    kw = dict(n_b=n_b, n_alpha=n_alpha, seed=3, r_star=I.R_SUN)
+    resident, est = _needs(grid, table, **kw)
+    ncell, nch, nslot = int(np.prod(shape)), n_b * n_alpha, min(nrow, 64)
+    # extinction of the cells, their places in the table, the most segments that
+    # chords can have, sums and chunks, 1 MB of small arrays
+    assert est <= ncell * (8 * nslot + 40) + nch * (24 + 12 * (2 * shape[2] + 2 * shape[1] + shape[0] + 8)) + \
+        (nch + 31) // 32 * 16 * nslot + 20 * nrow + (1 << 20) + 8
+    with M.Context(0) as ctx:
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        ref = ctx.solve_transmission(gid, oid, table, **kw)
+    with M.Context(0, hbm_budget_bytes=resident + est) as ctx:
+        ctx.serve_config(1)
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        ticket = ctx.submit("transmission", gid, oid, table, **kw)
+        peak = 0
+        while not ctx.poll(ticket):
+            peak = max(peak, ctx.memory_in_use)
+        got = ctx.wait(ticket)
+    assert peak <= resident + est
+    assert np.array_equal(got["sums"], ref["sums"]) and got["n_segments"] == ref["n_segments"]
