@@ -465,7 +465,9 @@ int mcrt_autotune(mcrt_ctx* ctx, int32_t mode, int32_t grid_id, int32_t opac_id,
  * Worker threads, each with its own HIP stream on a hardware queue of its
  * own (so their launches are not serialised behind each other), admit queued requests in
  * arrival order whenever the context's HBM budget covers the request's
- * device scratch (estimated at submit), so requests run concurrently on the
+ * device scratch (estimated at submit; a raytrace transmission holds more,
+ * and needs fewer passes, where that is at most a quarter of what the budget
+ * has left when it starts), so requests run concurrently on the
  * device while grids and tables stay resident.  A served request reaches
  * the device as persistent launches of at most 2^23 packets, each taking the
  * device's blocks shared among the requests running when it starts, so the

@@ -95,6 +95,7 @@ struct Slot {
     std::map<std::string, DevBuf> spare;
     bool spare_busy = false;
     bool stream_ordered = false;  // serving slots allocate with hipMallocAsync
+    uint64_t admitted = 0;        // bytes that the slot's served request was admitted with
     // Fixed arena (the allocation-free solve): scratch is carved from it in
     // order, from offset 0 at every call, instead of allocated.
     char* arena = nullptr;
@@ -1396,6 +1397,22 @@ uint64_t chord_estimate(const GridRes* g, int n_b, int n_alpha, int nrow)
            (1ULL << 20);
 }
 
+// And where they are a quarter of what the budget has left: those of all groups and rows at once, with two
+// rows per step that a chord can take (of 8 x 2 neighbouring chords of 256 x 360
+// on 128 x 64 x 60 cells half a row; spread chords share fewer).
+uint64_t chord_want(const GridRes* g, const OpacRes* op, int n_b, int n_alpha, int nrow)
+{
+    ChordDev q;
+    chord_shape(q, g->dev, g->ncell, n_b, n_alpha);
+    const uint64_t groups = q.n_total, slots = (uint64_t)q.n_wave * 64, ncell = (uint64_t)g->ncell;
+    const uint64_t chunks = (groups + kGroupChunk - 1) / kGroupChunk, blocks = ((uint64_t)nrow + 63) / 64;
+    const uint64_t stride = chord_stride(std::min(nrow, 64));
+    const uint64_t rows = groups * 2 * std::min<uint64_t>(q.cap, ncell);
+    const uint64_t tables = op->kind == MCRT_OPAC_HIRES ? 0 : blocks * 64 * 8 * ((uint64_t)op->nT * op->nP + 1);
+    return slots * (16 * (uint64_t)q.cap + 16) + groups * (8 + 16 * stride) + rows * (16 * 8 + 4) +
+           ncell * (8 * stride + sizeof(CellRow<double>) + 8) + chunks * blocks * 2048 + tables + (uint64_t)nrow * 24 + (1ULL << 20);
+}
+
 // Transmission: in batches of groups of chords, the geometry, then per block of
 // up to 64 spectral rows the crossed cells' extinction, the groups' optical
 // depths and their tallies.  Fills hs (two sums per row) and the result's
@@ -1485,7 +1502,7 @@ int chord_sums(mcrt_ctx* ctx, Slot& sl, hipStream_t st, GridRes* g, OpacRes* op,
         if (batch < chunk) part_blk = std::min(part_blk, kPartLess);
         return true;
     };
-    const uint64_t limit = sl.stream_ordered ? chord_estimate(g, p->n_b, p->n_alpha, nrow) : slot_room(ctx, sl) / 4;
+    const uint64_t limit = sl.stream_ordered ? sl.admitted : slot_room(ctx, sl) / 4;
     void* v;
     int rc;
     while (part_blk > 1 && carve_all(nullptr) > limit / 8) part_blk = (part_blk + 1) / 2;
@@ -2142,7 +2159,8 @@ struct Request {
     int rc = MCRT_OK;
     std::string err;
     int ns = 0, ng = 1, no = 1;
-    uint64_t est = 0;
+    uint64_t est = 0;   // bytes it is admitted with, at least
+    uint64_t want = 0;  // and where the budget has plenty
     std::vector<double> value, se, per_g, sums, counters, l_tot;
     double elapsed_ms = 0.0, kernel_ms = 0.0;
     int64_t launches = 0;
@@ -2217,7 +2235,9 @@ void worker_main(mcrt_ctx* ctx, Slot* sl)
                 std::lock_guard<std::mutex> mk(ctx->mem_mu);
                 held = held_locked(ctx);
                 fits = held + r->est <= ctx->budget;
-                if (fits) ctx->reserved += r->est;
+                // (a quarter of what is left, so that others find room beside it)
+                sl->admitted = fits && r->want <= (ctx->budget - held) / 4 ? r->want : r->est;
+                if (fits) ctx->reserved += sl->admitted;
             }
             if (fits || attempt > 0) break;
             lk.unlock();  // the blocking solves' kept scratch gives way, if no blocking solve runs
@@ -2255,7 +2275,7 @@ void worker_main(mcrt_ctx* ctx, Slot* sl)
         lk.lock();
         {
             std::lock_guard<std::mutex> mk(ctx->mem_mu);
-            ctx->reserved -= r->est;
+            ctx->reserved -= sl->admitted;
         }
         r->rc = rc;
         r->err = err;
@@ -2335,7 +2355,9 @@ int submit(mcrt_ctx* ctx, int mode, int32_t gid, int32_t oid, const mcrt_solve_p
     r->sums.assign(ng * r->no * 2, 0.0);
     r->counters.assign(ng * kNCounters, 0.0);
     r->l_tot.assign(ng, 0.0);
-    r->est = estimate_bytes(ctx, *r, ls.g, ls.op);
+    r->est = r->want = estimate_bytes(ctx, *r, ls.g, ls.op);
+    if (mode == MCRT_MODE_TRANSMISSION && !p->ms_transmission)
+        r->want = std::max(r->est, chord_want(ls.g, ls.op, p->n_b, p->n_alpha, r->ns * r->ng));
     bool crowded;
     {
         std::lock_guard<std::mutex> mk(ctx->mem_mu);

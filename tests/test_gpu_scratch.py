@@ -128,3 +128,26 @@ def test_served_chords_stay_in_what_they_were_admitted_with(torch_dev, kind, sha
         got = ctx.wait(ticket)
     assert peak <= resident + est
     assert np.array_equal(got["sums"], ref["sums"]) and got["n_segments"] == ref["n_segments"]
+
+
+def test_served_chords_take_one_batch_where_there_is_room(torch_dev):
+    """Launches of the optical depths of a served transmission: with the whole
+    device for it one per block of 64 rows, as in a blocking solve; admitted with
+    no more than it must have, more, and the same sums."""
+    print("served chords in one batch", flush=True)
+    from paper_2110_15640_amd import mcrt as M
+    grid, table = I.make_transmission_hires(16, 8, 10, nlam=20000, nT=5, nP=6)
+    kw = dict(n_b=64, n_alpha=80, seed=3, r_star=I.R_SUN, profile=1)
+    resident, est = _needs(grid, table, **kw)
+    res = []
+    for budget in (0, resident + est):
+        with M.Context(0, hbm_budget_bytes=budget) as ctx:
+            ctx.serve_config(1)
+            gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+            res.append(ctx.wait(ctx.submit("transmission", gid, oid, table, **kw)))
+            if budget == 0:
+                res.append(ctx.solve_transmission(gid, oid, table, **kw))
+    served, blocking, tight = res
+    assert served["kernel_launches"] == blocking["kernel_launches"] == 313
+    assert tight["kernel_launches"] > 313
+    assert np.array_equal(served["sums"], blocking["sums"]) and np.array_equal(tight["sums"], blocking["sums"])
