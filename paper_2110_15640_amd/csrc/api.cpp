@@ -1787,10 +1787,11 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
             for (int g = 0; g < I.pl.ng; ++g) fl.push_back(Flat{q, (int)s, g, by});
     }
     const int nsolve = (int)fl.size();
-    uint64_t room;
+    uint64_t room;  // (spare scratch gives way)
     {
         std::lock_guard<std::mutex> mk(ctx->mem_mu);
-        room = ctx->budget - std::min(ctx->budget, held_locked(ctx));
+        const uint64_t held = held_locked(ctx), spare = spare_bytes(sl);
+        room = ctx->budget - std::min(ctx->budget, held - std::min(held, spare));
     }
     const uint64_t cap = std::min<uint64_t>(room / 2, 24ULL << 30);
     // launches: consecutive solves while the footprint fits (and <= max_batch)

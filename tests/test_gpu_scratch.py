@@ -151,3 +151,27 @@ def test_served_chords_take_one_batch_where_there_is_room(torch_dev):
     assert served["kernel_launches"] == blocking["kernel_launches"] == 313
     assert tight["kernel_launches"] > 313
     assert np.array_equal(served["sums"], blocking["sums"]) and np.array_equal(tight["sums"], blocking["sums"])
+
+
+def test_batch_launches_do_not_depend_on_kept_records(torch_dev):
+    """A batch that one launch holds in half of the budget's room, in a fresh
+    context and after a solve that kept packet records."""
+    print("batch after packets: launches", flush=True)
+    from paper_2110_15640_amd import mcrt as M
+    grid, table, _ = I.make_emission_3d(16, 8, 10, nband=30, ng=1)
+    args = dict(obs_phase=[0.3, 0.6], seed=1)
+    res = []
+    with M.Context(0) as ctx:
+        ctx.upload_grid(grid), ctx.upload_opacity(table)
+        resident = ctx.memory_in_use
+    for packets_first in (False, True):
+        with M.Context(0, hbm_budget_bytes=resident + (400 << 20)) as ctx:
+            gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+            if packets_first:
+                ctx.solve_emission(gid, oid, table, n_packets=2000, spec_idx=[0, 1], **args)
+                assert ctx.memory_in_use > resident + (50 << 20)
+            item = dict(mode="emission", gid=gid, oid=oid, table=table, n_packets=20000)
+            res.append(ctx.solve_batch([item] * 3, profile=1, **args))  # 90 solves of 2.15 MB
+    assert res[0][0]["kernel_launches"] == res[1][0]["kernel_launches"] == 1
+    for a, b in zip(*res):
+        assert np.array_equal(a["sums"], b["sums"])
