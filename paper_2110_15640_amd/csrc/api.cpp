@@ -836,20 +836,59 @@ int serving_blocks(mcrt_ctx* ctx, int bpc)
 // to 2^24 of them in all (a launch whose events need more repeats its kernels; with
 // eight per packet 20 solves of 5e4 in clouds took a second round: 7.7 ms, 6.4;
 // at 2^24 a round is tens of milliseconds of the whole device, so the
-// 50 us it costs do not show, and the records stay near 2 GB).  q.rec stays
-// null where the one-kernel form is taken: recorded solves (a graph cannot
-// repeat rounds), served requests and the fixed-scratch solve (both planned
-// without this scratch), and budgets it does not fit in.
-int split_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, bool use_graph, uint64_t T, int n_out, bool mixed, int blocks,
-                  PeelArgs& q)
+// 50 us it costs do not show, and the records stay near 2 GB).
+struct SplitShape {
+    uint64_t recs, chunk;
+    size_t lanes;
+};
+SplitShape split_shape(uint64_t T, int blocks)
+{
+    SplitShape s;
+    s.lanes = (size_t)blocks * 256;
+    s.recs = std::min<uint64_t>(std::max<uint64_t>(16 * T, 1ull << 19), 1ull << 24);
+    // a wave's chunk: an eighth of its share, so that few slots stay empty
+    s.chunk = std::min<uint64_t>(std::max<uint64_t>(s.recs * 64 / (s.lanes * 8), 16), 256);
+    s.recs = (s.recs + kXcds * s.chunk - 1) / (kXcds * s.chunk) * (kXcds * s.chunk);
+    return s;
+}
+// Lanes of a wave that carry packets, and blocks, of launches of up to T
+// packets: few packets are spread over all waves.
+int flight_lanes(uint64_t T, int pblocks)
+{
+    return (int)std::max<uint64_t>(1, std::min<uint64_t>(64, T / ((uint64_t)pblocks * 4)));
+}
+int flight_blocks(uint64_t T, int pblocks)
+{
+    const int lanes = flight_lanes(T, pblocks);
+    return (int)std::min<uint64_t>(pblocks, (T + 4 * lanes - 1) / (4 * lanes));
+}
+constexpr size_t kSplitPacketBytes = 2 * sizeof(uint32_t);  // of a packet: its first record, its rays' crossings
+
+// Whether a blocking solve in launches of up to T packets takes the split form:
+// not where it is recorded (a graph cannot repeat rounds), nor for served
+// requests and the fixed-scratch solve (planned without this scratch).  The
+// scratch other than per packet is taken out of the half of the room that the
+// launches are planned by (cap): the other half stays for uploads and served
+// requests while the solve runs; where it is more than half of that, the
+// one-kernel form is taken.
+bool split_fits(const Slot& sl, bool use_graph, uint64_t room, uint64_t T, int n_out, bool mixed, int pblocks, uint64_t& cap)
+{
+    if (use_graph || sl.arena || sl.stream_ordered) return false;
+    const SplitShape s = split_shape(T, flight_blocks(T, pblocks));
+    const uint64_t bytes = (peel_record_bytes(mixed) + sizeof(PeelOut) * n_out + sizeof(uint32_t)) * s.recs +
+                           (sizeof(double) * kParkD + sizeof(uint32_t) * kParkU) * s.lanes + sizeof(uint32_t) * kPeelCtl;
+    if (bytes > room / 4 || bytes > cap) return false;
+    cap -= bytes;
+    return true;
+}
+
+int split_scratch(mcrt_ctx* ctx, Slot& sl, hipStream_t st, uint64_t T, int n_out, bool mixed, int blocks, PeelArgs& q)
 {
     q = PeelArgs{};
-    if (use_graph || sl.arena || sl.stream_ordered || T >= kNoRecord) return MCRT_OK;
-    uint64_t recs = std::min<uint64_t>(std::max<uint64_t>(16 * T, 1ull << 19), 1ull << 24);
-    const size_t lanes = (size_t)blocks * 256;
-    // a wave's chunk: an eighth of its share, so that few slots stay empty
-    const uint64_t chunk = std::min<uint64_t>(std::max<uint64_t>(recs * 64 / (lanes * 8), 16), 256);
-    recs = (recs + kXcds * chunk - 1) / (kXcds * chunk) * (kXcds * chunk);
+    if (T >= kNoRecord) return MCRT_OK;
+    const SplitShape s = split_shape(T, blocks);
+    const uint64_t recs = s.recs, chunk = s.chunk;
+    const size_t lanes = s.lanes;
     const Want want[8] = {{"peel_rec", peel_record_bytes(mixed) * recs},
                           {"peel_out", sizeof(PeelOut) * n_out * recs},
                           {"peel_next", sizeof(uint32_t) * recs},
@@ -968,6 +1007,11 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     const size_t cf_n = p->contrib ? (size_t)ns * no * 2 * ncell : 0;  // [spec][observer][2][cell]
     const int npix = p->image_npix;
     const size_t img_n = (size_t)ns * no * npix * npix;  // [spec][observer][row][column]
+    const int bpc = p->tune_blocks_per_cu > 0 ? p->tune_blocks_per_cu : 4;
+    const int pblocks = ctx->n_cu * bpc;
+    const bool slab = g->dev.geom == 1 && mode == MCRT_MODE_ALBEDO && !p->contrib && !npix && !gs && p->absorption != 1 &&
+                      p->cloud_phase != 2 && p->forced == 0 && !(p->surface_albedo > 0.0);
+    bool split = false;
     int batch;
     if (sl.arena) {
         // the largest batch whose scratch, carved below in this order, fits the arena
@@ -1006,11 +1050,15 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     } else if (sl.stream_ordered) {
         batch = serving_batch(ctx, p->max_batch, nsolve, per_solve, gs ? N / ng + 1 : N);  // as admitted
     } else {
-        batch = p->max_batch > 0 ? p->max_batch : nsolve;
+        batch = p->max_batch > 0 ? std::min(p->max_batch, nsolve) : nsolve;
         const uint64_t room = slot_room(ctx, sl);
         uint64_t cap = room / 2;  // half of what the budget leaves: fewer launches, fewer drain tails
-        int fit = (int)std::max<uint64_t>(1, cap / std::max<size_t>(per_solve, 1));
-        batch = std::max(1, std::min(std::min(batch, fit), nsolve));
+        const uint64_t most = (uint64_t)(gs ? (batch + ng - 1) / ng : batch) * N;
+        split = !slab && split_fits(sl, p->graph != 0, room, most, no, mixed, pblocks, cap);
+        const size_t per = per_solve + (split ? (gs ? N / ng : N) * kSplitPacketBytes : 0);
+        if (per > cap) split = false;
+        int fit = (int)std::max<uint64_t>(1, cap / std::max<size_t>(per, 1));
+        batch = std::max(1, std::min(batch, fit));
     }
     batch = std::min(batch, kMaxSolvesPerLaunch);
     if (gs) batch = std::max(ng, batch / ng * ng);  // whole bands per launch
@@ -1071,17 +1119,13 @@ int solve_packets(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int32_t gid, 
     } else {
         A.peel_w = 1.0;
     }
-    const int bpc = p->tune_blocks_per_cu > 0 ? p->tune_blocks_per_cu : 4;
-    const int pblocks = ctx->n_cu * bpc;
     const uint64_t t_max = (uint64_t)(gs ? batch / ng : batch) * N;  // packets of a launch
     PeelArgs Q{};
-    // a split launch of few packets spreads them over all waves
-    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
-    const int fblocks = (int)std::min<uint64_t>(pblocks, (t_max + 4 * A.lanes - 1) / (4 * A.lanes));
-    A.slab = g->dev.geom == 1 && mode == MCRT_MODE_ALBEDO && !p->contrib && !npix && !gs && p->absorption != 1 &&
-             p->cloud_phase != 2 && p->forced == 0 && !(p->surface_albedo > 0.0);
-    if (!A.slab && (rc = split_scratch(ctx, sl, st, p->graph != 0, t_max, no, mixed, fblocks, Q))) return rc;
-    const bool split = Q.rec != nullptr;
+    A.lanes = flight_lanes(t_max, pblocks);
+    const int fblocks = flight_blocks(t_max, pblocks);
+    A.slab = slab;
+    if (split && (rc = split_scratch(ctx, sl, st, t_max, no, mixed, fblocks, Q))) return rc;
+    split = Q.rec != nullptr;
     A.head = Q.head;
     A.peel_cross = Q.peel_cross;
     if ((split || A.slab) && A.lanes < 64) A.batch = A.lanes;
@@ -1787,21 +1831,27 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
             for (int g = 0; g < I.pl.ng; ++g) fl.push_back(Flat{q, (int)s, g, by});
     }
     const int nsolve = (int)fl.size();
+    const int bpc = common->tune_blocks_per_cu > 0 ? common->tune_blocks_per_cu : 4;
+    const int pblocks = ctx->n_cu * bpc;
     uint64_t room;  // (spare scratch gives way)
     {
         std::lock_guard<std::mutex> mk(ctx->mem_mu);
         const uint64_t held = held_locked(ctx), spare = spare_bytes(sl);
         room = ctx->budget - std::min(ctx->budget, held - std::min(held, spare));
     }
-    const uint64_t cap = std::min<uint64_t>(room / 2, 24ULL << 30);
+    uint64_t cap = room / 2, most = 0;
+    for (auto& f : fl) most += it[f.item]->p.n_packets;
+    bool split = split_fits(sl, common->graph != 0, room, most, no, mixed, pblocks, cap);
+    cap = std::min<uint64_t>(cap, 24ULL << 30);
     // launches: consecutive solves while the footprint fits (and <= max_batch)
     std::vector<std::pair<int, int>> launches;
     for (int s0 = 0; s0 < nsolve;) {
         uint64_t acc = 0;
         int s1 = s0;
-        while (s1 < nsolve && (s1 == s0 || acc + fl[s1].bytes <= cap) && s1 - s0 < kMaxSolvesPerLaunch &&
+        auto bytes = [&](int s) { return fl[s].bytes + (split ? it[fl[s].item]->p.n_packets * kSplitPacketBytes : 0); };
+        while (s1 < nsolve && (s1 == s0 || acc + bytes(s1) <= cap) && s1 - s0 < kMaxSolvesPerLaunch &&
                (common->max_batch <= 0 || s1 - s0 < common->max_batch)) {
-            acc += fl[s1].bytes;
+            acc += bytes(s1);
             ++s1;
         }
         launches.push_back({s0, s1});
@@ -1863,8 +1913,6 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
     A.forced_first = common->forced_first;
     A.surface_albedo = common->surface_albedo;
     A.peel_w = 1.0;
-    const int bpc = common->tune_blocks_per_cu > 0 ? common->tune_blocks_per_cu : 4;
-    const int pblocks = ctx->n_cu * bpc;
     uint64_t t_max = 1;  // packets of a launch
     for (auto& L : launches) {
         uint64_t t = 0;
@@ -1872,11 +1920,10 @@ int solve_batch(mcrt_ctx* ctx, Slot& sl, hipStream_t def_stream, int n_items, co
         t_max = std::max(t_max, t);
     }
     PeelArgs Q{};
-    // a split launch of few packets spreads them over all waves
-    A.lanes = (int)std::max<uint64_t>(1, std::min<uint64_t>(64, t_max / ((uint64_t)pblocks * 4)));
-    const int fblocks = (int)std::min<uint64_t>(pblocks, (t_max + 4 * A.lanes - 1) / (4 * A.lanes));
-    if ((rc = split_scratch(ctx, sl, st, common->graph != 0, t_max, no, mixed, fblocks, Q))) return rc;
-    const bool split = Q.rec != nullptr;
+    A.lanes = flight_lanes(t_max, pblocks);
+    const int fblocks = flight_blocks(t_max, pblocks);
+    if (split && (rc = split_scratch(ctx, sl, st, t_max, no, mixed, fblocks, Q))) return rc;
+    split = Q.rec != nullptr;
     A.head = Q.head;
     A.peel_cross = Q.peel_cross;
     if (split && A.lanes < 64) A.batch = A.lanes;

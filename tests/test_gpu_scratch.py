@@ -175,3 +175,32 @@ def test_batch_launches_do_not_depend_on_kept_records(torch_dev):
     assert res[0][0]["kernel_launches"] == res[1][0]["kernel_launches"] == 1
     for a, b in zip(*res):
         assert np.array_equal(a["sums"], b["sums"])
+
+
+@pytest.mark.parametrize("batched", [False, True])
+@pytest.mark.parametrize("room_mb,n", [(120, 4000), (800, 30000)])  # records of 91 MB and 480 MB
+def test_packet_solves_leave_half_of_the_room(torch_dev, batched, room_mb, n):
+    """Packet solves hold at most half of what the budget leaves (and their
+    tallies), records included, so that uploads and served requests find room
+    while one runs; the sums do not depend on it."""
+    print(f"packets in half of {room_mb} MB, batched {batched}", flush=True)
+    from paper_2110_15640_amd import mcrt as M
+    grid, table, _ = I.make_emission_3d(16, 8, 10, nband=8, ng=1)
+    args = dict(obs_phase=[0.3, 0.6], seed=1)
+
+    def solve(ctx):
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        held = ctx.memory_in_use
+        if batched:
+            out = ctx.solve_batch([dict(mode="emission", gid=gid, oid=oid, table=table, n_packets=n)], **args)[0]
+        else:
+            out = ctx.solve_emission(gid, oid, table, n_packets=n, **args)
+        return held, ctx.memory_in_use - held, out
+
+    with M.Context(0) as ctx:
+        resident, _, ref = solve(ctx)
+    with M.Context(0, hbm_budget_bytes=resident + (room_mb << 20)) as ctx:
+        _, kept, out = solve(ctx)
+    tallies = 8 * 20 * 8 * (2 + n // 4096) + (1 << 20)
+    assert kept <= (room_mb << 19) + tallies
+    assert np.array_equal(out["sums"], ref["sums"])
