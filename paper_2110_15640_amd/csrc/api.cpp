@@ -2252,10 +2252,10 @@ uint64_t estimate_bytes(mcrt_ctx* ctx, const Request& r, GridRes* g, OpacRes* op
     if (r.p.g_sampling) batch = std::max<uint64_t>(r.ng, batch / r.ng * r.ng);  // whole bands, as the solve rounds
     const uint64_t chunks = (uint64_t)reduce_rows_chunks(N);
     uint64_t b = opt_b * batch + row_b * batch + nsolve * row_w * 8 + batch * chunks * pw * 8 +
-                 batch * (sizeof(SolveDev) + sizeof(PrepSlot)) + 8 * kXcds * kCtrStride;
+                 batch * (sizeof(SolveDev) + sizeof(PrepSlot)) + 64;
     if (r.mode == MCRT_MODE_EMISSION) b += src_b * batch + prep_scratch_doubles((int)ncell, (int)batch) * 8;
     if (op->kind == MCRT_OPAC_HIRES) b += ncell * 8;
-    return b + (1ULL << 20);
+    return b + (1ULL << 20);  // (the dispensers' 2 KB and what rounding to 256 bytes adds are in this)
 }
 
 void worker_main(mcrt_ctx* ctx, Slot* sl)

@@ -82,8 +82,8 @@ def test_chords_in_little_scratch(torch_dev, kind, shape, nrow, n_b, n_alpha, pr
         assert np.array_equal(got["sums"], ref["sums"]) and got["n_segments"] == ref["n_segments"], extra
 
 
-def _needs(grid, table, **kw):
-    """What a served transmission says it needs, where the budget has nothing left."""
+def _needs(grid, table, mode="transmission", **kw):
+    """What a served request says it needs, where the budget has nothing left."""
     from paper_2110_15640_amd import mcrt as M
     with M.Context(0) as ctx:
         ctx.upload_grid(grid), ctx.upload_opacity(table)
@@ -91,7 +91,7 @@ def _needs(grid, table, **kw):
     with M.Context(0, hbm_budget_bytes=resident) as ctx:
         gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
         with pytest.raises(M.McrtError) as e:
-            ctx.submit("transmission", gid, oid, table, **kw)
+            ctx.submit(mode, gid, oid, table, **kw)
     assert e.value.name == "EBUDGET"
     return resident, int(str(e.value).split("needs ")[1].split()[0])
 
@@ -204,3 +204,33 @@ def test_packet_solves_leave_half_of_the_room(torch_dev, batched, room_mb, n):
     tallies = 8 * 20 * 8 * (2 + n // 4096) + (1 << 20)
     assert kept <= (room_mb << 19) + tallies
     assert np.array_equal(out["sums"], ref["sums"])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_served_packets_need_what_they_did(torch_dev, precision):
+    """Admission of a served emission request: optics (and their FP32 copies),
+    sources, packet rows, tallies, solve tables, scan scratch, and 1 MB in which
+    the small arrays lie; what it then holds is no more."""
+    print(f"served packets and their scratch: {precision}", flush=True)
+    from paper_2110_15640_amd import mcrt as M
+    grid, table, _ = I.make_emission_3d(16, 8, 10, nband=3, ng=2)
+    n, ncell, ns, no = 5000, 1280, 6, 1
+    mixed = precision == "mixed"
+    kw = dict(n_packets=n, obs_phase=[0.3], seed=2, max_batch=1, precision=M.MCRT_MIXED if mixed else M.MCRT_FP64)
+    resident, est = _needs(grid, table, mode="emission", **kw)
+    arrays = ncell * (40 + (20 if mixed else 0) + 16) + n * (no + 11) * 8 + ns * (2 * no + 13) * 8 + \
+        -(-n // 4096) * (2 * no + 11) * 8
+    tables = 256 + 64  # 160 and 72 bytes a solve
+    scan = 8 * (2 * -(-ncell // 256) + -(-ncell // 2048) + 16)
+    assert arrays < est <= arrays + tables + scan + (1 << 20)
+    with M.Context(0) as ctx:
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        ref = ctx.solve_emission(gid, oid, table, **kw)
+    with M.Context(0, hbm_budget_bytes=resident + est) as ctx:
+        ctx.serve_config(1)
+        gid, oid = ctx.upload_grid(grid), ctx.upload_opacity(table)
+        ticket, peak = ctx.submit("emission", gid, oid, table, **kw), 0
+        while not ctx.poll(ticket):
+            peak = max(peak, ctx.memory_in_use)
+        assert np.array_equal(ctx.wait(ticket)["sums"], ref["sums"])
+    assert peak <= resident + est
