@@ -427,11 +427,7 @@ __host__ __device__ __forceinline__ ConePick wk_cone_pick(const Walker& w, doubl
     const double M = fma(Pz, Pz, (q2 * w.dz) * w.dz);
     const double sf = up ? su : sl, sb = up ? sl : su;  // the edges in front and behind
     const double mz = wk_flip(w.dz, dj);
-    // the extremum is ahead.  |Pz| <= |P|; of a line through the centre both are
-    // noise and q2 may come out negative: no extremum then (and no pole is
-    // picked: Pz^2 + q2 (dz^2 - 4) < 0)
-    const bool off = fma(Pz, Pz, -(q2 + q2)) <= 0.0, toward = wk_flip(Pz, dj) > 0.0;
-    const bool turn = off & toward;
+    const bool turn = wk_flip(Pz, dj) > 0.0;  // the extremum is ahead
     const double reach = turn ? fma(-(sf * sf), q2, M) : mz - wk_flip(sf, dj);
     const bool front = reach > 0.0;
     const bool back = !front & turn & (mz < wk_flip(sb, dj));
@@ -531,7 +527,6 @@ __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, d
     const double B = px * dx + py * dy + pz * dz;
     const double C0 = px * px + py * py + pz * pz;
     w.B0 = B;
-    w.C0 = C0;
     // the inner sphere where the walk goes inward and meets it, else the outer one
     const double Ci = wk_mad<FAST>(-fr.x, fr.x, C0), Di = wk_mad<FAST>(B, B, -Ci);
     const double Co = wk_mad<FAST>(-fr.y, fr.y, C0), Do = wk_mad<FAST>(B, B, -Co);
@@ -543,7 +538,13 @@ __host__ __device__ __forceinline__ void wk_start(const GridDev& g, Walker& w, d
     w.far = q;
     w.dk = inward ? -1 : 1;
     w.di = east ? 1 : -1;
-    const double q2 = fma(-B, B, C0), Pz = fma(-B, dz, pz);
+    // q2 >= Pz^2, but of a line through the centre both are rounding noise (some
+    // 1e-15 |p0|^2) and q2 would come out negative as often as not, which puts
+    // edges within reach, the poles among them.  Such a line is taken to pass the
+    // centre at 1e-7 |p0|: with Pz^2 <= 2 q2 no pole is ever picked
+    // (Pz^2 + q2 (dz^2 - 4) < 0).
+    w.C0 = wk_max(C0, fma(B, B, 1e-14 * C0));
+    const double q2 = fma(-B, B, w.C0), Pz = fma(-B, dz, pz);
     // (rising or falling: the sign of d sin(lat) / dt)
     const ConePick p = wk_cone_pick(w, q2, Pz, fma(dz, q2, -(Pz * B)) > 0.0 ? 1 : -1, fc.x, fc.y);
     w.dj = p.upper ? 1 : -1;
