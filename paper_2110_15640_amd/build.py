@@ -22,8 +22,10 @@ HIPFLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contrac
 
 # The transport kernels' loops hold rare code (sampling, births, phase
 # functions) whose many FP64 constants the machine-level loop-invariant motion
-# would keep in registers throughout: 117 instead of 91 VGPRs in the mixed
-# form, 128 with 26 spilled instead of 111 in the FP64 form.
+# would keep in registers throughout: of the one-kernel transport 127 VGPRs and
+# 4 spilled in place of 101 in the mixed form, 128 and 34 spilled in place of 119
+# in the FP64 form; of the flights 128 and 3 in place of 107, 128 and 14 in place
+# of 125.
 SOURCE_FLAGS = {s: ["-mllvm", "-disable-machine-licm"] for s in ("transport.hip", "flight.hip")}
 
 

@@ -2510,11 +2510,10 @@ int grid_upload(mcrt_ctx* ctx, const mcrt_grid_desc* d, hipStream_t st, int32_t*
         std::copy(d->lat_edges, d->lat_edges + nlat + 1, lat.begin());
         std::copy(d->lon_edges, d->lon_edges + nlon + 1, lon.begin());
     }
-    std::vector<double> lc2(nlat + 1), ls2(nlat + 1), lsn(nlat + 1), los(nlon), loc(nlon), volr(nlay);
+    std::vector<double> lc2(nlat + 1), lsn(nlat + 1), los(nlon), loc(nlon), volr(nlay);
     for (int e = 0; e <= nlat; ++e) {
         double c = std::cos(lat[e]), s = std::sin(lat[e]);
         lc2[e] = c * c;
-        ls2[e] = s * s;
         lsn[e] = s;
     }
     for (int e = 0; e < nlon; ++e) {
@@ -2548,11 +2547,8 @@ int grid_upload(mcrt_ctx* ctx, const mcrt_grid_desc* d, hipStream_t st, int32_t*
     UP(r, d->r_edges, (size_t)nlay + 1, dp);
     UP(lat, lat.data(), lat.size(), dp);
     UP(lat_c2, lc2.data(), lc2.size(), dp);
-    UP(lat_s2, ls2.data(), ls2.size(), dp);
     UP(lat_sin, lsn.data(), lsn.size(), dp);
     UP(lon, lon.data(), lon.size(), dp);
-    UP(lon_s, los.data(), los.size(), dp);
-    UP(lon_c, loc.data(), loc.size(), dp);
     UP(vol_r, volr.data(), volr.size(), dp);
     std::vector<double2> faces;
     faces.reserve((size_t)nlay + nlat + nlon + 1);

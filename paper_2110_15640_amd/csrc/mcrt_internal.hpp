@@ -22,11 +22,8 @@ struct GridDev {
     const double* r;       // [nlay+1]
     const double* lat;     // [nlat+1]
     const double* lat_c2;  // cos^2(lat edge)
-    const double* lat_s2;  // sin^2(lat edge)
     const double* lat_sin; // sin(lat edge)
     const double* lon;     // [nlon+1]
-    const double* lon_s;   // sin(lon edge) [nlon]
-    const double* lon_c;   // cos(lon edge) [nlon]
     const double* vol_r;   // (r_{k+1}^3 - r_k^3)/3 [nlay]
     // the edge values a crossing reads, in one array so that one base and a
     // per-lane offset reach any of them with one 16-byte load: the layer's

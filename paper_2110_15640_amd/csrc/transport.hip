@@ -566,9 +566,9 @@ __device__ __forceinline__ int birth(Lane& L, const BatchArgs& A)
     return A_PEEL;
 }
 
-// Registers: 91 VGPRs (mixed) or 111 (FP64), the extended forms up to 116, so
-// four blocks of four waves are resident per CU, five in the mixed form when
-// the peel-off sums (dynamic LDS, n_out * 256 doubles) leave room.
+// Registers: 101 VGPRs (mixed) or 119 (FP64; on several grids 103 and 121), the
+// extended forms 116 to 125, none spilled, so four blocks of four waves are
+// resident per CU.
 template <bool MIXED, bool MULTI, bool EXT>
 __global__ void __launch_bounds__(kTPB, 4) k_transport_persistent(GridDev g1, BatchArgs A)
 {
