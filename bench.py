@@ -46,50 +46,46 @@ PEAK_HBM = 8000.0  # GB/s
 # 256 CUs x 4 SIMDs at 2.4 GHz (the same unit counts give 78.6 FP64 TFLOP/s)
 PEAK_VALU_WAVE_INSTS = 256 * 4 * 2.4e9 / 4.0  # wave-level VALU instructions per second
 
-# HBM traffic of the transport kernel from two rocprofv3 counter passes
-# (FETCH_SIZE, WRITE_SIZE, each scaled by what it reads for a 1 GiB copy) and
-# its VALU busy fraction, measured on one launch configuration of this
-# workload.  Reported only while the kernel sources hash to `sha` and the run
-# matches that configuration (grid, packets per solve, observers, launch
-# shape, solves per launch); otherwise null.
+# HBM traffic and VALU instructions of the transport's kernels (flights, rays,
+# the records' sums) from rocprofv3 counter passes (FETCH_SIZE and WRITE_SIZE
+# each scaled by what they read for a 1 GiB copy), at launch configurations that
+# the autotuner picks for this workload.  Reported only while the kernels'
+# sources hash to `sha` and the run matches the configuration (grid, packets per
+# solve, observers, launch shape, solves per launch); otherwise null.
 def _traffic(fetch_kib, write_kib, copy_fetch_kib, copy_write_kib):
     """HBM bytes from FETCH_SIZE / WRITE_SIZE (KiB per dispatch), each scaled
     by what it reads for a 1 GiB device copy (1,048,576 KiB each way)."""
     return (fetch_kib * 1048576.0 / copy_fetch_kib + write_kib * 1048576.0 / copy_write_kib) * 1024.0
 
 
-def _busy(active_valu, wave_cycles, waves_per_simd=4):
-    """SQ_ACTIVE_INST_VALU per wave cycle times the waves sharing a SIMD: the
-    share of SIMD cycles with a VALU instruction in flight (about 1 when the
-    SIMDs issue VALU work every cycle; FP64 instructions that occupy a SIMD
-    for more than one cycle can take it slightly past 1)."""
-    return active_valu / wave_cycles * waves_per_simd
+def _shape(fetch_kib, write_kib, valu_insts):
+    return {"bytes_per_launch": _traffic(fetch_kib, write_kib, 524593.0, 1.04872e6), "valu_insts": valu_insts}
 
 
 K4_PROFILE = {
-    "sha": "672340fea5202d167d0d2aa733b7075f8f01962dfdbd22a013706e8becd4c134",
+    "sha": "4be0733618e037ac0d9a3d4e2710792f5907cd0d31093cb3a52855983b700dda",
     "grid": [128, 64, 50], "packets_per_solve": 1000000, "n_obs": 4, "solves_per_launch": 800,
-    # per event threshold (4 blocks per compute unit, wave batch 32): bytes, VALU busy and
-    # wave-level VALU instructions (SQ_INSTS_VALU) per launch
+    # per (event threshold, wave batch) at 4 blocks per compute unit: FETCH_SIZE and WRITE_SIZE (KiB)
+    # and wave-level VALU instructions (SQ_INSTS_VALU) of a launch's 118 rounds
     "shapes": {
-        20: {"bytes_per_launch": _traffic(1.31076e8, 1.18905e8, 524343, 1.04859e6),
-             "valu_busy": _busy(1.61723e12, 6.51007e12), "valu_insts": 1.57343e12},
-        24: {"bytes_per_launch": _traffic(2.61871e8 / 2, 2.3786e8 / 2, 524343, 1.04859e6),
-             "valu_busy": _busy(3.19614e12, 1.28055e13), "valu_insts": 3.1132e12 / 2},
-        28: {"bytes_per_launch": _traffic(1.30884e8, 1.18958e8, 524343, 1.04859e6),
-             "valu_busy": _busy(1.60599e12, 6.41207e12), "valu_insts": 1.5658e12},
-        32: {"bytes_per_launch": _traffic(1.31367e8, 1.18989e8, 524343, 1.04859e6),
-             "valu_busy": _busy(1.6346e12, 6.50642e12), "valu_insts": 1.59495e12},
+        (20, 32): _shape(8.21749e+08, 6.06536e+08, 6.29446e+11),
+        (24, 32): _shape(8.03435e+08, 6.04676e+08, 6.19887e+11),
+        (28, 32): _shape(7.69684e+08, 6.03072e+08, 6.13336e+11),
+        (32, 32): _shape(7.99120e+08, 6.01398e+08, 6.09073e+11),
+        (20, 128): _shape(7.73871e+08, 6.08667e+08, 6.28623e+11),
+        (24, 128): _shape(7.60887e+08, 6.06005e+08, 6.19064e+11),
+        (28, 128): _shape(7.38981e+08, 6.04514e+08, 6.12510e+11),
+        (32, 128): _shape(7.74768e+08, 6.04062e+08, 6.08241e+11),
     },
 }
-# The same for the chord optical-depth kernel of the transmission solve: bytes
-# per (chord segment, wavelength) over its launches.
+# The same for the chord groups' optical depths of the transmission solve: bytes
+# per (chord segment, wavelength) over their launches.
 K5_PROFILE = {
-    "sha": "0eb2314978dcf52aae2f8960283e4800abb4b033705255706a7519cf7c401028",
+    "sha": "13bc7e47675bbecbf5dde9dbd43b15d5f50074d7d2fc381212ed077e4b206ca3",
     "n_segments": 7861278, "n_lambda": 20000,
-    # per precision (1 mixed: FP32 rows; 0 FP64), over 314 launches of 64 wavelengths (20,064)
-    "bytes_per_seg_wl": {1: _traffic(1.88063e8, 902880, 524722, 1.04923e6) / (7861278 * 20064),
-                         0: _traffic(4.72339e8, 902880, 524722, 1.04923e6) / (7861278 * 20064)},
+    # per form, over 314 launches of 64 wavelengths (a warm-up block and the spectrum, 20,064)
+    "bytes_per_seg_wl": {"mixed": _traffic(3.05488e7, 1.87524e6, 524717, 1.04922e6) / (7861278 * 20064),
+                         "fp64": _traffic(6.20106e7, 2.05014e6, 524717, 1.04922e6) / (7861278 * 20064)},
 }
 
 
@@ -125,12 +121,12 @@ def parse():
     return ap.parse_args()
 
 
-def kernel_sha(main: str = "transport.hip") -> str:
-    """sha256 of a kernel's sources (its file, then the shared headers)."""
+def kernel_sha(*files: str) -> str:
+    """sha256 of a kernel's sources (its file, then the headers it shares)."""
     import hashlib
     d = os.path.join(ROOT, "paper_2110_15640_amd", "csrc")
     h = hashlib.sha256()
-    for f in (main, "device_common.hpp", "mcrt_internal.hpp"):
+    for f in files + ("device_common.hpp", "mcrt_internal.hpp"):
         h.update(open(os.path.join(d, f), "rb").read())
     return h.hexdigest()
 
@@ -213,6 +209,8 @@ def transmission_leg(M, I):
             # the optical depths (the tallies' sums with them)
             nseg, nl, nblk = r["n_segments"], table.nlam, r["kernel_launches"]
             k5_tflops = 2.0 * nseg * nl / (r["kernel_ms"] * 1e-3) / 1e12
+            P = K5_PROFILE
+            same = kernel_sha("chords.hip") == P["sha"] and nseg == P["n_segments"] and nl == P["n_lambda"]
             out[name] = {"ms": wall * 1e3, "chord_wavelengths_per_s": nch * nl / wall,
                          "chord_tau_kernel_ms": r["kernel_ms"], "chord_tau_launches": nblk, "segments": nseg,
                          # the extinction of one launch's rows is formed while the previous launch's
@@ -222,7 +220,10 @@ def transmission_leg(M, I):
                          "roofline": {"bound": "alu",
                                       "kernel": f"k_group_tau<{'float' if prec == M.MCRT_MIXED else 'double'}>",
                                       "achieved": k5_tflops, "peak": PEAK_FP64_VECTOR, "unit": "TFLOP/s",
-                                      "frac": k5_tflops / PEAK_FP64_VECTOR, "traffic": None}}
+                                      "frac": k5_tflops / PEAK_FP64_VECTOR,
+                                      "traffic": (P["bytes_per_seg_wl"][name] * nseg * nl / max(nblk, 1)
+                                                  if same else None),
+                                      "traffic_unit": "bytes per launch (mean)"}}
         depth = res["mixed"]["value"][:, 0]
         d64 = res["fp64"]["value"][:, 0]
         excess = np.abs(res["mixed"]["sums"][..., 0] - res["fp64"]["sums"][..., 0]) / \
@@ -435,10 +436,10 @@ def main():
     k4_bytes = cross * ALPHA_BYTES_MIXED + nint * OMEGA_PGAS_BYTES + pk_step * a.steps * probes * CDF_PROBE_BYTES
     k4_gbps = k4_bytes / ksec / 1e9
     P = K4_PROFILE
-    shape = P["shapes"].get(tune.get("tune_ev_threshold")) if (
-        tune.get("tune_blocks_per_cu") == 4 and tune.get("tune_wave_batch") == 32) else None
-    same_run = (shape is not None and kernel_sha() == P["sha"] and [grid.nlon, grid.nlat, grid.nlay] == P["grid"]
-                and npk == P["packets_per_solve"] and len(phases) == P["n_obs"]
+    shape = P["shapes"].get((tune.get("tune_ev_threshold"), tune.get("tune_wave_batch"))) if (
+        tune.get("tune_blocks_per_cu") == 4) else None
+    same_run = (shape is not None and kernel_sha("flight.hip", "transport_common.hpp") == P["sha"]
+                and [grid.nlon, grid.nlat, grid.nlay] == P["grid"] and npk == P["packets_per_solve"] and len(phases) == P["n_obs"]
                 and abs(solves_per_launch - P["solves_per_launch"]) < 1e-9)
     traffic = shape["bytes_per_launch"] if same_run else None
     avg_s = ksec / max(launches, 1)
@@ -467,7 +468,6 @@ def main():
                      "hbm_algorithmic_GBps": k4_gbps, "hbm_frac": k4_gbps / PEAK_HBM,
                      "hbm_algorithmic_bytes": k4_bytes,
                      "traffic_GBps": None if traffic is None else traffic / avg_s / 1e9,
-                     "valu_busy": shape["valu_busy"] if same_run else None,
                      # the issue roofline: wave-level VALU instructions per second (profiled
                      # count per launch over this run's launch time) against the VALU peak
                      "valu_insts_per_s": shape["valu_insts"] / avg_s if same_run else None,

@@ -504,8 +504,8 @@ struct __attribute__((aligned(sizeof(R) * NB))) RowVec {
 // small enough for eight waves a SIMD: a group has few cells (some 200, at the
 // poles 800) and the time goes on waiting for their rows.  Of a 128 x 64 x 60
 // grid's 256 x 360 chords and 64 rows in FP32 the matrix instructions alone are
-// 33 us, and the kernel takes 65 to 70 (a wave per segment's row, without
-// groups: 420).  One or four blocks a wave instead of two, and four waves that
+// 34 us, and the kernel takes 88 (a wave per segment's row, without groups:
+// 420).  One or four blocks a wave instead of two, and four waves that
 // share a group's cells, are 10 to 15 % slower there; twice the loads in flight
 // are no faster.
 template <typename R, int NB>
